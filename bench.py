@@ -79,7 +79,7 @@ def workload(name):
 def phase_bytes(w, ms, launches):
     """Algorithmic bytes per launch of each kernel phase: one read of every
     field element a launch needs and one write of every element it produces,
-    per cell; for the binomial passes, the mean over the passes of a step."""
+    per cell."""
     cfg = w["cfg"]
     N = cfg["nx"] * cfg["ny"] * cfg["nz"]
     d = 2 if cfg["lattice"] == 0 else 3
@@ -87,32 +87,21 @@ def phase_bytes(w, ms, launches):
     Q = 9 if d == 2 else 19
     e = 8 if w["precision"] == "fp64" else 4
     to = w["qois"] is not None
-    jv = jw = 0
-    has_z = False
+    ne = nz = mp = 0
     if to:
-        deg = {"I": 0, "B": 1, "B2": 2, "BMID": 2, "IMB": 1}
-        jv = max([2 * deg[f] for k, f, _ in w["qois"] if k == "E"] + [0])
-        jw = max([2 * deg[f] for k, f, _ in w["qois"] if k == "Z"] + [0])
-        has_z = any(k == "Z" for k, _, _ in w["qois"])
-    npass = max(jv, max(jw, 1) if has_z else 0)
-    binom = 0
-    for j in range(1, npass + 1):
-        dov, dow = j <= jv, has_z and j <= jw
-        if j == 1:   # v* in; B v*, w and (jw >= 1) B w, curl^T w out
-            binom += d + (d if dov else 0) + (nc if has_z else 0) + ((nc + d) if dow else 0)
-        else:        # B^(j-1) v, B^(j-1) w in; B^j v, B^j w, curl^T B^(j-1) w out
-            binom += (d if dov else 0) * 2 + (nc if dow else 0) * 2 + (d if dow else 0)
-    binom = binom / npass if npass else 0
-    wz = (min(jw, 2) + 1) * nc if has_z else 0   # W_0..W_2 read for the Z QoI densities
-    cz = jw * d + nc if has_z else 0             # C_0..C_jw-1, and W_jw for the top curl
+        ne = sum(k == "E" for k, _, _ in w["qois"])
+        nz = sum(k == "Z" for k, _, _ in w["qois"])
+        mp = any(k == "MP" for k, _, _ in w["qois"])
     per_cell = {
         # populations in and out, rho and v* out, and the SGS record (2d) in
         "stream_collide": e * (2 * Q + ((1 + d) + 2 * d if to else 0)),
         "curl": 0,
-        "binomial": e * binom,
-        "reduce": e * (d + jv * d + wz + cz),
-        # v*, P_j, C_j, W_jw and rho in; the record (rho dv, 2 v* + dv) out
-        "apply": e * (d + jv * d + cz + 1 + 2 * d),
+        # v* in; the E sensitivities and R R w of the Z QoIs out
+        "binomial": e * (d + ne * d + nz * nc),
+        # E sensitivities, R R w and v*_x in; the Z sensitivities out
+        "reduce": e * (ne * d + nz * nc + (1 if mp else 0) + nz * d),
+        # v*, rho and every sensitivity in; the record (rho dv, 2 v* + dv) out
+        "apply": e * (d + 1 + (ne + nz) * d + 2 * d),
         "solve": 0,
     }
     return {k: per_cell[k] * N for k in per_cell}

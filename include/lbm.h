@@ -79,9 +79,9 @@ typedef struct {
     int diag;           /* plain runs: 1 records mass, momentum, E and Z of the
                            post-streaming velocity every step */
     int rec_cap;        /* capacity of the per-step record ring (0: 4096) */
-    int tune_zc;        /* tuning: z planes per binomial-filter workgroup (0: automatic) */
+    int tune_zc;        /* tuning: z planes per workgroup of the tiled stream-collide (0: automatic) */
     int tune_cpt;       /* tuning: cells per thread of the QoI reduction (0: automatic) */
-    int tune_btx;       /* tuning: binomial tile width, 32 or 64 (0: automatic; 64 needs a
+    int tune_btx;       /* tuning: its tile width, 32 or 64 (0: automatic; 64 needs a
                            D3Q19 grid; bitwise the same result either way) */
     int tune_mem;       /* memory-access variant of the step (0: automatic by size): bit 0
                            forces 64-bit population offsets, bit 1 non-temporal population
@@ -320,8 +320,8 @@ int lbm_set_state(lbm_ctx* ctx, const void* host, size_t bytes);
 
 
 /* Autotuner of the launch shapes (the tune_* fields of lbm_config): the
- * binomial tile width, the z planes per binomial workgroup and the cells
- * per thread of the QoI reduction.  Candidates are timed on a scratch
+ * tile width and z planes per workgroup of the tiled stream-collide and the
+ * cells per thread of the reduction.  Candidates are timed on a scratch
  * context in dev_arena (caller-owned, 256-byte aligned, at least
  * lbm_autotune_bytes(cfg, closure) bytes; its contents are overwritten),
  * each for `steps` steps after a warm-up, started from a small seeded
@@ -411,7 +411,7 @@ void lbm_server_destroy(lbm_server* s);
 /* Per-phase timing for measurement: runs nsteps steps eagerly on the context
  * stream with HIP events between the kernel phases and returns the mean
  * duration per step of each phase in ms[6]: stream-collide (with the WALE
- * moments pass), curl, filters (binomial powers, or the kernel-filter pass
+ * moments pass), curl, filters (binomial chains, or the kernel-filter pass
  * program), reduce, cross-block sums and solve, apply (plain runs with
  * records: their diagnostics in the last slot); launches[6] (nullable)
  * receives the kernel launches per step of each phase.  Advances the run. */

@@ -42,6 +42,7 @@ int fail(int code, const char* fmt, ...)
     } while (0)
 
 constexpr size_t kAlign = 256;
+constexpr int kCus = 256;   // compute units of an MI355X
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 int filter_deg(int f) { return f == LBM_FILT_ID ? 0 : (f == LBM_FILT_B || f == LBM_FILT_IMB ? 1 : 2); }
@@ -63,6 +64,7 @@ struct ClosureShape {
     int nq = 0, nsa = 0, nmp = 0, jv = 0, jw = 0, has_z = 0, has_e = 0, nbands = 0;
     int h = 0, nhc = 0;   // LRS history length; k_sum workgroups of its product
     int kf = 0;           // E/Z QoIs use the kernel filters (materialised sensitivities)
+    int nzb = 0;          // Z QoIs
     int kslots = 0, nzq = 0;   // kernel filters: separable terms over the QoIs; Z QoIs
     int nf = 0, nfz = 0;       // Fourier band QoIs; of them Z QoIs
     int npart() const { return nsa + nsa * (nsa + 1) / 2 + nmp * (1 + nsa); }
@@ -128,7 +130,7 @@ int closure_shape(const lbm_config* cfg, const lbm_closure* cl, ClosureShape* ou
         if (q.kind == LBM_QOI_E || q.kind == LBM_QOI_Z) {
             const int p = s.kf ? 0 : 2 * filter_deg(q.filter);
             if (q.kind == LBM_QOI_E) { s.jv = std::max(s.jv, p); s.has_e = 1; }
-            else { s.jw = std::max(s.jw, p); s.has_z = 1; }
+            else { s.jw = std::max(s.jw, p); s.has_z = 1; s.nzb++; }
             s.nsa++;
         } else if (q.kind == LBM_QOI_MP) {
             if (!cfg->walls_y) return fail(LBM_EINVAL, "closure: mean-profile QoIs need walls_y = 1");
@@ -170,13 +172,49 @@ int check_config(const lbm_config* c)
 
 struct Plan {
     size_t member, param, ctl, recs, g0, g1, fprof, vn, part_stats, part_diag, work1, workp, workm;
-    size_t rho, vs, P, W, Cf, rec, part_to, bandw, cmp, workr, workb, sums, works, hpart, kV, kT, ktaps, kjobs;
+    size_t rho, vs, W, rec, part_to, part_q, bandw, cmp, workr, workb, workc, sums, works, hpart, kV, kT, ktaps, kjobs;
     size_t fspec_v, fspec_w, fband_e, fband_z;
     size_t total;
     int N, D, NC, Q, esz, nb1, nbp, nbx2, cpt2, nbr, nbb, nbs, zc, btx, rec_cap;
+    int cnl, cvx, cvy, czc, cntx, cnty, cnt, nbc;   // filter chains: powers, tile, tiles in x and y and in all, workgroups
     size_t popn;   // elements of one population buffer: Q * N rounded up to whole blocks of kPopBlk cells
     ClosureShape cap;
 };
+
+// Tiles of the filter chains (k_chain).  A wavefront's 64 lanes hold a tile's
+// cells in x and a halo of H = powers on each side; the workgroup's rows
+// hold its cells in y and the same halo, except at a wall, beyond which rows
+// are zero anyway.  Tiles are evened out over the grid.
+void chain_tiles(const lbm_config* c, Plan* P)
+{
+    const int H = P->cnl, NR = chain_waves(P->D) * chain_rows(P->D, P->esz);
+    const int vx = 64 - 2 * H, vy = NR - 2 * H;
+    P->cntx = (c->nx + vx - 1) / vx;
+    P->cvx = (c->nx + P->cntx - 1) / P->cntx;
+    P->cntx = (c->nx + P->cvx - 1) / P->cvx;
+    if (c->walls_y && c->ny <= NR) P->cnty = 1;
+    else if (c->walls_y && c->ny <= 2 * (NR - H)) P->cnty = 2;
+    else P->cnty = (c->ny + vy - 1) / vy;
+    P->cvy = (c->ny + P->cnty - 1) / P->cnty;
+    P->cnty = (c->ny + P->cvy - 1) / P->cvy;
+    const int nxy = P->cntx * P->cnty;
+    P->czc = 1;
+    if (P->D == 3) {
+        // z chunk: the fewest rounds of workgroups over the CUs (one per CU)
+        // times a workgroup's planes, taken in pairs, and about ten planes'
+        // time to start and end (measured on MI355X, whole phase: 96 x 48 x 48
+        // with chunks of 3, 4, 5, 6, 8 planes 37, 37, 26, 27, 30 us; 384 x 192
+        // x 192 with 32, 48, 64 planes 540, 571, 515 us)
+        double best = 0;
+        for (int zc = 1; zc <= c->nz; ++zc) {
+            const int wgs = nxy * ((c->nz + zc - 1) / zc) * (P->D + P->NC);
+            const double cost = (double)((wgs + kCus - 1) / kCus) * ((zc + 2 * P->cnl + 1) / 2 * 2 + 10);
+            if (zc == 1 || cost < best) { best = cost; P->czc = zc; }
+        }
+    }
+    P->cnt = nxy * (P->D == 3 ? (c->nz + P->czc - 1) / P->czc : 1);
+    P->nbc = P->cnt * (P->D + P->NC);
+}
 
 void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
 {
@@ -232,9 +270,12 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
     if (cs.nq > 0) {
         P.rho = take(e * N);
         P.vs = take(e * P.D * N);
-        P.P = take(e * (size_t)std::max(cs.jv, 1) * P.D * N);
-        P.W = take(cs.has_z ? e * (size_t)(cs.jw + 1) * P.NC * N : kAlign);
-        P.Cf = take(cs.has_z ? e * (size_t)(cs.jw + 1) * P.D * N : kAlign);
+        P.W = take(cs.has_z ? e * (size_t)cs.nsa * P.NC * N : kAlign);
+        P.kV = take(e * (size_t)std::max(cs.nsa, 1) * P.D * N);
+        P.cnl = std::max(cs.jv, cs.jw) <= 2 ? 2 : 4;
+        chain_tiles(c, &P);
+        P.part_q = take(sizeof(double) * (size_t)std::max(cs.nsa, 1) * P.cnt * P.D);
+        P.workc = take(sizeof(int2) * P.nbc);
         P.rec = take(e * 2 * P.D * N);
         P.part_to = take(sizeof(double) * (size_t)std::max(cs.npart(), 1) * P.nbr);
         P.bandw = take(sizeof(double) * (size_t)std::max(cs.nbands, 1) * c->ny);
@@ -248,10 +289,9 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
         P.works = take(sizeof(int2) * P.nbs);
         P.hpart = take(sizeof(double) * kMaxQ * std::max(cs.nhc, 1));
         if (cs.kf) {
-            // kernel filters: V_s [nsa][D][N]; [3][N] work fields: two per
-            // separable term, one per QoI, one more per Z QoI; tap tables;
-            // the job table of the pass program
-            P.kV = take(e * (size_t)cs.nsa * P.D * N);
+            // kernel filters: [3][N] work fields: two per separable term, one
+            // per QoI, one more per Z QoI; tap tables; the job table of the
+            // pass program
             P.kT = take(e * 3 * N * (size_t)(2 * cs.kslots + cs.nsa + cs.nzq));
             P.ktaps = take(e * kMaxSA * 3 * (2 * kMaxRad + 1));
             P.kjobs = take(sizeof(KJob) * (size_t)(2 * (2 * cs.kslots + cs.nsa) + cs.nzq + 1));
@@ -311,6 +351,16 @@ std::vector<int> xcd_order(int n)
 std::vector<int> xcd_tile_order(int ntx, int nty, int ntz)
 {
     return xcd_order(ntx * nty * ntz);
+}
+
+// The same for the reduce, whose workgroup y nbx2 + bx takes cells of one row
+// y: neighbouring rows of the same cells follow each other, so that the rows
+// y +- 1 that a curl reads are in that XCD's L2.
+std::vector<int> reduce_order(int nbx2, int ny)
+{
+    std::vector<int> o = xcd_order(nbx2 * ny);
+    for (int& b : o) b = (b % ny) * nbx2 + b / ny;
+    return o;
 }
 
 // Band weights (eq. 3d-mp-band-weights) in the reading of the library header.
@@ -422,21 +472,10 @@ struct lbm_batch {
 
 namespace {
 
-// Union of the chains each binomial pass advances for member c: pass j
-// computes B^j v (j <= jv) and B^j w with curl^T B^(j-1) w (j <= jw); pass 1
-// also forms w = curl v*, and the readers form the top curl^T B^jw w.
-void add_pass_masks(const lbm_ctx* c, LaunchGroup& g)
+// The larger of a closure's numbers of binomial E and Z QoIs.
+int chain_kinds(const ClosureShape& cs)
 {
-    for (int j = 1; j <= 8; ++j) {
-        if (j <= c->cur.jv) g.bmask[j - 1] |= 1;
-        if (c->cur.has_z && j <= c->cur.jw) g.bmask[j - 1] |= 2;
-    }
-}
-
-// Binomial passes per step of a closure shape.
-int binom_passes(const ClosureShape& cs)
-{
-    return cs.kf ? 0 : std::max(cs.jv, cs.has_z ? std::max(cs.jw, 1) : 0);
+    return cs.kf ? 0 : std::max(cs.nzb, cs.nsa - cs.nzb);
 }
 
 // The member record's fields that follow the closure mode.
@@ -454,16 +493,15 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.substrate = c->cfg.substrate;
     g.mode = c->mode();
     g.any_z = c->cur.has_z;
-    g.maxpow = std::max(c->cur.jv, c->cur.jw);
     g.maxsa = c->cur.nsa;
-    g.npass = binom_passes(c->cur);
+    g.maxk = chain_kinds(c->cur);
+    g.cnl = c->plan.cnl;
     g.btx = c->plan.btx;
     g.wt = write_through((double)c->plan.N * c->plan.Q * c->plan.esz);
     g.a32 = (double)c->plan.popn * c->plan.esz < 4294967296.0 && !(c->cfg.tune_mem & 1);
     g.nt = non_temporal((double)c->plan.popn * c->plan.esz) || (c->cfg.tune_mem & 2);
     g.defer = c->defers();
     g.sep_solve = (c->cfg.tune_mem & 8) != 0;
-    add_pass_masks(c, g);
     g.kf = c->cur.kf;
     g.kjobs = (const KJob*)(c->arena + c->plan.kjobs);
     g.klev = c->klev.data();
@@ -478,6 +516,8 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.nbr = c->plan.nbr;
     g.workb = (const int2*)(c->arena + c->plan.workb);
     g.nbb = c->plan.nbb;
+    g.workc = (const int2*)(c->arena + c->plan.workc);
+    g.nbc = c->plan.nbc;
     g.works = (const int2*)(c->arena + c->plan.works);
     g.nbs = c->plan.nbs;
     g.workm = (const int*)(c->arena + c->plan.workm);
@@ -728,8 +768,16 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         p.has_e = cs.has_e;
         p.spinup = cl->spinup;
         p.seed = cl->seed;
+        // the E/Z QoIs of a binomial closure in order of kind, E first
+        std::vector<int> order;
+        for (int kind : {LBM_QOI_E, LBM_QOI_Z, LBM_QOI_MP})
+            for (int k = 0; k < cl->nq; ++k)
+                if (cl->q[k].kind == kind || (cs.kf && kind == LBM_QOI_E && cl->q[k].kind == LBM_QOI_Z)) {
+                    if (cs.kf && kind == LBM_QOI_Z) continue;
+                    order.push_back(k);
+                }
         int isa = 0, imp = 0;
-        for (int k = 0; k < cl->nq; ++k) {
+        for (int k : order) {
             const lbm_qoi_spec& q = cl->q[k];
             if (q.kind == LBM_QOI_MP) {
                 p.mp_slot[imp] = k;
@@ -738,12 +786,18 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
             } else {
                 p.sa_slot[isa] = k;
                 p.sa_kind[isa] = q.kind == LBM_QOI_E ? 0 : 1;
+                const int kind = p.sa_kind[isa];
+                p.ks[kind][p.nk[kind]++] = isa;
+                // the chains' powers carry a factor 4^D each (and w a factor
+                // 2), taken out here: exact in binary
                 double r[3];
                 filter_poly(q.filter, r);
-                for (int j = 0; j < 3; ++j) p.r[isa][j] = r[j];
+                const double c0 = kind == 1 ? 0.5 : 1.0, cp = c->plan.D == 3 ? 1.0 / 64 : 1.0 / 16;
                 for (int j = 0; j <= kMaxPow; ++j) p.rr[isa][j] = 0;
-                for (int a = 0; a < 3; ++a)
-                    for (int b = 0; b < 3; ++b) p.rr[isa][a + b] += r[a] * r[b];
+                for (int a = 0; a < 3; ++a) {
+                    p.r[isa][a] = r[a] * c0 * std::pow(cp, a);
+                    for (int b = 0; b < 3; ++b) p.rr[isa][a + b] += r[a] * r[b] * c0 * std::pow(cp, a + b);
+                }
                 for (int j = 0; j < 3; ++j) p.rf[isa][j] = (float)p.r[isa][j];
                 for (int j = 0; j <= kMaxPow; ++j) p.rrf[isa][j] = (float)p.rr[isa][j];
                 isa++;
@@ -967,13 +1021,16 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
     m.recs = (lbm_qoi_rec*)(A + plan.recs);
     m.fprof = (double*)(A + plan.fprof);
     if (c->has_to) {
-        m.rho = A + plan.rho; m.vs = A + plan.vs; m.P = A + plan.P; m.W = A + plan.W; m.C = A + plan.Cf;
+        m.rho = A + plan.rho; m.vs = A + plan.vs; m.W = A + plan.W; m.kV = A + plan.kV;
         m.part_to = (double*)(A + plan.part_to);
         m.bandw = (double*)(A + plan.bandw);
         m.cmp = (double*)(A + plan.cmp);
         m.sums = (double*)(A + plan.sums);
         m.hpart = (double*)(A + plan.hpart);
-        if (plan.cap.kf) m.kV = A + plan.kV;
+        m.part_q = (double*)(A + plan.part_q);
+        m.cvx = plan.cvx; m.cvy = plan.cvy; m.czc = plan.czc;
+        m.cntx = plan.cntx; m.cnty = plan.cnty; m.cnt = plan.cnt;
+        m.cd = plan.D; m.cnc = plan.NC;
         m.rec = A + plan.rec;
     }
     m.nst = plan.nb1;
@@ -1000,7 +1057,10 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
     if (!rc) rc = upload(c, A + plan.workm, &zero, sizeof zero);
     if (!rc && c->has_to) {
         std::vector<int2> wr(plan.nbr);
-        for (int b = 0; b < plan.nbr; ++b) wr[b] = make_int2(0, b);
+        {
+            const std::vector<int> o = reduce_order(plan.nbx2, cfg->ny);
+            for (int b = 0; b < plan.nbr; ++b) wr[b] = make_int2(0, o[b]);
+        }
         rc = upload(c, A + plan.workr, wr.data(), sizeof(int2) * wr.size());
         std::vector<int2> wb(plan.nbb);
         {
@@ -1009,6 +1069,12 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
             for (int b = 0; b < plan.nbb; ++b) wb[b] = make_int2(0, o[b]);
         }
         if (!rc) rc = upload(c, A + plan.workb, wb.data(), sizeof(int2) * wb.size());
+        std::vector<int2> wc(plan.nbc);
+        {
+            const std::vector<int> o = xcd_order(plan.nbc);
+            for (int b = 0; b < plan.nbc; ++b) wc[b] = make_int2(0, o[b]);
+        }
+        if (!rc) rc = upload(c, A + plan.workc, wc.data(), sizeof(int2) * wc.size());
         std::vector<int2> ws(plan.nbs);
         for (int b = 0; b < plan.nbs; ++b) ws[b] = make_int2(0, ksum_slot(b, plan.cap.nhc));
         if (!rc) rc = upload(c, A + plan.works, ws.data(), sizeof(int2) * ws.size());
@@ -1461,10 +1527,7 @@ static void canonical_ctl(DevCtl& t)
     }
     t.step_snap = 0;
     for (int k = 0; k < kMaxQ; ++k) t.s_next[k] = 0.0;
-    for (int j = 0; j <= kMaxPow; ++j) {
-        t.cv[j] = t.cw[j] = 0.0;
-        t.cvf[j] = t.cwf[j] = 0.0f;
-    }
+    memset(t.unused, 0, sizeof t.unused);
     for (int k = 0; k < kMaxSA; ++k) {
         t.bsa[k] = 0.0;
         t.bsaf[k] = 0.0f;
@@ -1544,13 +1607,13 @@ static int batch_build(lbm_batch* b)
     batch_free_dev(b);
     const int n = (int)b->mem.size();
     // group members by kernel kind
-    struct Key { int lat, prec, sub, mode, sab, btx, kfm, def, sep; };   // kfm: kernel-filter member (own group)
+    struct Key { int lat, prec, sub, mode, sab, btx, cnl, kfm, def, sep; };   // kfm: kernel-filter member (own group)
     std::vector<Key> keys;
     std::vector<std::vector<int>> gm;
     for (int i = 0; i < n; ++i) {
         const lbm_ctx* c = b->mem[i];
         Key k{c->cfg.lattice, c->cfg.precision, c->cfg.substrate, c->mode(), c->cur.nsa <= 2 ? 2 : (c->cur.nsa <= 6 ? 6 : 8),
-              c->plan.btx, c->mode() == 2 && c->cur.kf ? i : -1, (int)c->defers(), (c->cfg.tune_mem & 8) != 0};
+              c->plan.btx, c->mode() == 2 ? c->plan.cnl : 0, c->mode() == 2 && c->cur.kf ? i : -1, (int)c->defers(), (c->cfg.tune_mem & 8) != 0};
         int gi = -1;
         for (size_t j = 0; j < keys.size(); ++j)
             if (!memcmp(&keys[j], &k, sizeof k)) gi = (int)j;
@@ -1560,7 +1623,7 @@ static int batch_build(lbm_batch* b)
     std::vector<DevMember> hmem(n);
     std::vector<int2> work;
     std::vector<int> workm;
-    struct Off { size_t w1, nb1, wp, nbp, wr, nbr, wb, nbb, ws, nbs, wm, nm; };
+    struct Off { size_t w1, nb1, wp, nbp, wr, nbr, wb, nbb, wc, nbc, ws, nbs, wm, nm; };
     std::vector<Off> offs;
     for (size_t gi = 0; gi < keys.size(); ++gi) {
         Off o{};
@@ -1579,7 +1642,7 @@ static int batch_build(lbm_batch* b)
         o.wr = work.size();
         if (keys[gi].mode == 2)
             for (int i : gm[gi])
-                for (int k = 0; k < b->mem[i]->plan.nbr; ++k) work.push_back(make_int2(i, k));
+                for (int k : reduce_order(b->mem[i]->plan.nbx2, b->mem[i]->cfg.ny)) work.push_back(make_int2(i, k));
         o.nbr = work.size() - o.wr;
         o.wb = work.size();
         if (keys[gi].mode == 2)
@@ -1591,6 +1654,13 @@ static int batch_build(lbm_batch* b)
                 for (int k = 0; k < b->mem[i]->plan.nbb; ++k) work.push_back(make_int2(i, o[k]));
             }
         o.nbb = work.size() - o.wb;
+        o.wc = work.size();
+        if (keys[gi].mode == 2)
+            for (int i : gm[gi]) {
+                const std::vector<int> oc = xcd_order(b->mem[i]->plan.nbc);
+                for (int k = 0; k < b->mem[i]->plan.nbc; ++k) work.push_back(make_int2(i, oc[k]));
+            }
+        o.nbc = work.size() - o.wc;
         o.ws = work.size();
         if (keys[gi].mode == 2)
             for (int i : gm[gi])
@@ -1626,6 +1696,7 @@ static int batch_build(lbm_batch* b)
         g.substrate = keys[gi].sub;
         g.mode = keys[gi].mode;
         g.btx = keys[gi].btx;
+        g.cnl = keys[gi].cnl;
         double pop_bytes = 0;   // one launch covers the whole group
         for (int i : gm[gi]) pop_bytes += (double)b->mem[i]->plan.N * b->mem[i]->plan.Q * b->mem[i]->plan.esz;
         g.wt = write_through(pop_bytes);
@@ -1637,15 +1708,12 @@ static int batch_build(lbm_batch* b)
             g.nt |= (b->mem[i]->cfg.tune_mem & 2) != 0;
             const lbm_ctx* c = b->mem[i];
             g.any_z |= c->cur.has_z;
-            g.maxpow = std::max(g.maxpow, std::max(c->cur.jv, c->cur.jw));
             g.maxsa = std::max(g.maxsa, c->cur.nsa);
-            g.npass = std::max(g.npass, binom_passes(c->cur));
+            g.maxk = std::max(g.maxk, chain_kinds(c->cur));
             g.defer = c->defers();   // (members of a group share mode and substrate)
             g.sep_solve = (c->cfg.tune_mem & 8) != 0;
-            add_pass_masks(c, g);
             if (keys[gi].kfm >= 0) {
                 g.kf = 1;
-                g.npass = 0;
                 g.kjobs = (const KJob*)(c->arena + c->plan.kjobs);
                 g.klev = c->klev.data();
                 g.nklev = (int)c->klev.size();
@@ -1661,6 +1729,8 @@ static int batch_build(lbm_batch* b)
         g.nbr = (int)offs[gi].nbr;
         g.workb = b->dwork + offs[gi].wb;
         g.nbb = (int)offs[gi].nbb;
+        g.workc = b->dwork + offs[gi].wc;
+        g.nbc = (int)offs[gi].nbc;
         g.works = b->dwork + offs[gi].ws;
         g.nbs = (int)offs[gi].nbs;
         g.workm = b->dworkm + offs[gi].wm;
@@ -1789,7 +1859,7 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
         const int m = g.mode;
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
         launches[1] = m == 2 && g.kf && g.any_z ? 1 : 0;
-        launches[2] = m == 2 ? (g.kf ? g.nklev : g.npass) : 0;
+        launches[2] = m == 2 ? (g.kf ? g.nklev : (g.maxk > 0 ? 1 : 0)) : 0;
         launches[3] = m == 2 ? 1 : 0;
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)
         launches[5] = m == 2 ? 1 : (m == 1 ? 2 : 0);

@@ -19,9 +19,9 @@ constexpr int kBlock = 256;     // threads per workgroup of the cell kernels
 // its Q populations one after another, [ceil(N / kPopBlk)][Q][kPopBlk].
 constexpr int kPopLog = 10;
 constexpr int kPopBlk = 1 << kPopLog;
-constexpr int kBinTX = 32;      // binomial-filter tile: x extent
+constexpr int kBinTX = 32;      // tiled stream-collide: x extent of a tile
 constexpr int kBinTY = kBlock / kBinTX;  // y extent
-constexpr int kBinTXW = 64;     // the wide tile (64 x 8, 512 threads) of the tiled kernels
+constexpr int kBinTXW = 64;     // the wide tile (64 x 8, 512 threads)
 constexpr int kBinZCMax = 16;   // most z planes per workgroup chosen automatically (3-D)
 // The binomial apply forms the member's solve in every workgroup (one per
 // pair of 256-cell blocks of a member) where its launch has at most this
@@ -29,6 +29,14 @@ constexpr int kBinZCMax = 16;   // most z planes per workgroup chosen automatica
 // the 256 CUs, so the solve's latency is paid once per launch, under the
 // apply's own loads; larger launches keep k_solve.
 constexpr int kFusedApplyPairs = 512;
+// Shape of a filter-chain workgroup (k_chain): wavefronts, and rows in y held
+// by each thread.  3-D: 8 wavefronts of 4 rows in FP32 (172 VGPRs; 12 or 16
+// wavefronts, or 2, 3, 5 or 6 rows, are within 10% on 96 x 48 x 48 and
+// 384 x 192 x 192; two workgroups per CU, at 128 VGPRs, spill and take twice
+// the time) and of 3 in FP64; 2-D: one wavefront of 16 rows, which needs no
+// exchange.
+__host__ __device__ constexpr int chain_waves(int d) { return d == 3 ? 8 : 1; }
+__host__ __device__ constexpr int chain_rows(int d, int esz) { return d == 3 ? (esz == 4 ? 4 : 3) : 16; }
 constexpr int kHistRows = 512;   // LRS history rows (x entries) per k_sum workgroup
 constexpr int kMaxHistChunks = 64;                 // so 2 h nq <= 32768
 constexpr int kMaxRad = 12;     // kernel filters: largest radius of a 1-D factor
@@ -45,9 +53,11 @@ struct DevParam {
     int sa_kind[kMaxSA];               // 0 E, 1 Z
     int mp_slot[kMaxQ];                // user index of each MP QoI
     int mp_band[kMaxQ];
-    double r[kMaxSA][3];               // R   = sum_j r[j]  B^j
-    double rr[kMaxSA][kMaxPow + 1];    // R R = sum_j rr[j] B^j
-    float rf[kMaxSA][3];               // the same rounded to FP32 (for the FP32 kernels)
+    int nk[2], ks[2][kMaxSA];          // binomial closures: the E (Z) QoIs, their indices
+    // R = sum_j r[j] B^j, R R = sum_j rr[j] B^j, scaled for the chains' powers: times 4^(-D j), Z: and 1/2
+    double r[kMaxSA][3];
+    double rr[kMaxSA][kMaxPow + 1];
+    float rf[kMaxSA][3];               // the same in FP32 (exact)
     float rrf[kMaxSA][kMaxPow + 1];
     double C[(kMaxQ + 1) * kMaxQ];
     double mu[kMaxQ];
@@ -65,13 +75,9 @@ struct DevCtl {
     int flags;                         // sticky bit0: unstable
     int s_set;
     double s[kMaxQ];                   // LRS scale
-    double cv[kMaxPow + 1];            // dv = sum_j cv[j] B^j v + curl^T(sum_j cw[j] B^j w) + e_x cmp(y)
-    double cw[kMaxPow + 1];
-    float cvf[kMaxPow + 1];            // cv, cw rounded to FP32
-    float cwf[kMaxPow + 1];
-    double pad[1];
+    double unused[16];                 // (zero; keeps the layout of saved state images)
     double lrs_e[kMaxQ];               // mu + L xi of the current step's LRS draw
-    double bsa[kMaxSA];                // beta of each E/Z QoI (kernel-filter dv build)
+    double bsa[kMaxSA];                // beta of each E/Z QoI: dv = sum_s bsa[s] V_s + e_x cmp(y)
     float bsaf[kMaxSA];
     long long step_snap;               // step as k_sum found it (read by a fused apply)
     int s_pend;                        // a first LRS scale in s_next, committed by the next k_sum
@@ -89,14 +95,16 @@ struct DevMember {
     void* rho;                         // rho - 1 of the predictor [N]      (TO)
     void* vs;                          // predictor velocity v* [D][N]      (TO)
     void* vn;                          // post-streaming velocity [D][N]    (diag, WALE)
-    void* P;                           // B^j v*, j = 1..jv   [jv][D][N]
-    void* W;                           // B^j curl v*, j=0..jw [jw+1][NC][N]
-    void* C;                           // curl^T B^j curl v*, j=0..jw-1 [jw+1][D][N] (C_jw: from W_jw)
+    void* W;                           // binomial Z QoIs: U_s = R R w [nsa][NC][N]; else w [NC][N]
     double* part_stats;                // [nb1][4]: sum(rho-1), sum(rho v)
     double* part_to;                   // [npart][ny * nbx2]
+    double* part_q;                    // [nsa][cnt * D]: QoI sums of the chain workgroups
     double* part_diag;                 // [nb1][2]
     int nb1, nbx2, npart, cpt2;        // block counts; cells per thread of the reduce
-    int zc, btx;                       // z planes per binomial-filter workgroup; its tile width
+    int zc, btx;                       // tiled stream-collide: z planes per workgroup; tile width
+    int cvx, cvy, czc;                 // filter chains: cells of a tile in x, y and z
+    int cntx, cnty, cnt;               // tiles in x, in y, and in all
+    int cd, cnc;                       // components of v and of w
     DevParam* prm;
     DevCtl* ctl;
     lbm_qoi_rec* recs;
@@ -105,7 +113,7 @@ struct DevMember {
     double* fprof;                     // body force F_x(y) [ny]
     double* sums;                      // [4 + npart]: reduced statistics and TO partials
     double* hpart;                     // [nhc][kMaxQ]: LRS history product per k_sum workgroup
-    void* kV;                          // kernel filters: V_s = R(R v*) or curl^T R(R w), [nsa][D][N]
+    void* kV;                          // sensitivities V_s = R R v* or curl^T R R w, [nsa][D][N]
     void* rec;                         // pending SGS change of the last step: (rho dv, 2 v* + dv) [2D][N]
     int nst;                           // stream-collide statistics partials (workgroups of the launch)
     int defer;                         // TO steps defer the SGS change into the next pull (k_step_t)

@@ -12,17 +12,17 @@
 //   k_step_t   the same on 2.5-D tiles, adding during the pull the SGS change
 //              the previous step recorded per cell (grids whose populations
 //              exceed the L2s).
-//   k_binom1   first powers of the binomial filter (Sec. 4.1): w = curl v*,
-//              B v*, B w and curl^T w from v* staged with a two-cell halo.
-//   k_binom    further powers B^j v*, B^j w and curl^T B^(j-1) w.
-//   k_reduce   per-cell QoIs, sensitivities (App. A) and Gram products,
-//              reduced per workgroup in FP64.
+//   k_chain    binomial closures (Sec. 4.1): from v* the sensitivities
+//              R R v* of the E QoIs, U = R R w of the Z QoIs (w = curl v*) and
+//              the QoI sums, every power of B on chip.
+//   k_reduce   sensitivities curl^T U of the Z QoIs (App. A) and the Gram
+//              products, reduced per workgroup in FP64.
 //   k_sum      fixed-order cross-workgroup sums; the step's LRS draw.
 //   k_solve    one workgroup per member: dQ (tracking or LRS, eqs.
 //              dQ-from-ref, LRS), Gram solve (eq. O-from-V, eq.
 //              orthogonality), gamma (eq. tau-from-dQ-for-tracking).
 //   k_apply    dv_SGS = sum_i gamma_i O_i (eq. TO-ansatz), evaluated as
-//              sum_j beta_j V_j with beta = G^-1 dQ; its change of the
+//              sum_i beta_i V_i with beta = G^-1 dQ; its change of the
 //              equilibrium is added to the predictor populations in place, or
 //              recorded as (rho dv, 2 v* + dv) for the next k_step_t (k_flush
 //              applies pending records before the state is read).
@@ -882,18 +882,50 @@ __device__ __forceinline__ void curl_nb(const T* __restrict__ u, unsigned sN, un
     }
 }
 
-// The adjoint curl of a curl field psi (NC components) at a cell: 2-D
+// The adjoint curl of a curl field psi (NC components) at a cell, 2-D
 // (D_y psi, -D_x psi) (eq. enstrophy-sensitivity-2d), 3-D curl psi
-// (eq. enstrophy-sensitivity-3d).
+// (eq. enstrophy-sensitivity-3d), in two steps, so that a caller can hold the
+// loads and form the curl later: the neighbour values (2-D: psi at y+1, y-1,
+// x+1, x-1; 3-D: psi_z, psi_y, psi_x at the pairs of neighbours of D_y psi_z,
+// D_z psi_y, D_z psi_x, D_x psi_z, D_x psi_y, D_y psi_x), then central
+// differences (zero beyond the walls), without contraction.
 template <int D, typename T>
-__device__ __forceinline__ void curlT_nb(const T* __restrict__ psi, unsigned sN, unsigned c, const Nbr& n, T* out)
+__device__ __forceinline__ void curlT_load(const T* __restrict__ psi, unsigned sN, const Nbr& n, T* r)
 {
-    if (D == 2) {
-        auto y0 = [](bool ok, T v) { return ok ? v : T(0); };
-        out[0] = T(0.5) * (y0(n.okp, ld_at(psi, n.yp)) - y0(n.okm, ld_at(psi, n.ym)));
-        out[1] = -(T(0.5) * (ld_at(psi, n.xp) - ld_at(psi, n.xm)));
+    if constexpr (D == 2) {
+        r[0] = ld_at(psi, n.yp); r[1] = ld_at(psi, n.ym);
+        r[2] = ld_at(psi, n.xp); r[3] = ld_at(psi, n.xm);
     } else {
-        curl_nb<3, T>(psi, sN, c, n, out);
+        const T* ux = psi;
+        const T* uy = psi + sN;
+        const T* uz = psi + 2 * (size_t)sN;
+        r[0] = ld_at(uz, n.yp); r[1] = ld_at(uz, n.ym);
+        r[2] = ld_at(uy, n.zp); r[3] = ld_at(uy, n.zm);
+        r[4] = ld_at(ux, n.zp); r[5] = ld_at(ux, n.zm);
+        r[6] = ld_at(uz, n.xp); r[7] = ld_at(uz, n.xm);
+        r[8] = ld_at(uy, n.xp); r[9] = ld_at(uy, n.xm);
+        r[10] = ld_at(ux, n.yp); r[11] = ld_at(ux, n.ym);
+    }
+}
+
+template <int D, typename T>
+__device__ __forceinline__ void curlT_eval(const T* r, bool okm, bool okp, T* out)
+{
+#pragma clang fp contract(off)
+    auto y0 = [](bool ok, T v) { return ok ? v : T(0); };
+    if constexpr (D == 2) {
+        out[0] = T(0.5) * (y0(okp, r[0]) - y0(okm, r[1]));
+        out[1] = -(T(0.5) * (r[2] - r[3]));
+    } else {
+        const T dyuz = T(0.5) * (y0(okp, r[0]) - y0(okm, r[1]));
+        const T dzuy = T(0.5) * (r[2] - r[3]);
+        const T dzux = T(0.5) * (r[4] - r[5]);
+        const T dxuz = T(0.5) * (r[6] - r[7]);
+        const T dxuy = T(0.5) * (r[8] - r[9]);
+        const T dyux = T(0.5) * (y0(okp, r[10]) - y0(okm, r[11]));
+        out[0] = dyuz - dzuy;
+        out[1] = dzux - dxuz;
+        out[2] = dxuy - dyux;
     }
 }
 
@@ -919,690 +951,423 @@ __global__ __launch_bounds__(kBlock) void k_curl(const DevMember* __restrict__ m
     for (int a = 0; a < L::NC; ++a) st_fld_at(W + (size_t)a * N, c, w[a], WT);
 }
 
-// Binomial filter B = (x)_a [1,2,1]/4 of one scalar field at (x,y,z).
-template <int D, typename T>
-__device__ __forceinline__ T binom_at(const T* __restrict__ u, int x, int y, int z, int nx, int ny, int nz, int walls)
+// ---------------------------------------------------------------------------
+// K2: the filter chains of the binomial closures, v* to sensitivities in one
+// launch.  Filters are polynomials of the binomial operator
+// B = (x)_a [1,2,1]/4, so with P_j = B^j v* and W_j = B^j w, w = curl v*:
+//   E: V_s = R R v* = sum_j rr_sj P_j        (stored, the final sensitivity);
+//   Z: U_s = R R w  = sum_j rr_sj W_j        (stored; k_reduce forms
+//      V_s = curl^T U_s from it);
+// and the QoI densities 1/2 |R v*|^2, 1/2 |R w|^2 of the tile's cells, summed
+// in FP64 per workgroup.  Each component of v* and of w is a chain of its own
+// and a workgroup's whole work, so nothing passes between components.
+//
+// A wavefront's lanes are 64 neighbouring cells in x, of which the inner
+// 64 - 2 H are the tile's own (H = NL, a cell for each power); each
+// thread holds chain_rows() rows in y.  x neighbours come from DPP lane moves,
+// y neighbours from the thread's own rows, except those of its first and last
+// row, which pass through LDS between the wavefronts of the workgroup
+// (3-D).  In 3-D the workgroup marches in z, two planes at a time (one barrier
+// per power and pair): every power keeps the two values its z part needs and
+// lags the one before it by a plane, and W_0.. wait in registers until the
+// highest power of their plane is known.  [1,2,1] is applied as [1,1] twice
+// (two additions per axis, no products); the scale 4^-D per power, exact in
+// binary, is in the coefficients.
+//
+// The powers are never stored: about 100 B of traffic per cell (FP32 channel,
+// three QoIs of each kind; counters: 25 in, 76 out) where one launch per power
+// moved 260.  Bound by its vector instructions (half of the time; half of
+// those form the sensitivities and densities) and by the stores of row
+// segments that are not whole lines; measured on MI355X: 31.8 us in four
+// launches -> 23 us on 96 x 48 x 48, 781 -> 514 us on 384 x 192 x 192 (352 us
+// with the stores left out); on 256 x 256 two launches of 4.6 us -> one of 5.
+// The stores are plain ones: neighbouring tiles share lines, which the L2
+// merges (non-temporal 624 us, written through 2 us slower on 96 x 48 x 48).
+// Without two planes at a time, with the phases of the waiting rings unrolled
+// (75 to 100 KB of code), the same march took 660 us.
+// ---------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ T fma_(T a, T b, T c);
+template <> __device__ __forceinline__ float fma_<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <> __device__ __forceinline__ double fma_<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// The value of the previous (next) lane of the wavefront; zero past its ends.
+template <int CTRL> __device__ __forceinline__ float lane_shift(float v)
 {
-    const int xm = wrapi(x - 1, nx), xp = wrapi(x + 1, nx);
-    T acc = 0;
-    const int zr = D == 3 ? 1 : 0;
-#pragma unroll
-    for (int oz = -zr; oz <= zr; ++oz) {
-        const int zz = D == 3 ? wrapi(z + oz, nz) : 0;
-        T sy = 0;
-#pragma unroll
-        for (int oy = -1; oy <= 1; ++oy) {
-            int yy = y + oy;
-            T r = 0;
-            if (walls && (yy < 0 || yy >= ny)) {
-                r = T(0);
-            } else {
-                yy = wrapi(yy, ny);
-                const T* row = u + (size_t)nx * (yy + (size_t)ny * zz);
-                r = T(0.25) * (row[xm] + T(2) * row[x] + row[xp]);
-            }
-            sy += (oy == 0 ? T(0.5) : T(0.25)) * r;
-        }
-        acc += (D == 3 ? (oz == 0 ? T(0.5) : T(0.25)) : T(1)) * sy;
-    }
-    return acc;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
+template <int CTRL> __device__ __forceinline__ double lane_shift(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <typename T> __device__ __forceinline__ T lane_prev(T v) { return lane_shift<0x138>(v); }   // wave_shr:1
+template <typename T> __device__ __forceinline__ T lane_next(T v) { return lane_shift<0x130>(v); }   // wave_shl:1
 
-// K2b, passes j >= 2: P_j = B P_{j-1} for j <= jv and W_j = B W_{j-1} with
-// C_{j-1} = curl^T W_{j-1} for j <= jw (pass 1 is k_binom1).
-// 2.5-D tiling: a workgroup of 8 TX threads owns a TX x 8 tile of the xy
-// plane (32 x 8, or 64 x 8 on wide grids: each staged row then wastes fewer
-// 128-byte lines on its one-cell x halo) and a chunk of zc planes (chosen per grid for enough
-// workgroups); every plane of the chunk (plus one halo plane on each side)
-// is staged with its xy halo in LDS, filtered in x and y there, and the z
-// pass runs on a three-plane window kept in registers.
+// Coefficients of the chains in the kernel's arithmetic type.
+template <typename T> __device__ __forceinline__ T chain_r(KParam* p, int s, int j);
+template <> __device__ __forceinline__ float chain_r<float>(KParam* p, int s, int j) { return p->rf[s][j]; }
+template <> __device__ __forceinline__ double chain_r<double>(KParam* p, int s, int j) { return p->r[s][j]; }
+template <typename T> __device__ __forceinline__ T chain_rr(KParam* p, int s, int j);
+template <> __device__ __forceinline__ float chain_rr<float>(KParam* p, int s, int j) { return p->rrf[s][j]; }
+template <> __device__ __forceinline__ double chain_rr<double>(KParam* p, int s, int j) { return p->rr[s][j]; }
 
-// CH: the chains the launch advances (1: v, 2: w and its curl, 3: both);
-// the launch passes the union over its members, and a member whose chain
-// this pass does not advance either returns (CH = 1, 2) or re-reads the
-// other chain's source (CH = 3).
-template <int LAT, typename T, int TX, int CH, bool WT>
-__global__ __launch_bounds__(TX * kBinTY) void k_binom(const DevMember* __restrict__ mems, const int2* __restrict__ work,
-                                                  int j)
+// One component's chain on one tile.  CURL < 0: component comp of v*; 0, 1,
+// 2: that component of w (2-D: 2, the only one).  edge: LDS of the row
+// exchange, [NL][NW + 2][2][2][64], its first and last wavefront slots zero.
+template <int LAT, typename T, int NL, int MS, int CURL>
+__device__ __forceinline__ void chain_job(KMember& m, KParam* prm, int comp, int tile, T* edge, double* red)
 {
     using L = Lat<LAT>;
-    constexpr int D = L::D, NC = L::NC;
-    constexpr int NV = (CH & 1) ? D : 0, NW = (CH & 2) ? NC : 0, NCMP = NV + NW;   // tile: v, then w
-    constexpr int NT = TX * kBinTY, TY = kBinTY;   // tile TX x 8, one cell per thread
-    constexpr int HX = TX + 2, HY = TY + 2, HXY = HX * HY;
-    // the staged plane [component][halo tile]
-    __shared__ T tile[NCMP * HXY];
-    const int2 wk = work[blockIdx.x];
-    KMember& m = *kc(mems + wk.x);
-    KParam* prm = kc(m.prm);
-    // this pass: B^j v (j <= jv), B^j w (j <= jw) and C_{j-1} = curl^T B^{j-1} w (j - 1 <= jw)
-    const bool dov = j <= prm->jv, dow = prm->has_z && j <= prm->jw;
-    const bool doc = dow;   // the top C_jw is formed by its readers from W_jw
-    if (!dov && !doc) return;
-    if ((CH == 1 && !dov) || (CH == 2 && !doc)) return;
-    const int nx = m.nx, ny = m.ny, nz = m.nz;
+    constexpr int D = L::D, NC = L::NC, H = NL, R = chain_rows(D, sizeof(T)), NW = chain_waves(D);
+    constexpr int KIND = CURL < 0 ? 0 : 1;
+    const int nx = m.nx, ny = m.ny, nz = m.nz, walls = m.walls;
     const size_t sN = (size_t)m.N;
-    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
-    const int zc = m.zc;
-    const int tx0 = (wk.y % ntx) * TX;
-    const int ty0 = ((wk.y / ntx) % nty) * TY;
-    const int tz0 = (wk.y / (ntx * nty)) * zc;
-    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
-    const int x = tx0 + lx, y = ty0 + ly;
-    const bool own = x < nx && y < ny;
-    // Source and destination component pointers.  Every component is loaded
-    // unconditionally (no branch-joined loads, so the loads of a plane stay
-    // in flight together); a chain this pass does not advance re-reads the
-    // other chain's source (cache hits) and stores nothing.
-    const T* src[NCMP];
-    T* dst[NCMP];
-    const T* sv = j == 1 ? (const T*)m.vs : (const T*)m.P + (size_t)(j - 2) * D * sN;
-    const T* sw = (const T*)m.W + (size_t)(j - 1) * NC * sN;
+    const int nk = prm->nk[KIND];
+    const int tx = tile % m.cntx, ty = (tile / m.cntx) % m.cnty, tz = tile / (m.cntx * m.cnty);
+    const int lane = threadIdx.x & 63;
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int x0 = tx * m.cvx, xe = min(x0 + m.cvx, nx), y0 = ty * m.cvy, ye = min(y0 + m.cvy, ny);
+    // byte offsets of the lane's cell and (for D_x) of its x neighbours
+    const int xc = modi(x0 - H + lane, nx);
+    const unsigned xb = (unsigned)xc * sizeof(T), xm = (unsigned)wrapi(xc - 1, nx) * sizeof(T),
+                   xp = (unsigned)wrapi(xc + 1, nx) * sizeof(T);
+    const bool ownx = lane >= H && lane - H < xe - x0;
+    // rows -1 .. R of the wavefront: offset in the plane, whether inside the
+    // walls (a row beyond them counts as zero and loads row 0), whether own
+    const int ys = (walls && ty == 0 ? 0 : y0 - H) + wv * R;
+    unsigned yo[R + 2];     // in bytes
+    unsigned outm = 0;      // bit r + 1: row r is beyond a wall
+    bool any_own = false;
+    {
+        int yy = modi(ys - 1, ny);
 #pragma unroll
-    for (int a = 0; a < NV; ++a) {
-        src[a] = dov ? sv + a * sN : sw + (a % NC) * sN;
-        dst[a] = dov ? (T*)m.P + ((size_t)(j - 1) * D + a) * sN : nullptr;
-    }
-#pragma unroll
-    for (int a = 0; a < NW; ++a) {
-        src[NV + a] = doc ? sw + a * sN : sv + (a % D) * sN;
-        dst[NV + a] = dow ? (T*)m.W + ((size_t)j * NC + a) * sN : nullptr;
-    }
-    T* cdst = NW > 0 && doc ? (T*)m.C + (size_t)(j - 1) * D * sN : nullptr;
-    const int zr = D == 3 ? 1 : 0;
-    const int zend = D == 3 ? min(tz0 + zc, nz) : 1;
-    // the (at most two) halo elements this thread stages, as offsets within
-    // a plane; an element outside the walls loads cell 0 and stages zero
-    constexpr int NE = (HXY + NT - 1) / NT;
-    int eoff[NE];
-    bool eok[NE];
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int e = threadIdx.x + k * NT;
-        const int hx = e % HX, hy = e / HX;
-        int gx = tx0 + hx - 1;       // in [-1, nx + TX - 1]
-        gx = gx < 0 ? gx + nx : (gx >= nx ? modi(gx, nx) : gx);
-        int gy = ty0 + hy - 1;       // in [-1, ny + TY - 1]
-        bool ok = e < HXY;
-        if (m.walls) ok = ok && gy >= 0 && gy < ny;
-        else gy = gy < 0 ? gy + ny : (gy >= ny ? modi(gy, ny) : gy);
-        eok[k] = ok;
-        eoff[k] = ok ? gx + nx * gy : 0;
-    }
-    const int plane = nx * ny;
-    auto fetch = [&](int pz, T (&buf)[NE][NCMP]) {
-        const int zz = D == 3 ? modi(pz, nz) : 0;
-        const unsigned zo = (unsigned)(plane * zz);
-#pragma unroll
-        for (int k = 0; k < NE; ++k)
-#pragma unroll
-            for (int c = 0; c < NCMP; ++c) buf[k][c] = ld_at(src[c], zo + (unsigned)eoff[k]);
-    };
-    auto stage = [&](int pl, const T (&buf)[NE][NCMP]) {
-#pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            const int e = threadIdx.x + k * NT;
-            if (e < HXY) {
-#pragma unroll
-                for (int c = 0; c < NCMP; ++c) tile[(pl * NCMP + c) * HXY + e] = eok[k] ? buf[k][c] : T(0);
-            }
-        }
-    };
-    // x and y passes of the staged plane pl at the own cell; the own value
-    // and xy derivatives of w for the curl
-    auto xyfilter = [&](int pl, T (&sn)[NCMP], T (&rn)[NC], T (&dn)[NC][2]) {
-#pragma unroll
-        for (int c = 0; c < NCMP; ++c) {
-            const T* t = tile + (pl * NCMP + c) * HXY + ly * HX + lx;   // (lx, ly): lower-left halo corner
-            const T q0 = T(0.25) * (t[0] + T(2) * t[1] + t[2]);
-            const T q1 = T(0.25) * (t[HX] + T(2) * t[HX + 1] + t[HX + 2]);
-            const T q2 = T(0.25) * (t[2 * HX] + T(2) * t[2 * HX + 1] + t[2 * HX + 2]);
-            sn[c] = T(0.25) * q0 + T(0.5) * q1 + T(0.25) * q2;
-        }
-#pragma unroll
-        for (int a = 0; a < NW; ++a) {
-            const T* t = tile + (pl * NCMP + NV + a) * HXY + (ly + 1) * HX + lx + 1;
-            rn[a] = t[0];
-            dn[a][0] = T(0.5) * (t[1] - t[-1]);
-            dn[a][1] = T(0.5) * (t[HX] - t[-HX]);
-        }
-    };
-    // 3-D output of plane zo from the xy-filtered planes zo-1, zo, zo+1 (sa,
-    // sb, sc), w at zo-1 and zo+1 (ra, rc) and the xy derivatives at zo
-    auto emit3 = [&](int zo, const T (&sa)[NCMP], const T (&sb)[NCMP], const T (&sc)[NCMP], const T (&ra)[NC],
-                     const T (&rc)[NC], const T (&dxyb)[NC][2]) {
-        if (!own) return;
-        const size_t ci = (size_t)x + (size_t)nx * (y + (size_t)ny * zo);
-#pragma unroll
-        for (int c = 0; c < NCMP; ++c)
-            if (dst[c]) st_fld(dst[c] + ci, T(0.25) * sa[c] + T(0.5) * sb[c] + T(0.25) * sc[c], WT);
-        if constexpr (D == 3 && NW > 0) {
-            if (cdst) {   // curl w at plane zo, D_z from the planes below and above
-                st_fld(cdst + ci, (T(0.5) * ra[1] + dxyb[2][1]) - T(0.5) * rc[1], WT);        // D_y w_z - D_z w_y
-                st_fld(cdst + sN + ci, (T(-0.5) * ra[0] - dxyb[2][0]) + T(0.5) * rc[0], WT);  // D_z w_x - D_x w_z
-                st_fld(cdst + 2 * sN + ci, dxyb[1][0] - dxyb[0][1], WT);                      // D_x w_y - D_y w_x
-            }
-        }
-    };
-    const int p0 = tz0 - zr, p1 = zend - 1 + zr;   // staged planes, inclusive
-    if (D == 2) {
-        T buf[NE][NCMP], sn[NCMP], rn[NC] = {}, dn[NC][2] = {};
-        fetch(0, buf);
-        stage(0, buf);
-        __syncthreads();
-        xyfilter(0, sn, rn, dn);
-        if (own) {
-            const size_t ci = (size_t)x + (size_t)nx * y;
-#pragma unroll
-            for (int c = 0; c < NCMP; ++c)
-                if (dst[c]) st_fld(dst[c] + ci, sn[c], WT);
-            if (NW > 0 && cdst) {   // curl^T of a scalar: (D_y w, -D_x w)
-                st_fld(cdst + ci, dn[0][1], WT);
-                st_fld(cdst + sN + ci, -dn[0][0], WT);
-            }
-        }
-    } else {
-        // zc output planes: software pipeline over a three-plane register
-        // window; the loads of the next plane are in flight while the
-        // current one is filtered.  (Measured on MI355X: deeper prefetch or
-        // a second LDS buffer do not pay here.)
-        T s0[NCMP], s1[NCMP];
-        T r1[NC], r2[NC], dxy[NC][2];   // w at planes z-1 and z (own cell), xy derivatives at z
-#pragma unroll
-        for (int c = 0; c < NCMP; ++c) { s0[c] = 0; s1[c] = 0; }
-#pragma unroll
-        for (int a = 0; a < NC; ++a) { r1[a] = 0; r2[a] = 0; dxy[a][0] = 0; dxy[a][1] = 0; }
-        T buf[NE][NCMP];
-        fetch(p0, buf);
-        for (int pz = p0; pz <= p1; ++pz) {
-            stage(0, buf);
-            __syncthreads();
-            if (pz < p1) fetch(pz + 1, buf);
-            T sn[NCMP], rn[NC] = {}, dn[NC][2] = {};
-            xyfilter(0, sn, rn, dn);
-            __syncthreads();
-            if (pz >= tz0 + 1) emit3(pz - 1, s0, s1, sn, r1, rn, dxy);  // once its upper neighbour is staged
-#pragma unroll
-            for (int c = 0; c < NCMP; ++c) { s0[c] = s1[c]; s1[c] = sn[c]; }
-#pragma unroll
-            for (int a = 0; a < NC; ++a) {
-                r1[a] = r2[a]; r2[a] = rn[a];
-                dxy[a][0] = dn[a][0]; dxy[a][1] = dn[a][1];
-            }
+        for (int r = 0; r < R + 2; ++r) {
+            const int y = ys - 1 + r;
+            const bool ok = !walls || (y >= 0 && y < ny);
+            yo[r] = ok ? (unsigned)(yy * nx) * (unsigned)sizeof(T) : 0u;
+            outm |= ok ? 0u : 1u << r;
+            any_own = any_own || (r >= 1 && r <= R && y >= y0 && y < ye);
+            yy = yy + 1 == ny ? 0 : yy + 1;
         }
     }
-}
-
-// K2b, pass 1: the first power of both chains from v* alone.  v* is staged
-// with a two-cell xy halo; w = curl v* is formed in LDS on the tile and its
-// one-cell halo (zero beyond the walls, as every filtered field), from which
-// the pass forms B w and C_0 = curl^T w; it writes P_1 = B v* (jv >= 1),
-// W_0 = w and, when jw >= 1, W_1 = B w and C_0.  In 3-D the z direction runs
-// through a ring of three staged v* planes and register windows of the xy
-// parts, w lagging v* by one plane.  ZC: some member of the launch has Z
-// QoIs (otherwise only B v* is formed).
-template <int LAT, typename T, int TX, bool ZC, bool WT>
-__global__ __launch_bounds__(TX * kBinTY) void k_binom1(const DevMember* __restrict__ mems, const int2* __restrict__ work)
-{
-    using L = Lat<LAT>;
-    constexpr int D = L::D, NC = L::NC;
-    constexpr int NT = TX * kBinTY, TY = kBinTY;
-    constexpr int HX1 = TX + 2, HY1 = TY + 2, HXY1 = HX1 * HY1;   // tile and one-cell halo
-    constexpr int HX2 = TX + 4, HY2 = TY + 4, HXY2 = HX2 * HY2;   // tile and two-cell halo
-    constexpr int NE1 = (HXY1 + NT - 1) / NT, NE2 = (HXY2 + NT - 1) / NT;
-    constexpr int NSL = D == 3 ? 3 : 1;
-    __shared__ T vt[NSL][D][HXY2];
-    __shared__ T wt[ZC ? NC : 1][ZC ? HXY1 : 1];
-    const int2 wk = work[blockIdx.x];
-    KMember& m = *kc(mems + wk.x);
-    KParam* prm = kc(m.prm);
-    const bool dov = prm->jv >= 1;
-    const bool doz = ZC && prm->has_z;
-    const bool dow1 = doz && prm->jw >= 1;
-    if (!dov && !doz) return;   // uniform
-    const int nx = m.nx, ny = m.ny, nz = m.nz;
-    const size_t sN = (size_t)m.N;
-    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
-    const int zc = m.zc;
-    const int tx0 = (wk.y % ntx) * TX;
-    const int ty0 = ((wk.y / ntx) % nty) * TY;
-    const int tz0 = D == 3 ? (wk.y / (ntx * nty)) * zc : 0;
-    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
-    const int x = tx0 + lx, y = ty0 + ly;
-    const bool own = x < nx && y < ny;
+    double acc[MS];
+#pragma unroll
+    for (int i = 0; i < MS; ++i) acc[i] = 0;
     const T* vs = (const T*)m.vs;
-    T* P1 = (T*)m.P;
-    T* W0 = (T*)m.W;
-    T* W1 = (T*)m.W + (size_t)NC * sN;
-    T* C0 = (T*)m.C;
-    // the staged v* elements of this thread (plane offsets; beyond the walls
-    // cell 0 is loaded and zero staged)
-    int eoff[NE2];
-    bool eok[NE2];
-#pragma unroll
-    for (int k = 0; k < NE2; ++k) {
-        const int e = threadIdx.x + k * NT;
-        const int gx = modi(tx0 + e % HX2 - 2, nx);
-        int gy = ty0 + e / HX2 - 2;
-        bool ok = e < HXY2;
-        if (m.walls) ok = ok && gy >= 0 && gy < ny;
-        else gy = modi(gy, ny);
-        eok[k] = ok;
-        eoff[k] = ok ? gx + nx * gy : 0;
-    }
-    // the w elements of this thread: zero beyond the walls
-    bool wok[NE1];
-#pragma unroll
-    for (int k = 0; k < NE1; ++k) {
-        const int e = threadIdx.x + k * NT;
-        const int gy = ty0 + e / HX1 - 1;
-        wok[k] = e < HXY1 && !(m.walls && (gy < 0 || gy >= ny));
-    }
-    const int plane = nx * ny;
-    auto fetch = [&](int pz, T (&buf)[NE2][D]) {
-        const unsigned zo = (unsigned)(plane * (D == 3 ? modi(pz, nz) : 0));
-#pragma unroll
-        for (int k = 0; k < NE2; ++k)
-#pragma unroll
-            for (int a = 0; a < D; ++a) buf[k][a] = ld_at(vs + a * sN, zo + (unsigned)eoff[k]);
+    // (32-bit byte offsets from scalar bases, the row's part added per use:
+    // TO fields stay below 2^32 bytes)
+    auto row = [&](const T* base, unsigned zo, int r, unsigned x) {
+        return *(const T*)((const char*)base + (zo + yo[r + 1] + x));
     };
-    auto stage = [&](int sl, const T (&buf)[NE2][D]) {
+    // rows beyond the walls of a field count as zero
+    auto mask = [&](T (&a)[R]) {
+        if (!outm) return;   // uniform
 #pragma unroll
-        for (int k = 0; k < NE2; ++k) {
-            const int e = threadIdx.x + k * NT;
-            if (e < HXY2) {
+        for (int r = 0; r < R; ++r) a[r] = (outm >> (r + 1)) & 1 ? T(0) : a[r];
+    };
+    auto mask2 = [&](T (&a)[R + 2]) {
+        if (!outm) return;
 #pragma unroll
-                for (int a = 0; a < D; ++a) vt[sl][a][e] = eok[k] ? buf[k][a] : T(0);
+        for (int r = 0; r < R + 2; ++r) a[r] = (outm >> r) & 1 ? T(0) : a[r];
+    };
+    // x and y parts of one power, [1,2,1] along x and along y, of NP planes
+    // at once (one barrier)
+    constexpr int NP = D == 3 ? 2 : 1;
+    auto filter_xy = [&](int l, T (&a)[NP][R]) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T t = a[u][r] + lane_prev(a[u][r]);
+                a[u][r] = t + lane_next(t);
+            }
+        T lo[NP] = {}, hi[NP] = {};
+        if constexpr (NW > 1) {
+            T* e = edge + (size_t)l * (NW + 2) * NP * 128 + lane;
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+                e[((wv + 1) * NP + u) * 128] = a[u][0];
+                e[((wv + 1) * NP + u) * 128 + 64] = a[u][R - 1];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+                lo[u] = e[(wv * NP + u) * 128 + 64];
+                hi[u] = e[((wv + 2) * NP + u) * 128];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            T s = lo[u] + a[u][0];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T n = a[u][r] + (r + 1 < R ? a[u][r + 1 < R ? r + 1 : r] : hi[u]);
+                a[u][r] = s + n;
+                s = n;
             }
         }
     };
-    // xy part of B at the own cell of a tile t with row length H, own
-    // position c
-    auto bxy = [](const T* t, int c, int H) {
-        const T q0 = T(0.25) * (t[c - H - 1] + T(2) * t[c - H] + t[c - H + 1]);
-        const T q1 = T(0.25) * (t[c - 1] + T(2) * t[c] + t[c + 1]);
-        const T q2 = T(0.25) * (t[c + H - 1] + T(2) * t[c + H] + t[c + H + 1]);
-        return T(0.25) * q0 + T(0.5) * q1 + T(0.25) * q2;
-    };
-    // w = curl v* on the tile and its halo, from the staged planes z - 1,
-    // z, z + 1 (s0, s1, s2; the same slot in 2-D)
-    auto curl_tile = [&](int s0, int s1, int s2) {
+    auto own_row = [&](int r) { return ys + r >= y0 && ys + r < ye; };
+    T cr[MS][3], crr[MS][NL + 1];
+    T* dst[MS];
 #pragma unroll
-        for (int k = 0; k < NE1; ++k) {
-            const int e = threadIdx.x + k * NT;
-            if (e >= HXY1) continue;
-            const int p = (e / HX1 + 1) * HX2 + e % HX1 + 1;
-            T w[3];
-            if (D == 2) {
-                w[0] = T(0.5) * (vt[s1][1][p + 1] - vt[s1][1][p - 1]) -
-                       T(0.5) * (vt[s1][0][p + HX2] - vt[s1][0][p - HX2]);
-            } else {
-                const T dyvz = T(0.5) * (vt[s1][2 % D][p + HX2] - vt[s1][2 % D][p - HX2]);
-                const T dzvy = T(0.5) * (vt[s2][1][p] - vt[s0][1][p]);
-                const T dzvx = T(0.5) * (vt[s2][0][p] - vt[s0][0][p]);
-                const T dxvz = T(0.5) * (vt[s1][2 % D][p + 1] - vt[s1][2 % D][p - 1]);
-                const T dxvy = T(0.5) * (vt[s1][1][p + 1] - vt[s1][1][p - 1]);
-                const T dyvx = T(0.5) * (vt[s1][0][p + HX2] - vt[s1][0][p - HX2]);
-                w[0] = dyvz - dzvy;
-                w[1] = dzvx - dxvz;
-                w[2] = dxvy - dyvx;
+    for (int i = 0; i < MS; ++i) {
+        const int s = prm->ks[KIND][i];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) cr[i][j] = chain_r<T>(prm, s, j);
+#pragma unroll
+        for (int j = 0; j <= NL; ++j) crr[i][j] = chain_rr<T>(prm, s, j);
+        dst[i] = (T*)(KIND == 0 ? m.kV : m.W) + ((size_t)s * (KIND == 0 ? D : NC) + comp) * sN;
+    }
+    // sensitivities of the own rows from their powers w_0 .. w_NL, stored;
+    // densities
+    auto emit = [&](unsigned zo, const T (&w)[NL + 1][R]) {
+        if (!any_own || !ownx) return;
+#pragma unroll
+        for (int i = 0; i < MS; ++i) {
+            if (i >= nk) break;   // uniform
+            T v[R], d[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v[r] = crr[i][0] * w[0][r];
+#pragma unroll
+                for (int j = 1; j <= NL; ++j) v[r] = fma_(crr[i][j], w[j][r], v[r]);
+                d[r] = fma_(cr[i][2], w[2][r], fma_(cr[i][1], w[1][r], cr[i][0] * w[0][r]));
             }
 #pragma unroll
-            for (int a = 0; a < NC; ++a) wt[a % (ZC ? NC : 1)][ZC ? e : 0] = wok[k] ? w[a] : T(0);
+            for (int r = 0; r < R; ++r) {
+                if (!own_row(r)) continue;   // uniform
+                acc[i] = __builtin_fma((double)d[r], (double)d[r], acc[i]);
+                *(T*)((char*)dst[i] + (zo + yo[r + 1] + xb)) = v[r];
+            }
         }
     };
-    const int pv = (ly + 2) * HX2 + lx + 2;   // own cell in the v* tile
-    const int pw = (ly + 1) * HX1 + lx + 1;   // own cell in the w tile
     if constexpr (D == 2) {
-        T buf[NE2][D];
-        fetch(0, buf);
-        stage(0, buf);
-        __syncthreads();
-        if constexpr (ZC) {
-            if (doz) curl_tile(0, 0, 0);
-            __syncthreads();
-        }
-        if (!own) return;
-        const size_t ci = (size_t)x + (size_t)nx * y;
-        if (dov)
+        T a[R], b[R + 2];
+        if constexpr (CURL < 0) {
 #pragma unroll
-            for (int a = 0; a < D; ++a) st_fld(P1 + a * sN + ci, bxy(&vt[0][a][0], pv, HX2), WT);
-        if constexpr (ZC) {
-            if (doz) st_fld(W0 + ci, wt[0][pw], WT);
-            if (dow1) {
-                st_fld(W1 + ci, bxy(&wt[0][0], pw, HX1), WT);
-                st_fld(C0 + ci, T(0.5) * (wt[0][pw + HX1] - wt[0][pw - HX1]), WT);        // D_y w
-                st_fld(C0 + sN + ci, -(T(0.5) * (wt[0][pw + 1] - wt[0][pw - 1])), WT);    // -D_x w
-            }
+            for (int r = 0; r < R; ++r) a[r] = row(vs + comp * sN, 0, r, xb);
+        } else {
+            T c[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) { a[r] = row(vs + sN, 0, r, xp); c[r] = row(vs + sN, 0, r, xm); }
+#pragma unroll
+            for (int r = -1; r <= R; ++r) b[r + 1] = row(vs, 0, r, xb);
+            mask2(b);
+#pragma unroll
+            for (int r = 0; r < R; ++r) a[r] = (a[r] - c[r]) - (b[r + 2] - b[r]);
         }
+        mask(a);
+        T w[NL + 1][R], f[1][R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[0][r] = f[0][r] = a[r];
+#pragma unroll
+        for (int j = 1; j <= NL; ++j) {
+            filter_xy(j - 1, f);
+            mask(f[0]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) w[j][r] = f[0][r];
+        }
+        emit(0, w);
     } else {
-        // output planes [tz0, zend); v* staged on tz0 - 2 .. zend + 1, w
-        // formed on tz0 - 1 .. zend
-        const int zend = min(tz0 + zc, nz);
-        const int p0 = tz0 - 2, p1 = zend + 1;
-        T bva[D] = {}, bvb[D] = {};                 // B_xy v* at planes pz - 2, pz - 1
-        T oma[3] = {}, omb[3] = {};                 // w (own cell) at planes pz - 3, pz - 2
-        T bwa[3] = {}, bwb[3] = {};                 // B_xy w at planes pz - 3, pz - 2
-        T dxb[3] = {}, dyb[3] = {};                 // D_x w, D_y w at plane pz - 2
-        T buf[NE2][D];
-        fetch(p0, buf);
-        for (int pz = p0; pz <= p1; ++pz) {
-            const int sl = (pz - p0) % 3;
-            stage(sl, buf);
-            __syncthreads();
-            if (pz < p1) fetch(pz + 1, buf);
-            T bvn[D];
+        const unsigned plane = (unsigned)(nx * ny) * (unsigned)sizeof(T);
+        const int z0 = tz * m.czc, z1 = min(z0 + m.czc, nz);
+        const T* fa = CURL < 0 ? vs + comp * sN : CURL == 1 ? vs : vs + sN;
+        const T* fb = CURL == 2 ? vs : vs + 2 * sN;
+        // CURL 0: D_y fb - D_z fa; 1: D_z fa - D_x fb; 2: D_x fa - D_y fb.
+        // fa's z difference takes planes p - 1 and p + 1 (am, an); D_y takes
+        // fb's rows -1 .. R, D_x the rows at x + 1 and x - 1.
+        constexpr bool ZD = CURL == 0 || CURL == 1;
+        constexpr int NB = CURL < 0 ? 1 : (CURL == 1 ? 2 * R : R + 2);
+        T am[R], ac[R], an[2][R], ax[2][CURL == 2 ? R : 1], bn[2][NB];
+        T px[NL][R], pt[NL][R];             // per power: last plane's xy part; sum of the last two
+        T d[NL][NL][R];                     // w_j waiting for the highest power of their plane: d[j][0 .. NL - j - 1]
 #pragma unroll
-            for (int a = 0; a < D; ++a) bvn[a] = bxy(&vt[sl][a][0], pv, HX2);
-            if (dov && own && pz - 1 >= tz0 && pz - 1 < zend) {
-                const size_t ci = (size_t)x + (size_t)nx * (y + (size_t)ny * (pz - 1));
+        for (int r = 0; r < R; ++r) {
+            am[r] = ac[r] = T(0);
 #pragma unroll
-                for (int a = 0; a < D; ++a)
-                    st_fld(P1 + a * sN + ci, T(0.25) * bva[a] + T(0.5) * bvb[a] + T(0.25) * bvn[a], WT);
+            for (int l = 0; l < NL; ++l) {
+                px[l][r] = 0;
+                pt[l][r] = 0;
+#pragma unroll
+                for (int k = 0; k < NL - l; ++k) d[l][k][r] = 0;
             }
+        }
+        // planes of w_0: [pa, pb), two at a time (a plane past pb is loaded
+        // and filtered to no effect)
+        const int pa = z0 - NL, pb = z1 + NL;
+        const unsigned zlast = (unsigned)(nz - 1) * plane;
+        auto next = [&](unsigned z) { return z == zlast ? 0u : z + plane; };
+        unsigned za = (unsigned)modi(ZD ? pa - 1 : pa, nz) * plane;   // planes of the fa and fb rows fetched next
+        unsigned zb = (unsigned)modi(pa, nz) * plane;
+        auto fetch = [&] {
 #pragma unroll
-            for (int a = 0; a < D; ++a) { bva[a] = bvb[a]; bvb[a] = bvn[a]; }
-            if constexpr (ZC) {
-                if (doz && pz >= tz0) {
-                    // w at plane pz - 1 on the tile and its halo
-                    curl_tile((pz - 2 - p0) % 3, (pz - 1 - p0) % 3, sl);
-                    __syncthreads();
-                    T omn[3], bwn[3], dxn[3], dyn[3];
+            for (int u = 0; u < 2; ++u) {
 #pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        const T* t = &wt[a][0];
-                        omn[a] = t[pw];
-                        bwn[a] = bxy(t, pw, HX1);
-                        dxn[a] = T(0.5) * (t[pw + 1] - t[pw - 1]);
-                        dyn[a] = T(0.5) * (t[pw + HX1] - t[pw - HX1]);
-                    }
-                    if (own && pz - 1 >= tz0 && pz - 1 < zend) {
-                        const size_t ci = (size_t)x + (size_t)nx * (y + (size_t)ny * (pz - 1));
+                for (int r = 0; r < R; ++r) {
+                    an[u][r] = row(fa, za, r, CURL == 2 ? xp : xb);
+                    if constexpr (CURL == 2) ax[u][r] = row(fa, za, r, xm);
+                }
+                za = next(za);
+                if constexpr (CURL == 1) {
 #pragma unroll
-                        for (int a = 0; a < 3; ++a) st_fld(W0 + a * sN + ci, omn[a], WT);
-                    }
-                    if (dow1 && own && pz - 2 >= tz0 && pz - 2 < zend) {
-                        const size_t ci = (size_t)x + (size_t)nx * (y + (size_t)ny * (pz - 2));
+                    for (int r = 0; r < R; ++r) { bn[u][r] = row(fb, zb, r, xp); bn[u][R + r] = row(fb, zb, r, xm); }
+                } else if constexpr (CURL >= 0) {
 #pragma unroll
-                        for (int a = 0; a < 3; ++a)
-                            st_fld(W1 + a * sN + ci, T(0.25) * bwa[a] + T(0.5) * bwb[a] + T(0.25) * bwn[a], WT);
-                        // curl w at plane pz - 2, D_z from the planes below and above
-                        st_fld(C0 + ci, dyb[2] - T(0.5) * (omn[1] - oma[1]), WT);           // D_y w_z - D_z w_y
-                        st_fld(C0 + sN + ci, T(0.5) * (omn[0] - oma[0]) - dxb[2], WT);      // D_z w_x - D_x w_z
-                        st_fld(C0 + 2 * sN + ci, dxb[1] - dyb[0], WT);                      // D_x w_y - D_y w_x
-                    }
+                    for (int k = 0; k < NB; ++k) bn[u][k] = row(fb, zb, k - 1, xb);
+                }
+                zb = next(zb);
+            }
+        };
+        if constexpr (ZD) {
 #pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        oma[a] = omb[a]; omb[a] = omn[a];
-                        bwa[a] = bwb[a]; bwb[a] = bwn[a];
-                        dxb[a] = dxn[a]; dyb[a] = dyn[a];
-                    }
+            for (int r = 0; r < R; ++r) am[r] = row(fa, za, r, xb);
+            za = next(za);
+#pragma unroll
+            for (int r = 0; r < R; ++r) ac[r] = row(fa, za, r, xb);
+            za = next(za);
+        }
+        // w_0 of the two planes fetched last
+        auto form = [&](T (&a)[2][R]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if constexpr (CURL == 0 || CURL == 2) mask2(bn[u]);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if constexpr (CURL < 0) a[u][r] = an[u][r];
+                    const T below = u == 0 ? am[r] : ac[r];
+                    if constexpr (CURL == 0) a[u][r] = (bn[u][r + 2] - bn[u][r]) - (an[u][r] - below);    // D_y v_z - D_z v_y
+                    if constexpr (CURL == 1) a[u][r] = (an[u][r] - below) - (bn[u][r] - bn[u][R + r]);    // D_z v_x - D_x v_z
+                    if constexpr (CURL == 2) a[u][r] = (an[u][r] - ax[u][r]) - (bn[u][r + 2] - bn[u][r]); // D_x v_y - D_y v_x
                 }
             }
-            __syncthreads();
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Per-cell sensitivities of all E/Z QoIs (App. A):
-//   E: V = R R v = sum_j rr_j B^j v;
-//   Z: V = curl^T R R w = sum_j rr_j C_j with C_j = curl^T B^j w, formed by
-//      the binomial passes (2-D: curl^T psi = (D_y psi, -D_x psi); 3-D: curl).
-// Also returns the QoI densities 1/2 |R v|^2 and 1/2 |R w|^2 of the cell.
-// ---------------------------------------------------------------------------
-// Filter coefficients in the kernel's arithmetic type (FP32 copies are made
-// on the host, so both read them from scalar registers without conversion).
-template <typename T> __device__ __forceinline__ T coef_r(KParam* p, int s, int j);
-template <> __device__ __forceinline__ float coef_r<float>(KParam* p, int s, int j) { return p->rf[s][j]; }
-template <> __device__ __forceinline__ double coef_r<double>(KParam* p, int s, int j) { return p->r[s][j]; }
-template <typename T> __device__ __forceinline__ T coef_rr(KParam* p, int s, int j);
-template <> __device__ __forceinline__ float coef_rr<float>(KParam* p, int s, int j) { return p->rrf[s][j]; }
-template <> __device__ __forceinline__ double coef_rr<double>(KParam* p, int s, int j) { return p->rr[s][j]; }
-template <typename T> __device__ __forceinline__ T coef_cv(KCtl* c, int j);
-template <> __device__ __forceinline__ float coef_cv<float>(KCtl* c, int j) { return c->cvf[j]; }
-template <> __device__ __forceinline__ double coef_cv<double>(KCtl* c, int j) { return c->cv[j]; }
-template <typename T> __device__ __forceinline__ T coef_cw(KCtl* c, int j);
-template <> __device__ __forceinline__ float coef_cw<float>(KCtl* c, int j) { return c->cwf[j]; }
-template <> __device__ __forceinline__ double coef_cw<double>(KCtl* c, int j) { return c->cw[j]; }
-
-// C_jw = curl^T W_jw at cell (x, y, z) from the neighbours of W_jw: the
-// binomial passes store C_j only for j < jw.
-template <int LAT, typename T>
-__device__ __forceinline__ void top_curl(KMember& m, int jw, int x, int y, int z, T* out)
-{
-    using L = Lat<LAT>;
-    const unsigned sN = (unsigned)m.N;
-    const unsigned c = (unsigned)(x + m.nx * (y + m.ny * z));
-    const Nbr nb = nbr_at(c, x, y, z, m.nx, m.ny, m.nz, m.walls, L::D);
-    curlT_nb<L::D, T>((const T*)m.W + (size_t)jw * L::NC * sN, sN, c, nb, out);
-}
-
-// The top C_jw = curl^T W_jw of a cell in two steps, so that a caller can
-// hold the loads and form the curl later: the neighbour values (2-D: psi at
-// y+1, y-1, x+1, x-1; 3-D: w_z, w_y, w_x at the pairs of neighbours of
-// D_y w_z, D_z w_y, D_z w_x, D_x w_z, D_x w_y, D_y w_x), then central
-// differences (zero beyond the walls), without contraction.
-template <int LAT, typename T>
-__device__ __forceinline__ void top_curl_load(KMember& m, int jw, int x, int y, int z, T* r, bool& okm, bool& okp)
-{
-    using L = Lat<LAT>;
-    const unsigned sN = (unsigned)m.N;
-    const unsigned c = (unsigned)(x + m.nx * (y + m.ny * z));
-    const Nbr n = nbr_at(c, x, y, z, m.nx, m.ny, m.nz, m.walls, L::D);
-    const T* psi = (const T*)m.W + (size_t)jw * L::NC * sN;
-    okm = n.okm;
-    okp = n.okp;
-    if constexpr (L::D == 2) {
-        r[0] = ld_at(psi, n.yp); r[1] = ld_at(psi, n.ym);
-        r[2] = ld_at(psi, n.xp); r[3] = ld_at(psi, n.xm);
-    } else {
-        const T* ux = psi;
-        const T* uy = psi + sN;
-        const T* uz = psi + 2 * sN;
-        r[0] = ld_at(uz, n.yp); r[1] = ld_at(uz, n.ym);
-        r[2] = ld_at(uy, n.zp); r[3] = ld_at(uy, n.zm);
-        r[4] = ld_at(ux, n.zp); r[5] = ld_at(ux, n.zm);
-        r[6] = ld_at(uz, n.xp); r[7] = ld_at(uz, n.xm);
-        r[8] = ld_at(uy, n.xp); r[9] = ld_at(uy, n.xm);
-        r[10] = ld_at(ux, n.yp); r[11] = ld_at(ux, n.ym);
-    }
-}
-
-template <int D, typename T>
-__device__ __forceinline__ void top_curl_eval(const T* r, bool okm, bool okp, T* out)
-{
-#pragma clang fp contract(off)
-    auto y0 = [](bool ok, T v) { return ok ? v : T(0); };
-    if constexpr (D == 2) {
-        out[0] = T(0.5) * (y0(okp, r[0]) - y0(okm, r[1]));
-        out[1] = -(T(0.5) * (r[2] - r[3]));
-    } else {
-        const T dyuz = T(0.5) * (y0(okp, r[0]) - y0(okm, r[1]));
-        const T dzuy = T(0.5) * (r[2] - r[3]);
-        const T dzux = T(0.5) * (r[4] - r[5]);
-        const T dxuz = T(0.5) * (r[6] - r[7]);
-        const T dxuy = T(0.5) * (r[8] - r[9]);
-        const T dyux = T(0.5) * (y0(okp, r[10]) - y0(okm, r[11]));
-        out[0] = dyuz - dzuy;
-        out[1] = dzux - dxuz;
-        out[2] = dxuy - dyux;
-    }
-}
-
-// The fields a cell's sensitivities are formed from, loaded in one batch
-// (no branch between the loads, so that the loads of several cells can be
-// in flight together) and evaluated afterwards.
-template <int LAT, typename T, int MAXSA>
-struct CellIn {
-    T pv[kMaxPow + 1][Lat<LAT>::D];   // B^j v*, j = 0..kMaxPow (clamped to jv)
-    T wc[3][Lat<LAT>::NC];            // B^j w, j = 0..2 (clamped to jw)
-    T cv[kMaxPow][Lat<LAT>::D];       // stored C_j (clamped to jw - 1)
-    T nb[Lat<LAT>::D == 2 ? 4 : 12];  // W_jw at the neighbours of the top curl
-    bool okm, okp;
-    T kv[MAXSA][Lat<LAT>::D];         // kernel filters: V_s (clamped to nsa - 1)
-};
-
-template <int LAT, typename T, int MAXSA, bool KF>
-__device__ __forceinline__ void cell_load(KMember& m, KParam* prm, int x, int y, int z, CellIn<LAT, T, MAXSA>& in)
-{
-    const int cell = x + m.nx * (y + m.ny * z);
-    using L = Lat<LAT>;
-    constexpr int D = L::D, NC = L::NC;
-    const int jv = prm->jv, jw = prm->jw;
-    const size_t sN = (size_t)m.N;
-    const T* __restrict__ vs = (const T*)m.vs;
-    if constexpr (KF) {
-        const int nsa = prm->nsa;
-        const T* __restrict__ kV = (const T*)m.kV;
+            if constexpr (ZD) {
 #pragma unroll
-        for (int a = 0; a < D; ++a) in.pv[0][a] = vs[a * sN + cell];
-#pragma unroll
-        for (int s2 = 0; s2 < MAXSA; ++s2) {
-            const int sc = s2 < nsa ? s2 : nsa - 1;
-#pragma unroll
-            for (int a = 0; a < D; ++a) in.kv[s2][a] = kV[((size_t)sc * D + a) * sN + cell];
-        }
-        return;
-    }
-    const T* __restrict__ P = (const T*)m.P;
-    const T* __restrict__ W = (const T*)m.W;
-    // Every load is unconditional, with the power clamped to the highest one
-    // stored: a power above jv (jw) only ever meets a zero coefficient.
-#pragma unroll
-    for (int jj = 0; jj <= kMaxPow; ++jj) {
-        const int je = jj < jv ? jj : jv;
-        const T* src = je == 0 ? vs : P + (size_t)(je - 1) * D * sN;
-#pragma unroll
-        for (int a = 0; a < D; ++a) in.pv[jj][a] = src[a * sN + cell];
-    }
-    const bool hz = prm->has_z;
-#pragma unroll
-    for (int jj = 0; jj < 3; ++jj) {
-        const T* src = hz ? W + (size_t)(jj < jw ? jj : jw) * NC * sN : vs;   // (unused without Z QoIs)
-#pragma unroll
-        for (int a = 0; a < NC; ++a) in.wc[jj][a] = src[a * sN + cell];
-    }
-    // C_j = curl^T B^j w (Z sensitivities): the stored C_j for j < jw, the
-    // top one formed at evaluation from the neighbours of W_jw (no
-    // arithmetic here, so the loads of a next cell need not wait for these)
-    if (!hz) return;
-    top_curl_load<LAT, T>(m, jw, x, y, z, in.nb, in.okm, in.okp);
-    const T* __restrict__ Cc = (const T*)m.C;
-    const int jc = jw > 0 ? jw - 1 : 0;
-#pragma unroll
-    for (int jj = 0; jj < kMaxPow; ++jj) {
-        const T* src = Cc + (size_t)(jj < jc ? jj : jc) * D * sN;
-#pragma unroll
-        for (int a = 0; a < D; ++a) in.cv[jj][a] = src[a * sN + cell];
-    }
-}
-
-// The closure's filter coefficients of every E/Z QoI, read once per
-// workgroup ahead of the field loads (zero past nsa, so that those QoIs
-// contribute exact zeros), and its kinds (1 for Z).
-template <typename T, int MAXSA>
-struct SensCoef {
-    T r[MAXSA][3], rr[MAXSA][kMaxPow + 1];
-    int z[MAXSA];
-    int nsa, hz, jw;
-};
-
-template <typename T, int MAXSA>
-__device__ __forceinline__ void sens_coef(KParam* prm, SensCoef<T, MAXSA>& c)
-{
-    c.nsa = prm->nsa;
-    c.hz = prm->has_z;
-    c.jw = prm->jw;
-#pragma unroll
-    for (int s = 0; s < MAXSA; ++s) {
-        c.z[s] = prm->sa_kind[s];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) c.r[s][j] = coef_r<T>(prm, s, j);
-#pragma unroll
-        for (int j = 0; j <= kMaxPow; ++j) c.rr[s][j] = coef_rr<T>(prm, s, j);
-    }
-}
-
-template <int LAT, typename T, int MAXSA, bool KF>
-__device__ __forceinline__ void cell_eval(const SensCoef<T, MAXSA>& cf, const CellIn<LAT, T, MAXSA>& in,
-                                          T (&V)[MAXSA][Lat<LAT>::D], double (&qd)[MAXSA])
-{
-    using L = Lat<LAT>;
-    constexpr int D = L::D, NC = L::NC;
-    const int nsa = cf.nsa;
-    if constexpr (KF) {
-        // kernel filters: the sensitivities V_s are materialised; both E and Z
-        // QoIs are 1/2 <v*, V_s> (R self-adjoint, curl^T the adjoint of curl)
-#pragma unroll
-        for (int s2 = 0; s2 < MAXSA; ++s2) {
-            qd[s2] = 0;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                V[s2][a] = s2 < nsa ? in.kv[s2][a] : T(0);
-                qd[s2] += 0.5 * (double)(in.pv[0][a] * V[s2][a]);
+                for (int r = 0; r < R; ++r) { am[r] = an[0][r]; ac[r] = an[1][r]; }
             }
-        }
-        return;
-    }
+            mask(a[0]);
+            mask(a[1]);
+        };
+        fetch();
+        T a[2][R];
+        form(a);
+        unsigned zo = (unsigned)z0 * plane;   // output plane
+#pragma unroll 1
+        for (int p = pa; p < pb; p += 2) {
+            T w[2][NL + 1][R];
+            fetch();   // the next planes, in flight during this pair's filtering
+            // w_j of planes p - NL and p + 1 - NL: waiting ones first; the
+            // new ones take their places
+            auto queue = [&](int j) {
 #pragma unroll
-    for (int s = 0; s < MAXSA; ++s) {
-        qd[s] = 0;
+                for (int r = 0; r < R; ++r) {
+                    const int L = NL - j;   // planes w_j waits
+                    if (L == 0) { w[0][j][r] = a[0][r]; w[1][j][r] = a[1][r];}
+                    else if (L == 1) { w[0][j][r] = d[j][0][r]; w[1][j][r] = a[0][r]; d[j][0][r] = a[1][r]; }
+                    else {
+                        w[0][j][r] = d[j][0][r];
+                        w[1][j][r] = d[j][1][r];
 #pragma unroll
-        for (int a = 0; a < D; ++a) V[s][a] = 0;
-        if (s >= nsa) continue;
-        const T r0 = cf.r[s][0], r1 = cf.r[s][1], r2 = cf.r[s][2];
-        if (cf.z[s] == 0) {
+                        for (int k = 0; k + 2 < L; ++k) d[j][k][r] = d[j][k + 2][r];
+                        d[j][L - 2][r] = a[0][r];
+                        d[j][L - 1][r] = a[1][r];
+                    }
+                }
+            };
+            queue(0);
 #pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const T rv = r0 * in.pv[0][a] + r1 * in.pv[1][a] + r2 * in.pv[2][a];
-                qd[s] += 0.5 * (double)(rv * rv);
-                T vv = 0;
+            for (int j = 1; j <= NL; ++j) {
+                filter_xy(j - 1, a);
 #pragma unroll
-                for (int jj = 0; jj <= kMaxPow; ++jj) vv += cf.rr[s][jj] * in.pv[jj][a];
-                V[s][a] = vv;
+                for (int r = 0; r < R; ++r) {
+                    const T t0 = px[j - 1][r] + a[0][r], t1 = a[0][r] + a[1][r];
+                    px[j - 1][r] = a[1][r];
+                    a[0][r] = pt[j - 1][r] + t0;
+                    a[1][r] = t0 + t1;
+                    pt[j - 1][r] = t1;
+                }
+                mask(a[0]);
+                mask(a[1]);
+                queue(j);
             }
-        } else {
+            // the next pair's w_0, formed ahead of this pair's stores: loads
+            // and stores complete in one order, so a wait for the loads at the
+            // head of the next pair would wait for the stores as well
+            form(a);
 #pragma unroll
-            for (int a = 0; a < NC; ++a) {
-                const T rw = r0 * in.wc[0][a] + r1 * in.wc[1][a] + r2 * in.wc[2][a];
-                qd[s] += 0.5 * (double)(rw * rw);
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) asm volatile("" : "+v"(a[u][r]) : : "memory");
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (p + u < z0 + NL || p + u >= pb) continue;   // uniform
+                emit(zo, w[u]);
+                zo += plane;
             }
         }
     }
-    if (!cf.hz) return;
-    // Z sensitivities from C_j = curl^T B^j w: the stored ones for j < jw,
-    // the top one above
-    T ctop[D];
-    top_curl_eval<D, T>(in.nb, in.okm, in.okp, ctop);
+    if constexpr (NW > 1) __syncthreads();
+    block_sum<MS, NW>(acc, red);
+    if (threadIdx.x == 0) {
+        const int ncw = m.cnt * D;   // row length of part_q
 #pragma unroll
-    for (int s = 0; s < MAXSA; ++s) {
-        if (s >= nsa || cf.z[s] == 0) continue;
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            T vv = 0;
-#pragma unroll
-            for (int jj = 0; jj <= kMaxPow; ++jj)
-                vv += cf.rr[s][jj] * (jj < cf.jw && jj < kMaxPow ? in.cv[jj < kMaxPow ? jj : 0][a] : ctop[a]);
-            V[s][a] = vv;
-        }
+        for (int i = 0; i < MS; ++i)
+            if (i < nk) m.part_q[(size_t)prm->ks[KIND][i] * ncw + tile * (KIND == 0 ? D : NC) + comp] = 0.5 * acc[i];
     }
 }
 
+template <int LAT, typename T, int NL, int MS>
+__global__ __launch_bounds__(64 * chain_waves(Lat<LAT>::D), Lat<LAT>::D == 2 ? 1 : 2) void k_chain(
+    const DevMember* __restrict__ mems, const int2* __restrict__ work)
+{
+    using L = Lat<LAT>;
+    constexpr int D = L::D, NC = L::NC, NW = chain_waves(D);
+    __shared__ T edge[NW > 1 ? NL * (NW + 2) * 256 : 1];
+    __shared__ double red[MS * NW];
+    const int2 wk = work[blockIdx.x];
+    KMember& m = *kc(mems + wk.x);
+    KParam* prm = kc(m.prm);
+    const int tile = wk.y / (D + NC), job = wk.y % (D + NC);
+    if (prm->nk[job < D ? 0 : 1] == 0) return;   // uniform
+    if constexpr (NW > 1) {
+        for (int k = threadIdx.x; k < NL * 512; k += 64 * NW) {   // the slots beyond the first and last wavefront
+            const int l = k / 512, e = k % 512;
+            edge[(size_t)l * (NW + 2) * 256 + (e < 256 ? e : (NW + 1) * 256 + e - 256)] = T(0);
+        }
+        __syncthreads();
+    }
+    if (job < D) chain_job<LAT, T, NL, MS, -1>(m, prm, job, tile, edge, red);
+    else if (D == 2) chain_job<LAT, T, NL, MS, 2>(m, prm, 0, tile, edge, red);
+    else if (job == D) chain_job<LAT, T, NL, MS, D == 3 ? 0 : 2>(m, prm, 0, tile, edge, red);
+    else if (job == D + 1) chain_job<LAT, T, NL, MS, D == 3 ? 1 : 2>(m, prm, 1, tile, edge, red);
+    else chain_job<LAT, T, NL, MS, 2>(m, prm, 2, tile, edge, red);
+}
+
 // ---------------------------------------------------------------------------
-// K2c: per-cell QoIs, sensitivities and Gram products, FP64 partial sums per
+// K2c: per-cell sensitivities and Gram products, FP64 partial sums per
 // workgroup.  Workgroups cover one y row (2-D) or one y plane (3-D) each, so
-// the mean-profile partial sums stay separated by y.
-// Partial layout: q_sa[nsa], G_sa[nsa(nsa+1)/2], then (with MP QoIs)
-// U = sum v*_x and P_s = sum V_s,x.
+// the mean-profile partial sums stay separated by y.  Binomial closures: V_s
+// of an E QoI read, of a Z QoI formed as curl^T U_s and stored for the apply;
+// their QoI sums come from k_chain.  Kernel-filter and Fourier closures: every
+// V_s read, and the QoIs formed here as 1/2 <v*, V_s>.
+// Partial layout: q_sa[nsa] (kernel filters), G_sa[nsa(nsa+1)/2], then (with
+// MP QoIs) U = sum v*_x and P_s = sum V_s,x.
 // ---------------------------------------------------------------------------
-template <int LAT, typename T, int MAXSA, bool KF>
-__global__ __launch_bounds__(kBlock) void k_reduce(const DevMember* __restrict__ mems, const int2* __restrict__ work)
+// ME, MZ: most E and Z QoIs of a member (its E QoIs come first, so that the
+// loads of each kind have their own registers); ME = 0: MZ of either kind
+// (uneven closures); with KF, ME counts all.
+template <int LAT, typename T, int ME, int MZ, bool KF, bool WT>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) void k_reduce(
+    const DevMember* __restrict__ mems, const int2* __restrict__ work)
 {
     using L = Lat<LAT>;
-    constexpr int D = L::D;
-    constexpr int NG = MAXSA * (MAXSA + 1) / 2;
-    constexpr int NV = MAXSA + NG + 1 + MAXSA;
+    constexpr int D = L::D, NC = L::NC;
+    constexpr int MAXSA = ME + MZ, NG = MAXSA * (MAXSA + 1) / 2;
+    constexpr int NQ = KF ? MAXSA : 0;
+    constexpr int NV = NQ + NG + 1 + MAXSA;
     __shared__ double lds[NV * (kBlock / 64)];
     const int2 wk = work[blockIdx.x];
     KMember& m = *kc(mems + wk.x);
@@ -1610,54 +1375,83 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const DevMember* __restrict__
     const int nx = m.nx, ny = m.ny, nz = m.nz;
     const int y = wk.y / m.nbx2, bx = wk.y % m.nbx2;
     const int plane = nx * nz;
-    const int nsa = prm->nsa;
+    const int nsa = prm->nsa, ne = KF ? nsa : prm->nk[0];
     const bool hasmp = prm->nmp > 0;
+    const unsigned sN = (unsigned)m.N;
+    T* kV = (T*)m.kV;
+    const int nz0 = ME > 0 ? ne : 0;   // QoI of the first Z position
+    // QoI of position k of the accumulators; nsa or more: none
+    auto qoi = [&](int k) { return k < ME ? (k < ne ? k : nsa) : nz0 + k - ME; };
     double acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0;
-    SensCoef<T, MAXSA> cf;
-    sens_coef<T, MAXSA>(prm, cf);
-    // One cell at a time (NP = 1), its fields loaded in one batch before it
-    // is evaluated.  (Measured on MI355X: pairs of cells in FP32 took 197
-    // VGPRs and two waves per SIMD, 510 us on 384 x 192 x 192 against 434 us
-    // for single cells at three waves; 18.4 against 17.4 us on 96 x 48 x 48.)
-    // The additions keep the order of the cells.
-    constexpr int NP = 1;
-    for (int c = 0; c < m.cpt2; c += NP) {
-        const int pa = (bx * m.cpt2 + c) * kBlock + threadIdx.x;
-        if (pa >= plane) break;
-        bool has[NP];
-        CellIn<LAT, T, MAXSA> in[NP];
+    // one cell at a time, all its loads in flight before it is evaluated
+    for (int c = 0; c < m.cpt2; ++c) {
+        const int p = (bx * m.cpt2 + c) * kBlock + threadIdx.x;
+        if (p >= plane) break;
+        const int x = p % nx, z = p / nx;
+        const unsigned cell = (unsigned)(x + nx * (y + ny * z));
+        const Nbr n = nbr_at(cell, x, y, z, nx, ny, nz, m.walls, D);
+        T V[MAXSA][D], v0[D], ld[MZ > 0 ? MZ : 1][D == 2 ? 4 : 12];
+        if (KF) {
 #pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            has[u] = u == 0 || (c + u < m.cpt2 && pa + u * kBlock < plane);
-            const int p = has[u] ? pa + u * kBlock : pa;
-            const int x = p % nx, z = p / nx;
-            cell_load<LAT, T, MAXSA, KF>(m, prm, x, y, z, in[u]);
+            for (int a = 0; a < D; ++a) v0[a] = ld_at((const T*)m.vs + (size_t)a * sN, cell);
+        } else {
+            v0[0] = hasmp ? ld_at((const T*)m.vs, cell) : T(0);
         }
 #pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            if (!has[u]) break;
-            T V[MAXSA][D];
-            double qd[MAXSA];
-            cell_eval<LAT, T, MAXSA, KF>(cf, in[u], V, qd);
+        for (int s = 0; s < MZ; ++s) {
 #pragma unroll
-            for (int s = 0; s < MAXSA; ++s) acc[s] += qd[s];
-            int g = 0;
+            for (int k = 0; k < (D == 2 ? 4 : 12); ++k) ld[s][k] = 0;
+            const int q = nz0 + s;   // (the branches are uniform)
+            if (ME == 0 && q < ne) {
 #pragma unroll
-            for (int s = 0; s < MAXSA; ++s)
-#pragma unroll
-                for (int t2 = s; t2 < MAXSA; ++t2, ++g) {
-                    T d = 0;
-#pragma unroll
-                    for (int a = 0; a < D; ++a) d += V[s][a] * V[t2][a];
-                    acc[MAXSA + g] += (double)d;
-                }
-            if (hasmp) {
-                acc[MAXSA + NG] += (double)in[u].pv[0][0];
-#pragma unroll
-                for (int s = 0; s < MAXSA; ++s) acc[MAXSA + NG + 1 + s] += (double)V[s][0];
+                for (int a = 0; a < D; ++a) ld[s][a] = ld_at(kV + (size_t)(q * D + a) * sN, cell);
+            } else if (q < nsa) {
+                curlT_load<D, T>((const T*)m.W + (size_t)q * NC * sN, sN, n, ld[s]);
             }
+        }
+#pragma unroll
+        for (int s = 0; s < ME; ++s)
+#pragma unroll
+            for (int a = 0; a < D; ++a) V[s][a] = s < ne ? ld_at(kV + (size_t)(s * D + a) * sN, cell) : T(0);
+#pragma unroll
+        for (int s = 0; s < MZ; ++s) {
+            const int q = nz0 + s;
+            if (ME == 0 && q < ne) {
+#pragma unroll
+                for (int a = 0; a < D; ++a) V[s][a] = ld[s][a];
+                continue;
+            }
+            curlT_eval<D, T>(ld[s], n.okm, n.okp, V[ME + s]);
+            if (q < nsa) {
+#pragma unroll
+                for (int a = 0; a < D; ++a) st_fld_at(kV + (size_t)(q * D + a) * sN, cell, V[ME + s][a], WT);
+            }
+        }
+        if constexpr (KF) {
+#pragma unroll
+            for (int s = 0; s < MAXSA; ++s) {
+                double qd = 0;
+#pragma unroll
+                for (int a = 0; a < D; ++a) qd += 0.5 * (double)(v0[a] * V[s][a]);
+                acc[s] += qd;
+            }
+        }
+        int g = 0;
+#pragma unroll
+        for (int s = 0; s < MAXSA; ++s)
+#pragma unroll
+            for (int t2 = s; t2 < MAXSA; ++t2, ++g) {
+                T d = 0;
+#pragma unroll
+                for (int a = 0; a < D; ++a) d += V[s][a] * V[t2][a];
+                acc[NQ + g] += (double)d;
+            }
+        if (hasmp) {
+            acc[NQ + NG] += (double)v0[0];
+#pragma unroll
+            for (int s = 0; s < MAXSA; ++s) acc[NQ + NG + 1 + s] += (double)V[s][0];
         }
     }
     // band weights w_j(y) of this row (workgroup-uniform: scalar loads,
@@ -1675,18 +1469,18 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const DevMember* __restrict__
     const int t = threadIdx.x;
     const size_t nblk = (size_t)ny * m.nbx2;
     double* out = m.part_to + wk.y;
-    if (t < MAXSA) {
+    if (t < NQ) {
         if (t < nsa) out[t * nblk] = r;
-    } else if (t < MAXSA + NG) {
-        int g = t - MAXSA, sa = 0;   // (sa, t2), sa <= t2 < MAXSA, in the order of acc
-        while (g >= MAXSA - sa) { g -= MAXSA - sa; ++sa; }
-        const int t2 = sa + g;
-        if (t2 < nsa) out[(nsa + sa * nsa - sa * (sa - 1) / 2 + (t2 - sa)) * nblk] = r;
+    } else if (t < NQ + NG) {
+        int g = t - NQ, k = 0;   // positions (k, k + g), in the order of acc
+        while (g >= MAXSA - k) { g -= MAXSA - k; ++k; }
+        const int sa = qoi(k), t2 = qoi(k + g);
+        if (sa < nsa && t2 < nsa) out[(nsa + sa * nsa - sa * (sa - 1) / 2 + (t2 - sa)) * nblk] = r;
     } else if (hasmp && t < NV) {
         // mean-profile terms, weighted by the band weights of this row:
         // w_j(y) sum v*_x (column 0) and w_j(y) sum V_s,x (column 1 + s)
-        const int col = t - (MAXSA + NG);
-        if (col == 0 || col - 1 < nsa) {
+        const int k = t - (NQ + NG), col = k == 0 ? 0 : 1 + qoi(k - 1);
+        if (col <= nsa) {
             const int o = nsa + nsa * (nsa + 1) / 2;
 #pragma unroll
             for (int jm = 0; jm < kMaxQ; ++jm)
@@ -1740,7 +1534,7 @@ __device__ inline void lrs_normals(unsigned long long seed, long long step, int 
     }
 }
 
-__global__ void k_philox_test(const uint32_t* in, uint32_t* out, int n)
+static __global__ void k_philox_test(const uint32_t* in, uint32_t* out, int n)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -1749,7 +1543,7 @@ __global__ void k_philox_test(const uint32_t* in, uint32_t* out, int n)
     for (int k = 0; k < 4; ++k) out[4 * i + k] = c[k];
 }
 
-__global__ void k_normals_test(unsigned long long seed, long long step0, int nsteps, int n, double* out)
+static __global__ void k_normals_test(unsigned long long seed, long long step0, int nsteps, int n, double* out)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= nsteps) return;
@@ -1765,7 +1559,7 @@ __global__ void k_normals_test(unsigned long long seed, long long step0, int nst
 // block counts.  Slot -1 makes the member's LRS draw of the step, slots
 // -2 - c chunk c of the product of the LRS history with its rows of C.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_sum(const DevMember* __restrict__ mems, const int2* __restrict__ work)
+static __global__ __launch_bounds__(kBlock) void k_sum(const DevMember* __restrict__ mems, const int2* __restrict__ work)
 {
     __shared__ double red[kBlock / 64];
     const int2 wk = work[blockIdx.x];
@@ -1846,8 +1640,12 @@ __global__ __launch_bounds__(kBlock) void k_sum(const DevMember* __restrict__ me
 #pragma unroll 8
         for (int b = threadIdx.x; b < m.nst; b += kBlock) v[0] += m.part_stats[(size_t)b * 4 + slot];
     } else {
-        const int nblk = m.ny * m.nbx2;
-        const double* p = m.part_to + (size_t)(slot - 4) * nblk;
+        // the QoI sums of binomial closures are k_chain's, the others k_reduce's
+        KParam* prm = kc(m.prm);
+        const int s = slot - 4;
+        const bool chain = s < prm->nsa && !prm->kf;
+        const int nblk = chain ? m.cnt * (prm->sa_kind[s] == 0 ? m.cd : m.cnc) : m.ny * m.nbx2;
+        const double* p = chain ? m.part_q + (size_t)s * m.cnt * m.cd : m.part_to + (size_t)s * nblk;
 #pragma unroll 8
         for (int b = threadIdx.x; b < nblk; b += kBlock) v[0] += p[b];
     }
@@ -1883,9 +1681,8 @@ struct SolveLds {
     double sf[kMaxSums];
     double Cs[(kMaxQ + 1) * kMaxQ], es[kMaxQ], hps[kMaxHistChunks * kMaxQ];
     double q[kMaxQ], dq[kMaxQ], beta[kMaxQ], gam[kMaxQ], sc[kMaxQ], qs[kMaxQ];
-    double rrs[kMaxSA][kMaxPow + 1], gmps[kMaxQ * kMaxQ];
-    double cv[kMaxPow + 1], cw[kMaxPow + 1];
-    int kinds[kMaxSA], saslot[kMaxSA], mpslot[kMaxQ], mpband[kMaxQ];
+    double gmps[kMaxQ * kMaxQ];
+    int saslot[kMaxSA], mpslot[kMaxQ], mpband[kMaxQ];
     long long step;
     int sset, flags;
 };
@@ -1894,7 +1691,7 @@ struct SolveLds {
 // leader of a fused apply (the record, the step counter, a pending scale);
 // 2: another workgroup of a fused apply (LDS outputs only).  Every thread of
 // the workgroup calls it; pre() issues the caller's loads right after the
-// solve's own; S.cv, S.cw and S.beta hold the results.
+// solve's own; S.beta holds the result.
 template <int NTH, int ROLE, typename Pre>
 __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
 {
@@ -1915,22 +1712,21 @@ __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
     // loads complete in order, so the stores wait only for the solve's own.
     // (Measured on MI355X: the caller's loads issued after the staging
     // barrier instead are no faster.)
-    static_assert(kMaxSums <= kBlock && kMaxQ * kMaxQ <= kBlock && kMaxSA * (kMaxPow + 1) <= kBlock &&
+    static_assert(kMaxSums <= kBlock && kMaxQ * kMaxQ <= kBlock &&
                   (kMaxQ + 1) * kMaxQ <= 2 * kBlock, "one or two staged values per thread");
     const double r_sf = tid < 4 + m.npart ? m.sums[tid] : 0.0;   // 4 + npart sums
     const double r_c0 = prm->C[tid];
     const double r_c1 = tid < (kMaxQ + 1) * kMaxQ - kBlock ? prm->C[kBlock + tid] : 0.0;
     const double r_g = prm->gmp[tid];
-    const double r_rr = tid < kMaxSA * (kMaxPow + 1) ? (&prm->rr[0][0])[tid] : 0.0;
     double r_es = 0, r_s = 0;
-    int r_kind = 0, r_sas = 0, r_mps = 0, r_mpb = 0;
+    int r_sas = 0, r_mps = 0, r_mpb = 0;
     if (tid < kMaxQ) {
         r_es = ctl->lrs_e[tid];
         r_s = ctl->s[tid];
         r_mps = prm->mp_slot[tid];
         r_mpb = prm->mp_band[tid];
     }
-    if (tid < kMaxSA) { r_kind = prm->sa_kind[tid]; r_sas = prm->sa_slot[tid]; }
+    if (tid < kMaxSA) r_sas = prm->sa_slot[tid];
     long long r_step = 0;
     int r_sset = 0, r_flags = 0;
     if (tid == 0) {
@@ -1943,7 +1739,6 @@ __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
     S.Cs[tid] = r_c0;
     if (tid < (kMaxQ + 1) * kMaxQ - kBlock) S.Cs[kBlock + tid] = r_c1;
     S.gmps[tid] = r_g;
-    if (tid < kMaxSA * (kMaxPow + 1)) (&S.rrs[0][0])[tid] = r_rr;
     if (tid < kMaxQ) {
         S.es[tid] = r_es;
         S.sc[tid] = r_s;
@@ -1951,7 +1746,7 @@ __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
         S.mpband[tid] = r_mpb;
         S.q[tid] = 0; S.dq[tid] = 0; S.beta[tid] = 0; S.gam[tid] = 0;
     }
-    if (tid < kMaxSA) { S.kinds[tid] = r_kind; S.saslot[tid] = r_sas; }
+    if (tid < kMaxSA) S.saslot[tid] = r_sas;
     if (tid == 0) {
         S.step = r_step;
         S.sset = r_sset;
@@ -2103,27 +1898,11 @@ __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
         S.gam[tid] = S.dq[tid] * S.M[cur][tid][kMaxQ + tid];
     }
     __syncthreads();
-    // (g) dv coefficients, record, counters
+    // (g) beta of the sensitivities, record, counters
     if (ROLE == 0 && tid < kMaxSA) {
         const double b = tid < nsa ? S.beta[S.saslot[tid]] : 0.0;
         ctl->bsa[tid] = b;
         ctl->bsaf[tid] = (float)b;
-    }
-    if (tid <= kMaxPow) {
-        double a = 0, b = 0;
-        for (int s = 0; s < nsa; ++s) {
-            const double bs = S.beta[S.saslot[s]];
-            if (S.kinds[s] == 0) a += bs * S.rrs[s][tid];
-            else b += bs * S.rrs[s][tid];
-        }
-        S.cv[tid] = a;
-        S.cw[tid] = b;
-        if (ROLE == 0) {
-            ctl->cv[tid] = a;
-            ctl->cw[tid] = b;
-            ctl->cvf[tid] = (float)a;
-            ctl->cwf[tid] = (float)b;
-        }
     }
     if (ROLE <= 1) {
         lbm_qoi_rec* rec = m.recs + (size_t)(step % m.rec_cap);
@@ -2170,88 +1949,80 @@ __device__ void solve_member(KMember& m, SolveLds& S, Pre&& pre)
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_solve(const DevMember* __restrict__ mems, const int* __restrict__ work)
+static __global__ __launch_bounds__(kBlock) void k_solve(const DevMember* __restrict__ mems, const int* __restrict__ work)
 {
     __shared__ SolveLds S;
     KMember& m = *kc(mems + work[blockIdx.x]);
     solve_member<kBlock, 0>(m, S, [] {});
 }
 
-// K4: dv = sum_j cv_j B^j v* + sum_j cw_j C_j + e_x cmp(y) (eq. TO-ansatz
-// as sum_j beta_j V_j), and the SGS change of the cell's predictor
-// populations delta f_i = feq_i(rho, v* + dv) - feq_i(rho, v*): DEF, the
-// record (a, b) = (rho dv, 2 v* + dv) that the next stream-collide applies
-// during its pull; otherwise added in place to the populations the
-// stream-collide of this step wrote (the WALE substrate, whose velocity
+// K4: dv = sum_s beta_s V_s + e_x cmp(y) (eq. TO-ansatz as sum_i beta_i V_i),
+// and the SGS change of the cell's predictor populations
+// delta f_i = feq_i(rho, v* + dv) - feq_i(rho, v*): DEF, the record
+// (a, b) = (rho dv, 2 v* + dv) that the next stream-collide applies during
+// its pull; otherwise added in place to the populations the stream-collide of
+// this step wrote (small grids, and the WALE substrate, whose velocity
 // gradients need the complete post-streaming state).
 template <typename T> __device__ __forceinline__ T coef_bsa(KCtl* c, int s);
 template <> __device__ __forceinline__ float coef_bsa<float>(KCtl* c, int s) { return c->bsaf[s]; }
 template <> __device__ __forceinline__ double coef_bsa<double>(KCtl* c, int s) { return c->bsa[s]; }
 
-// One cell of the binomial apply: its fields (loaded by apply_load, the
-// power clamped to the highest one stored: cv_j (cw_j) is zero above jv
-// (jw), so the extra terms add exact zeros; the top C_jw from the
-// neighbours of W_jw), and in place the populations the stream-collide of
-// this step wrote.
-template <int LAT, typename T, bool DEF>
+// One cell of the apply: its fields (the sensitivities of QoIs past nsa are
+// zero) and, in place, the populations the stream-collide of this step wrote.
+template <int LAT, typename T, int MAXSA, bool DEF>
 struct ApplyIn {
-    T fv[kMaxPow + 1][Lat<LAT>::D], fc[kMaxPow][Lat<LAT>::D];
-    T nb[Lat<LAT>::D == 2 ? 4 : 12];   // W_jw at the neighbours the top curl takes
-    bool okm, okp;                     // y neighbours inside the walls
+    T vs[Lat<LAT>::D], V[MAXSA][Lat<LAT>::D];
     T rho1;                            // rho - 1
     T gi[DEF ? 1 : Lat<LAT>::Q];
 };
 
-template <int LAT, typename T, bool WT, bool DEF>
-__device__ __forceinline__ void apply_load(KMember& m, KParam* prm, int flip, int cell, ApplyIn<LAT, T, DEF>& in)
+template <int LAT, typename T, int MAXSA, bool WT, bool DEF>
+__device__ __forceinline__ void apply_load(KMember& m, KParam* prm, int flip, int cell, ApplyIn<LAT, T, MAXSA, DEF>& in)
 {
     using L = Lat<LAT>;
     constexpr int D = L::D;
-    const int nx = m.nx, ny = m.ny;
-    const int x = cell % nx, t = cell / nx, y = t % ny, z = t / ny;
     const size_t sN = (size_t)m.N;
-    const int jv = prm->jv, jw = prm->jw;
-    const T* __restrict__ vsp = (const T*)m.vs;
+    const int nsa = prm->nsa;
+    const T* __restrict__ kV = (const T*)m.kV;
     if constexpr (!DEF) {
         const T* g = (const T*)m.g[m.parity ^ flip ^ 1];
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) in.gi[i] = ld_fld<WT>(g + pop_at64<L::Q>(i, (size_t)cell));
     }
 #pragma unroll
-    for (int jj = 0; jj <= kMaxPow; ++jj) {
-        const int je = jj < jv ? jj : jv;
-        const T* src = je == 0 ? vsp : (const T*)m.P + (size_t)(je - 1) * D * sN;
+    for (int a = 0; a < D; ++a) in.vs[a] = ld_fld<WT>((const T*)m.vs + a * sN + cell);
 #pragma unroll
-        for (int a = 0; a < D; ++a) in.fv[jj][a] = ld_fld<WT>(src + a * sN + cell);
-    }
-    if (prm->has_z) {
-        top_curl_load<LAT, T>(m, jw, x, y, z, in.nb, in.okm, in.okp);
-        const int jc = jw > 0 ? jw - 1 : 0;
+    for (int s = 0; s < MAXSA; ++s)
 #pragma unroll
-        for (int jj = 0; jj < kMaxPow; ++jj) {
-            const T* srcc = (const T*)m.C + (size_t)(jj < jc ? jj : jc) * D * sN;
-#pragma unroll
-            for (int a = 0; a < D; ++a) in.fc[jj][a] = ld_fld<WT>(srcc + a * sN + cell);
-        }
-    }
+        for (int a = 0; a < D; ++a) in.V[s][a] = s < nsa ? ld_fld<WT>(kV + (size_t)(s * D + a) * sN + cell) : T(0);
     in.rho1 = ((const T*)m.rho)[cell];
 }
 
-// The rest of the cell: the SGS change (rho dv, 2 v* + dv) from dv (out) and
-// v*, stored as the record (DEF) or added in place to the populations.
-template <int LAT, typename T, bool WT, bool DEF>
-__device__ __forceinline__ void apply_finish(KMember& m, int flip, int cell, const T (&vs)[Lat<LAT>::D],
-                                             const T (&out)[3], T rho1, const T* gi)
+// The rest of the cell: dv from the coefficients beta, and the SGS change
+// (rho dv, 2 v* + dv), stored as the record (DEF) or added in place to the
+// populations.
+template <int LAT, typename T, int MAXSA, bool WT, bool DEF>
+__device__ __forceinline__ void apply_finish(KMember& m, int flip, int cell, const ApplyIn<LAT, T, MAXSA, DEF>& in,
+                                             const T (&beta)[MAXSA], bool hasmp, double cmp)
 {
     using L = Lat<LAT>;
     constexpr int D = L::D;
     const size_t sN = (size_t)m.N;
-    const T rho = T(1) + rho1;
+    T out[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        T acc = 0;
+#pragma unroll
+        for (int s = 0; s < MAXSA; ++s) acc = fma_(beta[s], in.V[s][a], acc);
+        out[a] = acc;
+    }
+    if (hasmp) out[0] += T(cmp);
+    const T rho = T(1) + in.rho1;
     T ra[D], rb[D];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         ra[a] = rho * out[a];
-        rb[a] = T(2) * vs[a] + out[a];
+        rb[a] = T(2) * in.vs[a] + out[a];
     }
     // (TO fields stay below 2^32 bytes: 32-bit offsets from scalar bases)
     if constexpr (DEF) {
@@ -2267,122 +2038,50 @@ __device__ __forceinline__ void apply_finish(KMember& m, int flip, int cell, con
 #pragma unroll
         for (int i = 0; i < L::Q; ++i)
             st_fld(g + pop_at64<L::Q>(i, (size_t)cell),
-                   add_df<LAT, T>(gi[i], i, [&](int k) { return ra[k]; }, [&](int k) { return rb[k]; }, e), WT);
+                   add_df<LAT, T>(in.gi[i], i, [&](int k) { return ra[k]; }, [&](int k) { return rb[k]; }, e), WT);
     }
 }
 
-// dv of a binomial cell from its fields and the coefficients: sum_j cv_j
-// B^j v* + sum_j cw_j C_j + e_x cmp(y).
-template <int LAT, typename T, bool DEF>
-__device__ __forceinline__ void apply_dv(const ApplyIn<LAT, T, DEF>& in, bool hz, int jw, const T (&cvc)[kMaxPow + 1],
-                                         const T (&cwc)[kMaxPow + 1], bool hasmp, double cmp, T (&out)[3])
-{
-    constexpr int D = Lat<LAT>::D;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        T s = cvc[0] * in.fv[0][a];
-#pragma unroll
-        for (int jj = 1; jj <= kMaxPow; ++jj) s += cvc[jj] * in.fv[jj][a];
-        out[a] = s;
-    }
-    if (hz) {
-        T ctop[D];
-        top_curl_eval<D, T>(in.nb, in.okm, in.okp, ctop);
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            T sacc = 0;
-#pragma unroll
-            for (int jj = 0; jj <= kMaxPow; ++jj) sacc += cwc[jj] * (jj < jw && jj < kMaxPow ? in.fc[jj < kMaxPow ? jj : 0][a] : ctop[a]);
-            out[a] += sacc;
-        }
-    }
-    if (hasmp) out[0] += T(cmp);
-}
-
-template <int LAT, typename T, bool KF, bool WT, bool DEF>
+template <int LAT, typename T, int MAXSA, bool WT, bool DEF>
 __global__ __launch_bounds__(kBlock) void k_apply(const DevMember* __restrict__ mems, const int2* __restrict__ work,
                                                   int flip)
 {
-    using L = Lat<LAT>;
-    constexpr int D = L::D;
     const int2 wk = work[blockIdx.x];
     KMember& m = *kc(mems + wk.x);
     KParam* prm = kc(m.prm);
-    const int N = m.N, nx = m.nx, ny = m.ny;
     const int cell = wk.y * kBlock + threadIdx.x;
-    if (cell >= N) return;
-    const int y = (cell / nx) % ny;
+    if (cell >= m.N) return;
     KCtl* ctl = kc(m.ctl);
-    T out[3] = {0, 0, 0};
-    T vs[D];
-    if constexpr (KF) {
-        // dv = sum_s beta_s V_s (clamped loads; beta_s = 0 past nsa)
-        const size_t sN = (size_t)N;
-        const T* __restrict__ vsp = (const T*)m.vs;
-        T gi[DEF ? 1 : L::Q];
-        if constexpr (!DEF) {
-            const T* g = (const T*)m.g[m.parity ^ flip ^ 1];
+    ApplyIn<LAT, T, MAXSA, DEF> in;
+    apply_load<LAT, T, MAXSA, WT, DEF>(m, prm, flip, cell, in);
+    T beta[MAXSA];
 #pragma unroll
-            for (int i = 0; i < L::Q; ++i) gi[i] = ld_fld<WT>(g + pop_at64<L::Q>(i, (size_t)cell));
-        }
-        const int nsa = prm->nsa;
-        const T* __restrict__ kV = (const T*)m.kV;
-#pragma unroll
-        for (int a = 0; a < D; ++a) vs[a] = vsp[a * sN + cell];
-        T kv[kMaxSA][D];
-#pragma unroll
-        for (int s2 = 0; s2 < kMaxSA; ++s2)
-#pragma unroll
-            for (int a = 0; a < D; ++a) kv[s2][a] = kV[((size_t)(s2 < nsa ? s2 : nsa - 1) * D + a) * sN + cell];
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-            T acc = 0;
-#pragma unroll
-            for (int s2 = 0; s2 < kMaxSA; ++s2) acc += coef_bsa<T>(ctl, s2) * kv[s2][a];
-            out[a] = acc;
-        }
-        if (prm->nmp > 0) out[0] += T(m.cmp[y]);
-        apply_finish<LAT, T, WT, DEF>(m, flip, cell, vs, out, ((const T*)m.rho)[cell], gi);
-    } else {
-        ApplyIn<LAT, T, DEF> in;
-        apply_load<LAT, T, WT, DEF>(m, prm, flip, cell, in);
-        T cvc[kMaxPow + 1], cwc[kMaxPow + 1];
-#pragma unroll
-        for (int jj = 0; jj <= kMaxPow; ++jj) {
-            cvc[jj] = coef_cv<T>(ctl, jj);
-            cwc[jj] = coef_cw<T>(ctl, jj);
-        }
-        const bool hasmp = prm->nmp > 0;
-        apply_dv<LAT, T, DEF>(in, prm->has_z, prm->jw, cvc, cwc, hasmp, hasmp ? m.cmp[y] : 0.0, out);
-#pragma unroll
-        for (int a = 0; a < D; ++a) vs[a] = in.fv[0][a];
-        apply_finish<LAT, T, WT, DEF>(m, flip, cell, vs, out, in.rho1, in.gi);
-    }
+    for (int s = 0; s < MAXSA; ++s) beta[s] = coef_bsa<T>(ctl, s);   // zero past nsa
+    const bool hasmp = prm->nmp > 0;
+    apply_finish<LAT, T, MAXSA, WT, DEF>(m, flip, cell, in, beta, hasmp, hasmp ? m.cmp[(cell / m.nx) % m.ny] : 0.0);
 }
 
-// The binomial apply with the member's solve at its head (launches of at
-// most kFusedApplyPairs workgroups).  A workgroup takes a pair of
+// The apply with the member's solve at its head (launches of at most
+// kFusedApplyPairs workgroups).  A workgroup takes a pair of
 // blocks of one member (work entry (member, p): blocks 2p and 2p + 1), issues
 // the loads of both cells of every thread, then solves on all its threads
 // while they are in flight (two waves per SIMD: every workgroup of the launch
 // is resident at once), and finishes both cells with the solve's
 // coefficients; cmp(y) = sum_j beta_mp_j w_j(y) is formed per cell in the
 // order and precision k_solve forms it.  Pair 0 is the member's leader.
-template <int LAT, typename T, bool WT, bool DEF>
+template <int LAT, typename T, int MAXSA, bool WT, bool DEF>
 __global__ __launch_bounds__(kBlock, 2) void k_apply_fs(const DevMember* __restrict__ mems,
                                                          const int2* __restrict__ work, int flip)
 {
-    using L = Lat<LAT>;
-    constexpr int D = L::D;
     __shared__ SolveLds S;
     const int2 wk = work[blockIdx.x];
     KMember& m = *kc(mems + wk.x);
     KParam* prm = kc(m.prm);
     const int N = m.N, nx = m.nx, ny = m.ny;
-    const int nmp = prm->nmp;
+    const int nmp = prm->nmp, nsa = prm->nsa;
     int cells[2];
     bool own[2];
-    ApplyIn<LAT, T, DEF> in[2];
+    ApplyIn<LAT, T, MAXSA, DEF> in[2];
     double wv[2][kMaxQ];
     // the cells' loads, issued right after the solve's own
     auto load = [&] {
@@ -2391,7 +2090,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_fs(const DevMember* __restr
             const int c = (2 * wk.y + u) * kBlock + threadIdx.x;
             own[u] = c < N;
             cells[u] = own[u] ? c : 0;   // a thread past the grid loads cell 0 and stores nothing
-            apply_load<LAT, T, WT, DEF>(m, prm, flip, cells[u], in[u]);
+            apply_load<LAT, T, MAXSA, WT, DEF>(m, prm, flip, cells[u], in[u]);
             const int y = (cells[u] / nx) % ny;
             if (nmp > 0) {
 #pragma unroll
@@ -2402,14 +2101,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_fs(const DevMember* __restr
     };
     if (wk.y == 0) solve_member<kBlock, 1>(m, S, load);
     else solve_member<kBlock, 2>(m, S, load);
-    __syncthreads();   // S.cv and S.cw of (g)
-    T cvc[kMaxPow + 1], cwc[kMaxPow + 1];
+    T beta[MAXSA];   // (S.beta is complete at the solve's last barrier)
 #pragma unroll
-    for (int jj = 0; jj <= kMaxPow; ++jj) {
-        cvc[jj] = T(S.cv[jj]);
-        cwc[jj] = T(S.cw[jj]);
-    }
-    const bool hz = prm->has_z;
+    for (int s = 0; s < MAXSA; ++s) beta[s] = s < nsa ? T(S.beta[S.saslot[s]]) : T(0);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         if (!own[u]) continue;
@@ -2418,12 +2112,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_fs(const DevMember* __restr
 #pragma unroll
             for (int jm = 0; jm < kMaxQ; ++jm) cmp += jm < nmp ? S.beta[S.mpslot[jm]] * wv[u][jm] : 0.0;
         }
-        T out[3] = {0, 0, 0};
-        apply_dv<LAT, T, DEF>(in[u], hz, prm->jw, cvc, cwc, nmp > 0, cmp, out);
-        T vs[D];
-#pragma unroll
-        for (int a = 0; a < D; ++a) vs[a] = in[u].fv[0][a];
-        apply_finish<LAT, T, WT, DEF>(m, flip, cells[u], vs, out, in[u].rho1, in[u].gi);
+        apply_finish<LAT, T, MAXSA, WT, DEF>(m, flip, cells[u], in[u], beta, nmp > 0, cmp);
     }
 }
 
@@ -2682,7 +2371,7 @@ __global__ __launch_bounds__(kBlock) void k_diag(const DevMember* __restrict__ m
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_fin_diag(const DevMember* __restrict__ mems, const int* __restrict__ work)
+static __global__ __launch_bounds__(kBlock) void k_fin_diag(const DevMember* __restrict__ mems, const int* __restrict__ work)
 {
     __shared__ double red[6 * (kBlock / 64)];
     KMember& m = *kc(mems + work[blockIdx.x]);
@@ -2711,6 +2400,7 @@ __global__ __launch_bounds__(kBlock) void k_fin_diag(const DevMember* __restrict
     }
 }
 
+#ifndef LBM_PART
 // ---------------------------------------------------------------------------
 // State access kernels.
 // ---------------------------------------------------------------------------
@@ -2909,7 +2599,7 @@ __global__ __launch_bounds__(kBlock) void k_proj_bx(const DevMember* __restrict_
     tmp[(size_t)n + idx] = uy;
 }
 
-__global__ __launch_bounds__(kBlock) void k_proj_by(int m, int ncx, int ncy, int fny, double rS,
+static __global__ __launch_bounds__(kBlock) void k_proj_by(int m, int ncx, int ncy, int fny, double rS,
                                                     const double* __restrict__ tmp, void* __restrict__ vout,
                                                     int vout_fp64)
 {
@@ -2986,11 +2676,88 @@ __global__ void k_stream_only(const DevMember* __restrict__ mems, int flip)
     for (int i = 0; i < L::Q; ++i) gd[pop_at64<L::Q>(i, (size_t)cell)] = f[i];
 }
 
+#endif  // LBM_PART
+
 // ---------------------------------------------------------------------------
 // Launch wrappers (host side), one instantiation per lattice/precision/kind.
 // ---------------------------------------------------------------------------
+// The TO step after the stream-collide: sensitivities, reduction, solve and
+// apply.
+template <int LAT, typename T>
+void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
+{
+    const dim3 blk(kBlock);
+    auto mark = [&](int k) {
+        if (ev) (void)hipEventRecord(ev[k], st);
+    };
+    if (g.kf && g.any_z) {   // the binomial chains form w in their first pass
+        if (g.wt) hipLaunchKernelGGL((k_curl<LAT, T, true>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
+        else hipLaunchKernelGGL((k_curl<LAT, T, false>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
+    }
+    mark(2);
+    if (g.kf) {
+        if (g.fprog) launch_fourier<LAT, T>(*g.fprog, st);
+        for (int l = 0; l < g.nklev; ++l) {
+            if (g.wt)
+                hipLaunchKernelGGL((k_kjob<LAT, T, true>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
+                                   g.kjobs + g.klev[l].x);
+            else
+                hipLaunchKernelGGL((k_kjob<LAT, T, false>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
+                                   g.kjobs + g.klev[l].x);
+        }
+    }
+    if (!g.kf && g.maxk > 0) {
+#define LBM_CHAIN(NLV, MSV)                                                                                    \
+    hipLaunchKernelGGL((k_chain<LAT, T, NLV, MSV>), dim3(g.nbc), dim3(64 * chain_waves(Lat<LAT>::D)), 0, st, g.mems, g.workc)
+        if (g.cnl == 2) { if (g.maxk <= 4) LBM_CHAIN(2, 4); else LBM_CHAIN(2, 8); }
+        else { if (g.maxk <= 4) LBM_CHAIN(4, 4); else LBM_CHAIN(4, 8); }
+#undef LBM_CHAIN
+    }
+    mark(3);
+#define LBM_REDUCE(MEV, MZV, KFV)                                                                            \
+    do {                                                                                                     \
+        if (g.wt) hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, true>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
+        else hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, false>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
+    } while (0)
+    if (g.kf) { if (g.maxsa <= 2) LBM_REDUCE(2, 0, true); else if (g.maxsa <= 6) LBM_REDUCE(6, 0, true); else LBM_REDUCE(8, 0, true); }
+    else if (g.maxk <= 1) LBM_REDUCE(1, 1, false);
+    else if (g.maxk <= 3) LBM_REDUCE(3, 3, false);
+    else if (g.maxk <= 4) LBM_REDUCE(4, 4, false);
+    else LBM_REDUCE(0, 8, false);
+#undef LBM_REDUCE
+    mark(4);
+    hipLaunchKernelGGL(k_sum, dim3(g.nbs), blk, 0, st, g.mems, g.works);
+    // the binomial apply forms the solve itself (one launch less per step)
+    const bool fused = fused_solve(g);
+    if (!fused) hipLaunchKernelGGL(k_solve, dim3(g.nmem), blk, 0, st, g.mems, g.workm);
+    mark(5);
+    if (!g.probe) {
+#define LBM_APPLY(SAV, DEFV)                                                                                 \
+    do {                                                                                                     \
+    if (fused && g.wt) hipLaunchKernelGGL((k_apply_fs<LAT, T, SAV, true, DEFV>), dim3(g.nbp), blk, 0, st, g.mems, g.workp, flip); \
+    else if (fused) hipLaunchKernelGGL((k_apply_fs<LAT, T, SAV, false, DEFV>), dim3(g.nbp), blk, 0, st, g.mems, g.workp, flip); \
+    else if (g.wt) hipLaunchKernelGGL((k_apply<LAT, T, SAV, true, DEFV>), dim3(g.nb1), blk, 0, st, g.mems, g.work1, flip); \
+    else hipLaunchKernelGGL((k_apply<LAT, T, SAV, false, DEFV>), dim3(g.nb1), blk, 0, st, g.mems, g.work1, flip); \
+    } while (0)
+        if (g.defer && g.substrate != LBM_WALE) {
+            if (g.maxsa <= 2) LBM_APPLY(2, true); else if (g.maxsa <= 6) LBM_APPLY(6, true); else LBM_APPLY(kMaxSA, true);
+        } else {
+            if (g.maxsa <= 2) LBM_APPLY(2, false); else if (g.maxsa <= 6) LBM_APPLY(6, false); else LBM_APPLY(kMaxSA, false);
+        }
+#undef LBM_APPLY
+    }
+}
+#ifdef LBM_PART
+#if LBM_PART != 0
+extern template void launch_to<LBM_D2Q9, float>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#endif
+#if LBM_PART != 3
+extern template void launch_to<LBM_D3Q19, float>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#endif
+#endif
+
 template <int LAT, typename T, int PREC>
-static void launch_step_group(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
+void launch_step_group(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
 {
     const dim3 blk(kBlock);
     if (g.nb1 == 0) return;
@@ -3060,86 +2827,7 @@ static void launch_step_group(const LaunchGroup& g, hipStream_t st, int flip, hi
 to_chain:
     mark(1);
     if (g.mode == 2) {
-        if (g.kf && g.any_z) {   // the binomial chains form w in their first pass
-            if (g.wt) hipLaunchKernelGGL((k_curl<LAT, T, true>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
-            else hipLaunchKernelGGL((k_curl<LAT, T, false>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
-        }
-        mark(2);
-        if (g.kf) {
-            if (g.fprog) launch_fourier<LAT, T>(*g.fprog, st);
-            for (int l = 0; l < g.nklev; ++l) {
-                if (g.wt)
-                    hipLaunchKernelGGL((k_kjob<LAT, T, true>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
-                                       g.kjobs + g.klev[l].x);
-                else
-                    hipLaunchKernelGGL((k_kjob<LAT, T, false>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
-                                       g.kjobs + g.klev[l].x);
-            }
-        }
-        if (!g.kf && g.npass >= 1) {
-#define LBM_BINOM1(TXV, ZCV)                                                                                    \
-    do {                                                                                                        \
-        if (g.wt) hipLaunchKernelGGL((k_binom1<LAT, T, TXV, ZCV, true>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, g.workb); \
-        else hipLaunchKernelGGL((k_binom1<LAT, T, TXV, ZCV, false>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, g.workb); \
-    } while (0)
-            if (Lat<LAT>::D == 3 && g.btx == kBinTXW) {
-                if (g.any_z) LBM_BINOM1((Lat<LAT>::D == 3 ? kBinTXW : kBinTX), true);
-                else LBM_BINOM1((Lat<LAT>::D == 3 ? kBinTXW : kBinTX), false);
-            } else {
-                if (g.any_z) LBM_BINOM1(kBinTX, true); else LBM_BINOM1(kBinTX, false);
-            }
-#undef LBM_BINOM1
-        }
-        for (int j = 2; j <= (g.kf ? 0 : g.npass); ++j) {
-#define LBM_BINOM(TXV, CHV)                                                                                    \
-    do {                                                                                                       \
-        if (g.wt) hipLaunchKernelGGL((k_binom<LAT, T, TXV, CHV, true>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, g.workb, j); \
-        else hipLaunchKernelGGL((k_binom<LAT, T, TXV, CHV, false>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, g.workb, j); \
-    } while (0)
-            const int ch = g.bmask[j - 1];
-            if (g.btx == kBinTXW) {
-                if (ch == 1) LBM_BINOM(kBinTXW, 1); else if (ch == 2) LBM_BINOM(kBinTXW, 2); else LBM_BINOM(kBinTXW, 3);
-            } else {
-                if (ch == 1) LBM_BINOM(kBinTX, 1); else if (ch == 2) LBM_BINOM(kBinTX, 2); else LBM_BINOM(kBinTX, 3);
-            }
-#undef LBM_BINOM
-        }
-        mark(3);
-#define LBM_REDUCE(KFV)                                                                                      \
-    do {                                                                                                     \
-        if (g.maxsa <= 2)                                                                                    \
-            hipLaunchKernelGGL((k_reduce<LAT, T, 2, KFV>), dim3(g.nbr), blk, 0, st, g.mems, g.workr);        \
-        else if (g.maxsa <= 6)                                                                               \
-            hipLaunchKernelGGL((k_reduce<LAT, T, 6, KFV>), dim3(g.nbr), blk, 0, st, g.mems, g.workr);        \
-        else                                                                                                 \
-            hipLaunchKernelGGL((k_reduce<LAT, T, kMaxSA, KFV>), dim3(g.nbr), blk, 0, st, g.mems, g.workr);   \
-    } while (0)
-        if (g.kf) LBM_REDUCE(true); else LBM_REDUCE(false);
-#undef LBM_REDUCE
-        mark(4);
-        hipLaunchKernelGGL(k_sum, dim3(g.nbs), blk, 0, st, g.mems, g.works);
-        // the binomial apply forms the solve itself (one launch less per step)
-        const bool fused = fused_solve(g);
-        if (!fused) hipLaunchKernelGGL(k_solve, dim3(g.nmem), blk, 0, st, g.mems, g.workm);
-        mark(5);
-        if (!g.probe) {
-#define LBM_APPLY(KFV, DEFV)                                                                                 \
-    do {                                                                                                     \
-        if (g.wt) hipLaunchKernelGGL((k_apply<LAT, T, KFV, true, DEFV>), dim3(g.nb1), blk, 0, st, g.mems, g.work1, flip); \
-        else hipLaunchKernelGGL((k_apply<LAT, T, KFV, false, DEFV>), dim3(g.nb1), blk, 0, st, g.mems, g.work1, flip); \
-    } while (0)
-#define LBM_APPLY_FS(DEFV)                                                                                   \
-    do {                                                                                                     \
-        if (g.wt) hipLaunchKernelGGL((k_apply_fs<LAT, T, true, DEFV>), dim3(g.nbp), blk, 0, st, g.mems, g.workp, flip); \
-        else hipLaunchKernelGGL((k_apply_fs<LAT, T, false, DEFV>), dim3(g.nbp), blk, 0, st, g.mems, g.workp, flip); \
-    } while (0)
-            const bool def = g.defer && g.substrate != LBM_WALE;
-            if (g.kf) { if (def) LBM_APPLY(true, true); else LBM_APPLY(true, false); }
-            else if (fused) { if (def) LBM_APPLY_FS(true); else LBM_APPLY_FS(false); }
-            else { if (def) LBM_APPLY(false, true); else LBM_APPLY(false, false); }
-#undef LBM_APPLY
-#undef LBM_APPLY_FS
-        }
+        launch_to<LAT, T>(g, st, flip, ev);
         mark(6);
     } else if (g.mode == 1) {
         hipLaunchKernelGGL((k_diag<LAT, T>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
@@ -3149,6 +2837,33 @@ to_chain:
         mark(2); mark(3); mark(4); mark(5); mark(6);
     }
 }
+
+// The step kernels of one lattice and precision are compiled in a translation
+// unit of their own (LBM_PART = 3 lattice + precision, built in parallel; the
+// two FP32 forms share the TO kernels of the shifted one), everything else in
+// the one without LBM_PART.
+#ifdef LBM_PART
+#if LBM_PART == 0
+template void launch_step_group<LBM_D2Q9, float, LBM_FP32_SHIFTED>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#elif LBM_PART == 1
+template void launch_step_group<LBM_D2Q9, double, LBM_FP64>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#elif LBM_PART == 2
+template void launch_step_group<LBM_D2Q9, float, LBM_FP32_PLAIN>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#elif LBM_PART == 3
+template void launch_step_group<LBM_D3Q19, float, LBM_FP32_SHIFTED>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#elif LBM_PART == 4
+template void launch_step_group<LBM_D3Q19, double, LBM_FP64>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#else
+template void launch_step_group<LBM_D3Q19, float, LBM_FP32_PLAIN>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+#endif
+}  // namespace lbm
+#else
+extern template void launch_step_group<LBM_D2Q9, float, LBM_FP32_SHIFTED>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+extern template void launch_step_group<LBM_D2Q9, double, LBM_FP64>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+extern template void launch_step_group<LBM_D2Q9, float, LBM_FP32_PLAIN>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+extern template void launch_step_group<LBM_D3Q19, float, LBM_FP32_SHIFTED>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+extern template void launch_step_group<LBM_D3Q19, double, LBM_FP64>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
+extern template void launch_step_group<LBM_D3Q19, float, LBM_FP32_PLAIN>(const LaunchGroup&, hipStream_t, int, hipEvent_t*);
 
 void launch_step(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
 {
@@ -3251,3 +2966,4 @@ int lattice_table(int lattice, int* c, double* w)
 }
 
 }  // namespace lbm
+#endif

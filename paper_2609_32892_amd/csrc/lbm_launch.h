@@ -47,9 +47,9 @@ struct FourierProg {
 // the work tables.
 struct LaunchGroup {
     int lattice, precision, substrate, mode;  // mode 0 plain, 1 plain + records, 2 TO
-    int any_z, maxpow, maxsa, npass;  // npass: binomial passes per step
-    int btx;            // binomial tile width of every member (kBinTX or kBinTXW)
-    int bmask[8];       // per binomial pass j = 1..npass: chains advanced by some member (1 v, 2 w)
+    int any_z, maxsa;
+    int maxk, cnl;      // binomial closures: most E or Z QoIs of a member; powers of the chains (2 or 4)
+    int btx;            // stream-collide tile width of every member (kBinTX or kBinTXW)
     const DevMember* mems;
     const int2* work1;  // cell kernels: (member, block of kBlock cells)
     int nb1;
@@ -57,8 +57,10 @@ struct LaunchGroup {
     int nbp;
     const int2* workr;  // reduce: (member, y * nbx2 + bx)
     int nbr;
-    const int2* workb;  // binomial filter: (member, xyz tile)
+    const int2* workb;  // tiled stream-collide: (member, xyz tile)
     int nbb;
+    const int2* workc;  // filter chains: (member, tile * (D + NC) + chain)
+    int nbc;
     const int2* works;  // cross-block sums: (member, value slot)
     int nbs;
     const int* workm;   // one workgroup per member
@@ -66,7 +68,7 @@ struct LaunchGroup {
     int probe;          // TO mode only: the QoI chain of the field already in v* (no
                         // stream-collide, no apply); see lbm_project_qoi
     int kf;             // kernel-filter closure (one member per group): its job levels
-    const KJob* kjobs;  // replace the binomial passes; kjobs in device memory,
+    const KJob* kjobs;  // replace the filter chains; kjobs in device memory,
     const int2* klev;   // klev[l] = (first job, job count) of level l (host memory)
     int nklev;
     const FourierProg* fprog;   // Fourier band QoIs (host memory; null if none)
