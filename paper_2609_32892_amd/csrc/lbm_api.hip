@@ -270,7 +270,7 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
     if (cs.nq > 0) {
         P.rho = take(e * N);
         P.vs = take(e * P.D * N);
-        P.W = take(cs.has_z ? e * (size_t)cs.nsa * P.NC * N : kAlign);
+        P.W = take(cs.has_z ? e * (size_t)(cs.nsa + (cs.kf ? 1 : 0)) * P.NC * N : kAlign);
         P.kV = take(e * (size_t)std::max(cs.nsa, 1) * P.D * N);
         P.cnl = std::max(cs.jv, cs.jw) <= 2 ? 2 : 4;
         chain_tiles(c, &P);
@@ -289,12 +289,11 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
         P.works = take(sizeof(int2) * P.nbs);
         P.hpart = take(sizeof(double) * kMaxQ * std::max(cs.nhc, 1));
         if (cs.kf) {
-            // kernel filters: [3][N] work fields: two per separable term, one
-            // per QoI, one more per Z QoI; tap tables; the job table of the
-            // pass program
-            P.kT = take(e * 3 * N * (size_t)(2 * cs.kslots + cs.nsa + cs.nzq));
-            P.ktaps = take(e * kMaxSA * 3 * (2 * kMaxRad + 1));
-            P.kjobs = take(sizeof(KJob) * (size_t)(2 * (2 * cs.kslots + cs.nsa) + cs.nzq + 1));
+            // kernel filters: [D][N] work fields, three per QoI (the two
+            // intermediates and R u); tap tables; the jobs of both applications
+            P.kT = take(e * P.D * N * (size_t)(3 * cs.nsa));
+            P.ktaps = take(e * kMaxSA * (kMaxRad + 1));
+            P.kjobs = take(sizeof(KFil) * 2 * kMaxSA);
             if (cs.nf) {
                 // Fourier bands: spectra of v* and w and one work spectrum (complex)
                 P.fspec_v = take(2 * e * P.D * N);
@@ -432,7 +431,7 @@ struct lbm_ctx {
     double* proj_tmp = nullptr;    // scratch of the separable bicubic projection (probe contexts)
     size_t proj_tmp_bytes = 0;
     size_t chist_cap = 0;
-    std::vector<int2> klev;        // kernel filters: (first job, job count) per launch level
+    int nkfil = 0, krad = 0;       // kernel filters: QoIs and largest radius
     FourierProg fprog{};           // Fourier band QoIs (plans made at set_closure)
     // captured step graphs, keyed by chunk length, per starting phase; valid
     // for launch parameters of version gver
@@ -472,17 +471,24 @@ struct lbm_batch {
 
 namespace {
 
-// The larger of a closure's numbers of binomial E and Z QoIs.
-int chain_kinds(const ClosureShape& cs)
-{
-    return cs.kf ? 0 : std::max(cs.nzb, cs.nsa - cs.nzb);
-}
+// The larger of a closure's numbers of E and Z QoIs.
+int chain_kinds(const ClosureShape& cs) { return std::max(cs.nzb, cs.nsa - cs.nzb); }
 
 // The member record's fields that follow the closure mode.
 void refresh_member(lbm_ctx* c)
 {
     c->hm.defer = c->defers() ? 1 : 0;
     c->hm.nst = c->defers() ? c->plan.nbb : c->plan.nb1;
+}
+
+// The kernel filters of a member in a launch group.
+void set_kfil(const lbm_ctx* c, LaunchGroup& g, int member)
+{
+    g.kmem = member;
+    g.kfil = (const KFil*)(c->arena + c->plan.kjobs);
+    g.nkfil = c->nkfil;
+    g.krad = c->krad;
+    g.kdim[0] = c->cfg.nx; g.kdim[1] = c->cfg.ny; g.kdim[2] = c->cfg.nz;
 }
 
 LaunchGroup ctx_group(const lbm_ctx* c)
@@ -503,9 +509,7 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.defer = c->defers();
     g.sep_solve = (c->cfg.tune_mem & 8) != 0;
     g.kf = c->cur.kf;
-    g.kjobs = (const KJob*)(c->arena + c->plan.kjobs);
-    g.klev = c->klev.data();
-    g.nklev = (int)c->klev.size();
+    set_kfil(c, g, 0);
     g.fprog = c->cur.nf ? &c->fprog : nullptr;
     g.mems = c->dm;
     g.work1 = (const int2*)(c->arena + c->plan.work1);
@@ -550,7 +554,7 @@ void drop_fourier(lbm_ctx* c)
     c->fprog = FourierProg{};
 }
 
-int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq)
+int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq, int nsa)
 {
     drop_fourier(c);
     if (fq.empty()) return LBM_OK;
@@ -577,136 +581,78 @@ int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq)
     f.band_e = A + c->plan.fband_e;
     f.band_z = A + c->plan.fband_z;
     f.vs = A + c->plan.vs;
-    f.w = A + c->plan.W;
+    f.w = A + c->plan.W + (size_t)nsa * NC * N * c->plan.esz;
     f.nx = c->cfg.nx; f.ny = c->cfg.ny; f.nz = c->cfg.nz;
     return LBM_OK;
 }
 
-// The kernel filters as sums of separable terms (Sec. 4.1): G_s is the
-// product of the 1-D truncated Gaussian g (radius alpha s, alpha = 4 in 2-D
-// and 2 in 3-D, normalised so that its cube sums to one); L_s is the sum over
-// the axes a of (dilated biharmonic l_s along a) x (box of width s across a),
-// scaled by 2 / sum |L_s| = 1 / (8 d s^d) (the d arms share the centre
-// block, where the kernel is 6 d; each arm adds 10 s^d in absolute value).
-// The identity is one term with unit taps.  The program: for E,
-// V = R(R v*); for Z, V = curl^T R(R w).  One application of R is a level of
-// x passes (one job per QoI and term), a level of y passes and a level of z
-// passes that also sums the terms (2-D: the y level sums them); a last level
-// forms the adjoint curls.  Writes the tap tables and the job table into the
-// arena and the level list into the context.
-int build_kjobs(lbm_ctx* c, const lbm_closure* cl)
+// The kernel filters of a closure (Sec. 4.1): G_s is the product of the 1-D
+// truncated Gaussian g (radius alpha s, alpha = 4 in 2-D and 2 in 3-D,
+// normalised so that its sum is one); L_s is the sum over the axes a of
+// (dilated biharmonic l_s along a) x (box of width s across a), scaled by
+// 2 / sum |L_s| = 1 / (8 d s^d) (the d arms share the centre block, where the
+// kernel is 6 d; each arm adds 10 s^d in absolute value).  The identity is a
+// Gaussian of taps 1, 0, 0.  For E, V = R(R v*); for Z, U = R(R w), whose
+// adjoint curl the reduce forms.  Writes the tap and job tables into the arena;
+// sa: the index of each QoI among the E/Z QoIs.
+int build_kfil(lbm_ctx* c, const lbm_closure* cl, const ClosureShape& cs, const std::vector<int>& sa)
 {
-    const int D = c->plan.D, NC = c->plan.NC, W = 2 * kMaxRad + 1;
+    const int D = c->plan.D, NC = c->plan.NC, W = kMaxRad + 1;
     const size_t N = c->plan.N, e = c->plan.esz;
     char* A = c->arena;
-    std::vector<double> taps((size_t)kMaxSA * 3 * W, 0.0);
-    int ntap = 0;
-    auto add = [&](const std::vector<double>& t) -> const void* {
-        std::copy(t.begin(), t.end(), taps.begin() + (size_t)ntap * W);
-        return A + c->plan.ktaps + (size_t)(ntap++) * W * e;
-    };
-    char* tcur = A + c->plan.kT;
-    auto field = [&]() { char* f = tcur; tcur += 3 * N * e; return f; };
-    struct Term { double coef; const void* tap[3]; int rad[3]; char* T1; char* T2; };
-    struct QJob { std::vector<Term> terms; bool E; int nc; const void* X; char* Vs; char* Y1; char* Y2; };
-    std::vector<QJob> qj;
+    std::vector<double> taps((size_t)kMaxSA * W, 0.0);
+    std::vector<KFil> first, second;
     std::vector<FourierQ> fq;
-    int isa = 0;
+    c->krad = 0;
     for (int k = 0; k < cl->nq; ++k) {
         const lbm_qoi_spec& q = cl->q[k];
         if (q.kind == LBM_QOI_MP) continue;
-        QJob j{};
-        const int sc = q.scale;
-        if (q.filter == LBM_FILT_FOURIER) {
-            // no separable terms: the band goes through hipFFT
-        } else if (q.filter == LBM_FILT_GAUSS) {
-            const int r = (D == 2 ? 4 : 2) * sc;
-            std::vector<double> g(2 * r + 1);
+        const int sc = q.scale, s = sa[k];
+        const bool E = q.kind == LBM_QOI_E;
+        char* out = E ? A + c->plan.kV + (size_t)s * D * N * e : A + c->plan.W + (size_t)s * NC * N * e;
+        if (q.filter == LBM_FILT_FOURIER) {   // the band goes through hipFFT
+            fq.push_back({E ? 1 : 0, q.scale, q.kmax, (void*)out});
+            continue;
+        }
+        KFil j{};
+        double* t = &taps[first.size() * W];
+        j.kind = q.filter == LBM_FILT_LAPL ? LBM_FILT_LAPL : LBM_FILT_GAUSS;
+        j.coef = 1.0;
+        if (q.filter == LBM_FILT_GAUSS) {
+            j.ra = (D == 2 ? 4 : 2) * sc;
             double sum = 0;
-            for (int i = -r; i <= r; ++i) sum += g[i + r] = std::exp(-(double)i * i / (2.0 * sc * sc));
-            for (double& v : g) v /= sum;
-            const void* tp = add(g);
-            j.terms.push_back({1.0, {tp, tp, tp}, {r, r, r}, nullptr, nullptr});
+            for (int i = -j.ra; i <= j.ra; ++i) sum += std::exp(-(double)i * i / (2.0 * sc * sc));
+            for (int i = 0; i <= j.ra; ++i) t[i] = std::exp(-(double)i * i / (2.0 * sc * sc)) / sum;
         } else if (q.filter == LBM_FILT_LAPL) {
             static const double l5[5] = {1, -4, 6, -4, 1};
-            const int rl = (5 * sc - 1) / 2, rb = (sc - 1) / 2;
-            std::vector<double> l(2 * rl + 1), b(2 * rb + 1, 1.0);
-            for (int i = 0; i < 5 * sc; ++i) l[i] = l5[i / sc];
-            const void* tl = add(l);
-            const void* tb = add(b);
+            j.ra = (5 * sc - 1) / 2;
+            j.rb = (sc - 1) / 2;
+            for (int i = 0; i <= j.ra; ++i) t[i] = l5[(j.ra + i) / sc];
             double sd = 1;
             for (int a = 0; a < D; ++a) sd *= sc;
-            const double coef = 1.0 / (8.0 * D * sd);
-            for (int a = 0; a < D; ++a) {
-                Term t{coef, {tb, tb, tb}, {rb, rb, rb}, nullptr, nullptr};
-                t.tap[a] = tl;
-                t.rad[a] = rl;
-                j.terms.push_back(t);
-            }
+            j.coef = 1.0 / (8.0 * D * sd);
         } else {
-            const void* t1 = add(std::vector<double>{1.0});
-            j.terms.push_back({1.0, {t1, t1, t1}, {0, 0, 0}, nullptr, nullptr});
+            j.ra = 2;
+            t[0] = 1.0;
         }
-        for (Term& t : j.terms) { t.T1 = field(); t.T2 = field(); }
-        j.E = q.kind == LBM_QOI_E;
-        j.nc = j.E ? D : NC;
-        j.X = j.E ? (const void*)(A + c->plan.vs) : (const void*)(A + c->plan.W);
-        j.Vs = A + c->plan.kV + (size_t)isa * D * N * e;
-        j.Y1 = field();
-        j.Y2 = j.E ? nullptr : field();
-        if (q.filter == LBM_FILT_FOURIER) fq.push_back({j.E ? 1 : 0, q.scale, q.kmax, j.E ? (void*)j.Vs : (void*)j.Y2});
-        qj.push_back(j);
-        isa++;
+        c->krad = std::max(c->krad, j.ra);
+        j.ncomp = E ? D : NC;
+        j.taps = A + c->plan.ktaps + first.size() * W * e;
+        char* work = A + c->plan.kT + (size_t)(3 * s) * D * N * e;   // y1, y2, R u
+        j.y1 = work;
+        j.y2 = work + D * N * e;
+        j.src = E ? A + c->plan.vs : A + c->plan.W + (size_t)cs.nsa * NC * N * e;
+        j.dst = work + 2 * D * N * e;
+        first.push_back(j);
+        j.src = j.dst;
+        j.dst = out;
+        second.push_back(j);
     }
-    const int per_app = D == 3 ? 3 : 2;
-    std::vector<std::vector<KJob>> lev(2 * per_app + 1);
-    for (int app = 0; app < 2; ++app) {
-        const int l0 = app * per_app;
-        for (const QJob& q : qj) {
-            const void* src = app == 0 ? q.X : (const void*)q.Y1;
-            void* dst = app == 0 ? (void*)q.Y1 : (q.E ? (void*)q.Vs : (void*)q.Y2);
-            KJob sum{};
-            sum.op = 0;
-            sum.axis = D == 3 ? 2 : 1;
-            sum.ncomp = q.nc;
-            sum.nterm = (int)q.terms.size();
-            sum.dst = dst;
-            for (size_t t = 0; t < q.terms.size(); ++t) {
-                const Term& tm = q.terms[t];
-                KJob x{};
-                x.op = 0; x.axis = 0; x.ncomp = q.nc; x.nterm = 1;
-                x.radius[0] = tm.rad[0]; x.coef[0] = 1.0; x.taps[0] = tm.tap[0]; x.src[0] = src; x.dst = tm.T1;
-                lev[l0].push_back(x);
-                if (D == 3) {
-                    KJob y = x;
-                    y.axis = 1; y.radius[0] = tm.rad[1]; y.taps[0] = tm.tap[1]; y.src[0] = tm.T1; y.dst = tm.T2;
-                    lev[l0 + 1].push_back(y);
-                }
-                const int fa = D == 3 ? 2 : 1;   // the axis whose pass sums the terms
-                sum.radius[t] = tm.rad[fa];
-                sum.coef[t] = tm.coef;
-                sum.taps[t] = tm.tap[fa];
-                sum.src[t] = D == 3 ? tm.T2 : tm.T1;
-            }
-            if (!q.terms.empty()) lev[l0 + per_app - 1].push_back(sum);
-        }
-    }
-    for (const QJob& q : qj)
-        if (!q.E) {
-            KJob cj{};
-            cj.op = 1; cj.ncomp = q.nc; cj.src[0] = q.Y2; cj.dst = q.Vs;
-            lev[2 * per_app].push_back(cj);
-        }
-    std::vector<KJob> all;
-    c->klev.clear();
-    for (const auto& l : lev) {
-        if (l.empty()) continue;
-        c->klev.push_back(make_int2((int)all.size(), (int)l.size()));
-        all.insert(all.end(), l.begin(), l.end());
-    }
-    int rc = all.empty() ? LBM_OK : upload(c, A + c->plan.kjobs, all.data(), sizeof(KJob) * all.size());
+    c->nkfil = (int)first.size();
+    first.insert(first.end(), second.begin(), second.end());
+    int rc = first.empty() ? LBM_OK : upload(c, A + c->plan.kjobs, first.data(), sizeof(KFil) * first.size());
     if (rc) return rc;
-    rc = build_fourier(c, fq);
+    rc = build_fourier(c, fq, cs.nsa);
     if (rc) return rc;
     // tap tables in the run's element type
     if (e == 8) return upload(c, A + c->plan.ktaps, taps.data(), sizeof(double) * taps.size());
@@ -768,14 +714,11 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         p.has_e = cs.has_e;
         p.spinup = cl->spinup;
         p.seed = cl->seed;
-        // the E/Z QoIs of a binomial closure in order of kind, E first
-        std::vector<int> order;
+        // the E/Z QoIs in order of kind, E first
+        std::vector<int> order, sa(cl->nq, 0);
         for (int kind : {LBM_QOI_E, LBM_QOI_Z, LBM_QOI_MP})
             for (int k = 0; k < cl->nq; ++k)
-                if (cl->q[k].kind == kind || (cs.kf && kind == LBM_QOI_E && cl->q[k].kind == LBM_QOI_Z)) {
-                    if (cs.kf && kind == LBM_QOI_Z) continue;
-                    order.push_back(k);
-                }
+                if (cl->q[k].kind == kind) order.push_back(k);
         int isa = 0, imp = 0;
         for (int k : order) {
             const lbm_qoi_spec& q = cl->q[k];
@@ -785,6 +728,7 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
                 imp++;
             } else {
                 p.sa_slot[isa] = k;
+                sa[k] = isa;
                 p.sa_kind[isa] = q.kind == LBM_QOI_E ? 0 : 1;
                 const int kind = p.sa_kind[isa];
                 p.ks[kind][p.nk[kind]++] = isa;
@@ -806,7 +750,7 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         const int nq = cl->nq;
         p.kf = cs.kf;
         if (cs.kf) {
-            rc = build_kjobs(c, cl);
+            rc = build_kfil(c, cl, cs, sa);
             if (rc) return rc;
         }
         if (cl->mode == LBM_CLOSURE_LRS) {
@@ -1714,9 +1658,7 @@ static int batch_build(lbm_batch* b)
             g.sep_solve = (c->cfg.tune_mem & 8) != 0;
             if (keys[gi].kfm >= 0) {
                 g.kf = 1;
-                g.kjobs = (const KJob*)(c->arena + c->plan.kjobs);
-                g.klev = c->klev.data();
-                g.nklev = (int)c->klev.size();
+                set_kfil(c, g, i);
                 g.fprog = c->cur.nf ? &c->fprog : nullptr;
             }
         }
@@ -1859,7 +1801,7 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
         const int m = g.mode;
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
         launches[1] = m == 2 && g.kf && g.any_z ? 1 : 0;
-        launches[2] = m == 2 ? (g.kf ? g.nklev : (g.maxk > 0 ? 1 : 0)) : 0;
+        launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.maxk > 0 ? 1 : 0)) : 0;
         launches[3] = m == 2 ? 1 : 0;
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)
         launches[5] = m == 2 ? 1 : (m == 1 ? 2 : 0);

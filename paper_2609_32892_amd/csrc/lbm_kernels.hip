@@ -929,8 +929,8 @@ __device__ __forceinline__ void curlT_eval(const T* r, bool okm, bool okp, T* ou
     }
 }
 
-// K2a: w = curl v* into W_0 (kernel-filter and Fourier closures, whose
-// filter passes start from w).
+// K2a: w = curl v* of kernel-filter and Fourier closures, whose filter passes
+// start from w, into the field after the nsa fields U_s.
 template <int LAT, typename T, bool WT>
 __global__ __launch_bounds__(kBlock) void k_curl(const DevMember* __restrict__ mems, const int2* __restrict__ work)
 {
@@ -946,7 +946,7 @@ __global__ __launch_bounds__(kBlock) void k_curl(const DevMember* __restrict__ m
     const Nbr nb = nbr_at(c, x, y, z, nx, ny, nz, m.walls, L::D);
     T w[3];
     curl_nb<L::D, T>((const T*)m.vs, (unsigned)N, c, nb, w);
-    T* W = (T*)m.W;
+    T* W = (T*)m.W + (size_t)kc(m.prm)->nsa * L::NC * N;
 #pragma unroll
     for (int a = 0; a < L::NC; ++a) st_fld_at(W + (size_t)a * N, c, w[a], WT);
 }
@@ -1349,16 +1349,20 @@ __global__ __launch_bounds__(64 * chain_waves(Lat<LAT>::D), Lat<LAT>::D == 2 ? 1
 // ---------------------------------------------------------------------------
 // K2c: per-cell sensitivities and Gram products, FP64 partial sums per
 // workgroup.  Workgroups cover one y row (2-D) or one y plane (3-D) each, so
-// the mean-profile partial sums stay separated by y.  Binomial closures: V_s
-// of an E QoI read, of a Z QoI formed as curl^T U_s and stored for the apply;
-// their QoI sums come from k_chain.  Kernel-filter and Fourier closures: every
-// V_s read, and the QoIs formed here as 1/2 <v*, V_s>.
-// Partial layout: q_sa[nsa] (kernel filters), G_sa[nsa(nsa+1)/2], then (with
-// MP QoIs) U = sum v*_x and P_s = sum V_s,x.
+// the mean-profile partial sums stay separated by y.  V_s of an E QoI is read,
+// that of a Z QoI formed as curl^T U_s and stored for the apply.  The QoI sums
+// of binomial closures come from k_chain; KF, kernel-filter and Fourier
+// closures: the QoIs are formed here as 1/2 <v*, V_s>.
+// Partial layout: q_sa[nsa] (KF), G_sa[nsa(nsa+1)/2], then (with MP QoIs)
+// U = sum v*_x and P_s = sum V_s,x.
+// FP32, 3-D, three QoIs of each kind: 76 B in and 36 B out per cell; measured
+// on MI355X 392 us on 384 x 192 x 192 (counters: 114 B in, the curl's
+// neighbours missing the L2; 5.5 TB/s) and 11 us on 96 x 48 x 48 (436 and 14.5
+// us with the powers of B as input).
 // ---------------------------------------------------------------------------
 // ME, MZ: most E and Z QoIs of a member (its E QoIs come first, so that the
 // loads of each kind have their own registers); ME = 0: MZ of either kind
-// (uneven closures); with KF, ME counts all.
+// (uneven closures).
 template <int LAT, typename T, int ME, int MZ, bool KF, bool WT>
 __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) void k_reduce(
     const DevMember* __restrict__ mems, const int2* __restrict__ work)
@@ -1375,7 +1379,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) voi
     const int nx = m.nx, ny = m.ny, nz = m.nz;
     const int y = wk.y / m.nbx2, bx = wk.y % m.nbx2;
     const int plane = nx * nz;
-    const int nsa = prm->nsa, ne = KF ? nsa : prm->nk[0];
+    const int nsa = prm->nsa, ne = prm->nk[0];
     const bool hasmp = prm->nmp > 0;
     const unsigned sN = (unsigned)m.N;
     T* kV = (T*)m.kV;
@@ -1470,7 +1474,8 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) voi
     const size_t nblk = (size_t)ny * m.nbx2;
     double* out = m.part_to + wk.y;
     if (t < NQ) {
-        if (t < nsa) out[t * nblk] = r;
+        const int q = qoi(t);
+        if (q < nsa) out[q * nblk] = r;
     } else if (t < NQ + NG) {
         int g = t - NQ, k = 0;   // positions (k, k + g), in the order of acc
         while (g >= MAXSA - k) { g -= MAXSA - k; ++k; }
@@ -2150,91 +2155,230 @@ __global__ __launch_bounds__(kBlock) void k_flush(const DevMember* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Kernel filters (Sec. 4.1, eq. gaussian and eq. laplace): each filter is a
-// sum of separable terms, applied as 1-D passes along x, y and z; every
-// QoI's and every term's pass of the same depth runs in one launch.
+// Kernel filters (Sec. 4.1, eq. gaussian and eq. laplace) as separable
+// passes: G_s = g (x) g (x) g; L_s = sum over the axes a of the dilated
+// biharmonic l along a and boxes b of width s across a, gathered by the z part:
+//   L_s f = b_z (b_y l_x f + l_y b_x f) + l_z (b_y b_x f)        (2-D: the
+//   first bracket alone).
+// k_kxy forms the x and y parts of one QoI's filter on 64 x 16 tiles staged in
+// LDS with the filter's halo, k_kz the z parts and the sum, each thread eight
+// planes of a cell column from one window in registers; R R takes the pair
+// twice.  One launch of each per application serves all QoIs and components
+// (job blockIdx.y).  Periodic wrap, zero padding on the wall axis at every
+// pass.  Radii are template parameters (a branch on the job's, uniform), so
+// the windows live in registers and the taps in scalar registers; outputs are
+// formed four (k_kxy) and eight (k_kz) at a time, which divides the loads per
+// output by as many.  Bound by the traffic of the intermediates, 830 B per
+// cell for the paper's 3-D set where one 1-D pass per launch level and term
+// moved 1900; measured on MI355X, 295 x 47 x 98, FP32: seven launches of 129 us ->
+// 98 (k_kxy, half of it vector instructions) and 53 us (k_kz, 4.9 TB/s), twice
+// each.  (A wavefront staging whole rows, without the index divisions, has
+// fewer loads in flight: 109 us.)
 // ---------------------------------------------------------------------------
-// K2k: one level of the program: job blockIdx.y, cells of block blockIdx.x.
-// op 0: dst = sum_t coef_t sum_r taps_t[r] src_t(. + r e_axis), periodic wrap
-// or zero padding on the wall axis; op 1: the adjoint curl (2-D:
-// (D_y psi, -D_x psi); 3-D: curl psi) with the wall padding of curl_at.
-template <int LAT, typename T, bool WT>
-__global__ __launch_bounds__(kBlock) void k_kjob(const DevMember* __restrict__ mems, const int2* __restrict__ work,
-                                                 const KJob* __restrict__ jobs)
+constexpr int kFilTX = 64, kFilTY = 16, kFilZ = 8;
+
+// c-weighted symmetric sum: t_0 w_c + sum_k t_k (w_(c-k) + w_(c+k)).
+template <int R, typename T>
+__device__ __forceinline__ T sym_taps(const T (&t)[R + 1], const T* w)
 {
-    using L = Lat<LAT>;
-    const LBM_K KJob& j = *kc(jobs + blockIdx.y);
-    const int2 wk = work[blockIdx.x];
-    KMember& m = *kc(mems + wk.x);
-    const int N = m.N, nx = m.nx, ny = m.ny, nz = m.nz;
-    const int cell = wk.y * kBlock + threadIdx.x;
-    if (cell >= N) return;
-    const int x = cell % nx, t = cell / nx, y = t % ny, z = t / ny;
-    T* __restrict__ dst = (T*)j.dst;
-    if (j.op == 0) {
-        const int axis = j.axis;
-        const int n = axis == 0 ? nx : (axis == 1 ? ny : nz);
-        const int pos = axis == 0 ? x : (axis == 1 ? y : z);
-        const int stride = axis == 0 ? 1 : (axis == 1 ? nx : nx * ny);
-        const bool pad = axis == 1 && m.walls;
-        const size_t line = (size_t)cell - (size_t)pos * stride;   // first cell of this cell's line
-        // all components at once (up to three load streams in flight; a
-        // component past ncomp re-reads component 0 and is not stored)
-        const int nc = j.ncomp;
-        const size_t o1 = nc > 1 ? (size_t)N : 0, o2 = nc > 2 ? 2 * (size_t)N : 0;
-        T out[3] = {0, 0, 0};
-        for (int tt = 0; tt < j.nterm; ++tt) {
-            const T* __restrict__ sc = (const T*)j.src[tt] + line;
-            const LBM_K T* tp = kc((const T*)j.taps[tt]);   // uniform: scalar loads
-            const int rad = j.radius[tt];
-            T s0 = 0, s1 = 0, s2 = 0;
-            if (pos - rad >= 0 && pos + rad < n) {
-                // the whole stencil inside the line: no wrap, no padding
-                const T* __restrict__ q = sc + (size_t)(pos - rad) * stride;
-#pragma unroll 2
-                for (int r = 0; r <= 2 * rad; ++r) {
-                    const T t = tp[r];
-                    const size_t k = (size_t)r * stride;
-                    s0 += t * q[k];
-                    s1 += t * q[o1 + k];
-                    s2 += t * q[o2 + k];
-                }
-            } else {
-                for (int r = -rad; r <= rad; ++r) {
-                    int p = pos + r;
-                    if (pad) {
-                        if (p < 0 || p >= n) continue;
-                    } else {
-                        p %= n;
-                        if (p < 0) p += n;
-                    }
-                    const T t = tp[r + rad];
-                    const size_t k = (size_t)p * stride;
-                    s0 += t * sc[k];
-                    s1 += t * sc[o1 + k];
-                    s2 += t * sc[o2 + k];
-                }
-            }
-            const T cf = T(j.coef[tt]);
-            out[0] += cf * s0;
-            out[1] += cf * s1;
-            out[2] += cf * s2;
+    T s = t[0] * w[R];
+#pragma unroll
+    for (int k = 1; k <= R; ++k) s = fma_(t[k], w[R - k] + w[R + k], s);
+    return s;
+}
+template <int R, typename T>
+__device__ __forceinline__ T box_sum(const T* w)
+{
+    T s = w[R];
+#pragma unroll
+    for (int k = 1; k <= R; ++k) s += w[R - k] + w[R + k];
+    return s;
+}
+
+// GAUSS: y1 = g_y g_x f.  LAPL: y1 = b_y l_x f + l_y b_x f, y2 = b_y b_x f (RB
+// > 0; for RB = 0 b is the identity).  D = 2: the filter itself into dst.
+template <int D, typename T, int KIND, int RA, int RB>
+__device__ __forceinline__ void kfil_xy(KMember& m, const LBM_K KFil& j, int tile, int comp, T* sm)
+{
+    constexpr int TX = kFilTX, TY = kFilTY, HX = TX + 2 * RA, HY = TY + 2 * RA, SX = (HX + 3) / 4 * 4;
+    constexpr bool GA = KIND == LBM_FILT_GAUSS;
+    constexpr int RY = GA ? RA : RB;         // rows of A_x f beyond the tile
+    T* f = sm;                               // [HY][SX]
+    T* ax = f + HY * SX;                     // A_x f, rows -RY .. TY + RY
+    T* bx = ax + (TY + 2 * RY) * TX;         // b_x f, all rows (RB > 0)
+    const int nx = m.nx, ny = m.ny, tid = threadIdx.x;
+    const int ntx = (nx + TX - 1) / TX, nty = (ny + TY - 1) / TY;
+    const int x0 = tile % ntx * TX, y0 = tile / ntx % nty * TY, z = tile / (ntx * nty);
+    const size_t sN = (size_t)m.N;
+    const unsigned zo = (unsigned)z * (unsigned)(nx * ny);
+    const T* src = (const T*)j.src + comp * sN;
+    const LBM_K T* tp = kc((const T*)j.taps);
+    T t[RA + 1];
+#pragma unroll
+    for (int k = 0; k <= RA; ++k) t[k] = tp[k];
+    for (int e = tid; e < HY * HX; e += kBlock) {
+        const int hx = e % HX, hy = e / HX;
+        int gx = wrapi(x0 + hx - RA, nx), gy = y0 + hy - RA;
+        if ((unsigned)gx >= (unsigned)nx) gx = modi(gx, nx);
+        bool ok = true;
+        if (m.walls) ok = gy >= 0 && gy < ny;
+        else {
+            gy = wrapi(gy, ny);
+            if ((unsigned)gy >= (unsigned)ny) gy = modi(gy, ny);
         }
-        st_fld(dst + cell, out[0], WT);
-        if (nc > 1) st_fld(dst + (size_t)N + cell, out[1], WT);
-        if (nc > 2) st_fld(dst + 2 * (size_t)N + cell, out[2], WT);
-        return;
+        f[hy * SX + hx] = ok ? ld_at(src, zo + (unsigned)(gx + nx * gy)) : T(0);
     }
-    const T* __restrict__ src = (const T*)j.src[0];
-    if constexpr (L::D == 2) {
-        dst[cell] = T(0.5) * (fld(src, x, y + 1, z, nx, ny, nz, m.walls) - fld(src, x, y - 1, z, nx, ny, nz, m.walls));
-        dst[(size_t)N + cell] =
-            -T(0.5) * (fld(src, x + 1, y, z, nx, ny, nz, m.walls) - fld(src, x - 1, y, z, nx, ny, nz, m.walls));
+    __syncthreads();
+    for (int q = tid; q < HY * (TX / 4); q += kBlock) {
+        const int r = q / (TX / 4), c = q % (TX / 4) * 4;
+        const bool a_row = GA || (r >= RA - RY && r < RA + TY + RY);
+        if (!a_row && RB == 0) continue;
+        T w[4 + 2 * RA];
+#pragma unroll
+        for (int k = 0; k < 4 + 2 * RA; ++k) w[k] = f[r * SX + c + k];
+        if (a_row) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ax[(r - (RA - RY)) * TX + c + k] = sym_taps<RA, T>(t, w + k);
+        }
+        if constexpr (RB > 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bx[r * TX + c + k] = box_sum<RB, T>(w + k + RA - RB);
+        }
+    }
+    __syncthreads();
+    const int lx = tid % TX, yq = tid / TX * 4, x = x0 + lx;
+    if (x >= nx) return;
+    T o1[4], o2[4];
+    if constexpr (GA) {
+        T w[4 + 2 * RA];
+#pragma unroll
+        for (int k = 0; k < 4 + 2 * RA; ++k) w[k] = ax[(yq + k) * TX + lx];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o1[k] = sym_taps<RA, T>(t, w + k);
     } else {
-        T w[3];
-        curl_at<3, T>(src, (size_t)N, x, y, z, nx, ny, nz, m.walls, w);
-        for (int a = 0; a < 3; ++a) dst[(size_t)a * N + cell] = w[a];
+        T w[4 + 2 * RA], u[4 + 2 * RB];
+#pragma unroll
+        for (int k = 0; k < 4 + 2 * RA; ++k) w[k] = RB > 0 ? bx[(yq + k) * TX + lx] : f[(yq + k) * SX + lx + RA];
+#pragma unroll
+        for (int k = 0; k < 4 + 2 * RB; ++k) u[k] = ax[(yq + k) * TX + lx];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            o1[k] = box_sum<RB, T>(u + k) + sym_taps<RA, T>(t, w + k);
+            o2[k] = box_sum<RB, T>(w + k + RA - RB);
+        }
     }
+    T* d1 = (T*)(D == 2 ? j.dst : j.y1) + comp * sN;
+    T* d2 = (T*)j.y2 + comp * sN;
+    const T cf = T(j.coef);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int y = y0 + yq + k;
+        if (y >= ny) break;
+        const unsigned c = zo + (unsigned)(x + nx * y);
+        st_at(d1, c, D == 2 ? cf * o1[k] : o1[k]);
+        if (D == 3 && !GA && RB > 0) st_at(d2, c, o2[k]);
+    }
+}
+
+// GAUSS: dst = g_z y1.  LAPL: dst = coef (b_z y1 + l_z y2), y2 the source for
+// RB = 0.
+template <typename T, int KIND, int RA, int RB>
+__device__ __forceinline__ void kfil_z(KMember& m, const LBM_K KFil& j, int blk, int comp)
+{
+    constexpr int NO = kFilZ;
+    constexpr bool GA = KIND == LBM_FILT_GAUSS;
+    const unsigned plane = (unsigned)(m.nx * m.ny);
+    const int nz = m.nz, nb = (int)((plane + kBlock - 1) / kBlock);
+    const unsigned c = (unsigned)(blk % nb) * kBlock + threadIdx.x;
+    const int z0 = blk / nb * NO;
+    if (c >= plane) return;
+    const size_t sN = (size_t)m.N;
+    const T* a = (const T*)(GA ? j.y1 : (RB > 0 ? j.y2 : j.src)) + comp * sN;
+    const T* b = (const T*)j.y1 + comp * sN;
+    const LBM_K T* tp = kc((const T*)j.taps);
+    T t[RA + 1];
+#pragma unroll
+    for (int k = 0; k <= RA; ++k) t[k] = tp[k];
+    T w[NO + 2 * RA], u[GA ? 1 : NO + 2 * RB];
+    unsigned zo = (unsigned)modi(z0 - RA, nz) * plane;   // (uniform)
+    const unsigned zl = (unsigned)(nz - 1) * plane;
+#pragma unroll
+    for (int k = 0; k < NO + 2 * RA; ++k) {
+        w[k] = ld_at(a, zo + c);
+        if constexpr (!GA) {
+            if (k >= RA - RB && k < RA + RB + NO) u[k - (RA - RB)] = ld_at(b, zo + c);
+        }
+        zo = zo == zl ? 0u : zo + plane;
+    }
+    T* dst = (T*)j.dst + comp * sN;
+    const T cf = T(j.coef);
+#pragma unroll
+    for (int k = 0; k < NO; ++k) {
+        if (z0 + k >= nz) break;
+        T o;
+        if constexpr (GA) o = sym_taps<RA, T>(t, w + k);
+        else o = cf * (box_sum<RB, T>(u + k) + sym_taps<RA, T>(t, w + k));
+        st_at(dst, (unsigned)(z0 + k) * plane + c, o);
+    }
+}
+
+// The variants: GAUSS radii 2 (also the identity), 4, .., 12; LAPL radius 2, 7
+// and 12 (s = 1, 3, 5; boxes of radius 0, 1, 2).
+#define LBM_KFIL_SWITCH(CALL)                                  \
+    switch (j.kind * 16 + j.ra) {                              \
+    case LBM_FILT_GAUSS * 16 + 2: CALL(LBM_FILT_GAUSS, 2, 0); break;   \
+    case LBM_FILT_GAUSS * 16 + 4: CALL(LBM_FILT_GAUSS, 4, 0); break;   \
+    case LBM_FILT_GAUSS * 16 + 6: CALL(LBM_FILT_GAUSS, 6, 0); break;   \
+    case LBM_FILT_GAUSS * 16 + 8: CALL(LBM_FILT_GAUSS, 8, 0); break;   \
+    case LBM_FILT_GAUSS * 16 + 10: CALL(LBM_FILT_GAUSS, 10, 0); break; \
+    case LBM_FILT_GAUSS * 16 + 12: CALL(LBM_FILT_GAUSS, 12, 0); break; \
+    case LBM_FILT_LAPL * 16 + 2: CALL(LBM_FILT_LAPL, 2, 0); break;     \
+    case LBM_FILT_LAPL * 16 + 7: CALL(LBM_FILT_LAPL, 7, 1); break;     \
+    case LBM_FILT_LAPL * 16 + 12: CALL(LBM_FILT_LAPL, 12, 2); break;   \
+    }
+
+// Work of a filter launch in the XCDs' order: workgroup b runs on XCD b mod 8
+// and takes item (b mod 8) q + b / 8 of each XCD's q; none past n.
+__device__ __forceinline__ int xcd_item(int n)
+{
+    const int q = (n + 7) / 8, b = (int)blockIdx.x;
+    return (b & 7) * q + (b >> 3) < n && (b >> 3) < q ? (b & 7) * q + (b >> 3) : -1;
+}
+
+template <int LAT, typename T>
+__global__ __launch_bounds__(kBlock) void k_kxy(const DevMember* __restrict__ mems, int mem,
+                                               const KFil* __restrict__ jobs, int n)
+{
+    extern __shared__ __align__(16) unsigned char kfil_lds[];
+    constexpr int D = Lat<LAT>::D;
+    const LBM_K KFil& j = *kc(jobs + blockIdx.y / D);
+    const int comp = blockIdx.y % D, item = xcd_item(n);
+    if (item < 0 || comp >= j.ncomp) return;   // uniform
+    KMember& m = *kc(mems + mem);
+    T* sm = (T*)kfil_lds;
+#define LBM_KXY(KIND, RA, RB) kfil_xy<D, T, KIND, RA, RB>(m, j, item, comp, sm)
+    LBM_KFIL_SWITCH(LBM_KXY)
+#undef LBM_KXY
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_kz(const DevMember* __restrict__ mems, int mem,
+                                               const KFil* __restrict__ jobs, int n)
+{
+    const LBM_K KFil& j = *kc(jobs + blockIdx.y / 3);
+    const int comp = blockIdx.y % 3, item = xcd_item(n);
+    if (item < 0 || comp >= j.ncomp) return;
+    KMember& m = *kc(mems + mem);
+#define LBM_KZ(KIND, RA, RB) kfil_z<T, KIND, RA, RB>(m, j, item, comp)
+    LBM_KFIL_SWITCH(LBM_KZ)
+#undef LBM_KZ
+}
+
+// LDS of k_kxy for jobs of radius up to ra (the larger of the two kinds).
+constexpr size_t kfil_lds_bytes(int ra, size_t esz)
+{
+    const int hx = (kFilTX + 2 * ra + 3) / 4 * 4, hy = kFilTY + 2 * ra, rb = ra / 5;
+    return esz * (size_t)(hy * hx + (kFilTY + 2 * rb + hy) * kFilTX);
 }
 
 // ---------------------------------------------------------------------------
@@ -2697,13 +2841,15 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
     mark(2);
     if (g.kf) {
         if (g.fprog) launch_fourier<LAT, T>(*g.fprog, st);
-        for (int l = 0; l < g.nklev; ++l) {
-            if (g.wt)
-                hipLaunchKernelGGL((k_kjob<LAT, T, true>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
-                                   g.kjobs + g.klev[l].x);
-            else
-                hipLaunchKernelGGL((k_kjob<LAT, T, false>), dim3(g.nb1, g.klev[l].y), blk, 0, st, g.mems, g.work1,
-                                   g.kjobs + g.klev[l].x);
+        // R twice: the x and y parts, then (3-D) the z parts with the sum
+        const int ntile = (g.kdim[0] + kFilTX - 1) / kFilTX * ((g.kdim[1] + kFilTY - 1) / kFilTY) * g.kdim[2];
+        const int nzb = (g.kdim[0] * g.kdim[1] + kBlock - 1) / kBlock * ((g.kdim[2] + kFilZ - 1) / kFilZ);
+        for (int app = 0; app < (g.nkfil > 0 ? 2 : 0); ++app) {
+            const KFil* jobs = g.kfil + app * g.nkfil;
+            hipLaunchKernelGGL((k_kxy<LAT, T>), dim3((ntile + 7) / 8 * 8, g.nkfil * Lat<LAT>::D), blk,
+                               kfil_lds_bytes(g.krad, sizeof(T)), st, g.mems, g.kmem, jobs, ntile);
+            if constexpr (Lat<LAT>::D == 3)
+                hipLaunchKernelGGL((k_kz<T>), dim3((nzb + 7) / 8 * 8, g.nkfil * 3), blk, 0, st, g.mems, g.kmem, jobs, nzb);
         }
     }
     if (!g.kf && g.maxk > 0) {
@@ -2719,11 +2865,15 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
         if (g.wt) hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, true>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
         else hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, false>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
     } while (0)
-    if (g.kf) { if (g.maxsa <= 2) LBM_REDUCE(2, 0, true); else if (g.maxsa <= 6) LBM_REDUCE(6, 0, true); else LBM_REDUCE(8, 0, true); }
-    else if (g.maxk <= 1) LBM_REDUCE(1, 1, false);
-    else if (g.maxk <= 3) LBM_REDUCE(3, 3, false);
-    else if (g.maxk <= 4) LBM_REDUCE(4, 4, false);
-    else LBM_REDUCE(0, 8, false);
+#define LBM_REDUCE_KIND(KFV)                   \
+    do {                                       \
+        if (g.maxk <= 1) LBM_REDUCE(1, 1, KFV);    \
+        else if (g.maxk <= 3) LBM_REDUCE(3, 3, KFV); \
+        else if (g.maxk <= 4) LBM_REDUCE(4, 4, KFV); \
+        else LBM_REDUCE(0, 8, KFV);            \
+    } while (0)
+    if (g.kf) LBM_REDUCE_KIND(true); else LBM_REDUCE_KIND(false);
+#undef LBM_REDUCE_KIND
 #undef LBM_REDUCE
     mark(4);
     hipLaunchKernelGGL(k_sum, dim3(g.nbs), blk, 0, st, g.mems, g.works);

@@ -8,18 +8,18 @@
 
 namespace lbm {
 
-// One output field of a kernel-filter closure's sensitivity program (lives
-// in device memory; a launch runs every job of one level, one job per
-// blockIdx.y): op 0, dst = sum_t coef_t (1-D convolution of src_t along axis
-// with taps_t), periodic wrap or zero padding on the wall axis; op 1,
-// dst = curl^T src[0].  Pointers are device addresses in the member's arena.
-struct KJob {
-    int op, axis, ncomp, nterm;
-    int radius[3];
-    int pad;
-    double coef[3];
-    const void* taps[3];   // 2 radius + 1 values each, element type of the run
-    const void* src[3];
+// One application of a QoI's kernel filter R (in device memory, one job per
+// blockIdx.y and component): dst = R src through the intermediates y1 and y2
+// (k_kxy, k_kz).  kind LBM_FILT_GAUSS: taps g_0 .. g_ra; LBM_FILT_LAPL: the
+// dilated biharmonic l_0 .. l_ra, boxes of radius rb, times coef.  Pointers are
+// device addresses in the member's arena.
+struct KFil {
+    int kind, ra, rb, ncomp;
+    double coef;
+    const void* taps;      // element type of the run
+    const void* src;
+    void* y1;
+    void* y2;
     void* dst;
 };
 
@@ -67,10 +67,10 @@ struct LaunchGroup {
     int nmem;
     int probe;          // TO mode only: the QoI chain of the field already in v* (no
                         // stream-collide, no apply); see lbm_project_qoi
-    int kf;             // kernel-filter closure (one member per group): its job levels
-    const KJob* kjobs;  // replace the filter chains; kjobs in device memory,
-    const int2* klev;   // klev[l] = (first job, job count) of level l (host memory)
-    int nklev;
+    int kf;             // kernel-filter or Fourier closure (one member per group)
+    const KFil* kfil;   // kernel filters: nkfil jobs of the first application of R, then of
+    int nkfil, krad;    // the second (device memory); their largest radius
+    int kmem, kdim[3];  // the member and its grid
     const FourierProg* fprog;   // Fourier band QoIs (host memory; null if none)
     int wt;             // store the fields the next kernel reads through the L2 (small launches)
     int defer;          // TO mode: the SGS change is recorded and applied by the next step's pull
