@@ -172,32 +172,41 @@ int check_config(const lbm_config* c)
 
 struct Plan {
     size_t member, param, ctl, recs, g0, g1, fprof, vn, part_stats, part_diag, work1, workp, workm;
-    size_t rho, vs, W, rec, part_to, part_q, bandw, cmp, workr, workb, workc, sums, works, hpart, kV, kT, ktaps, kjobs;
+    size_t rho, vs, W, rec, part_to, part_q, bandw, cmp, workr, workb, workc, workq, sums, works, hpart, kV, kT, ktaps, kjobs;
     size_t fspec_v, fspec_w, fband_e, fband_z;
     size_t total;
     int N, D, NC, Q, esz, nb1, nbp, nbx2, cpt2, nbr, nbb, nbs, zc, btx, rec_cap;
-    int cnl, cvx, cvy, czc, cntx, cnty, cnt, nbc;   // filter chains: powers, tile, tiles in x and y and in all, workgroups
+    int cnl, cvx, cvy, czc, cntx, cnty, cnt, nbc, pvx, pvy, pntx, pnt;   // filter chains: powers, tile, tiles in x and y and in all, workgroups
     size_t popn;   // elements of one population buffer: Q * N rounded up to whole blocks of kPopBlk cells
     ClosureShape cap;
 };
 
-// Tiles of the filter chains (k_chain).  A wavefront's 64 lanes hold a tile's
+// Tiles of at most vx cells in x and, with rows rows and a halo of H, as many
+// in y as the rows leave; evened out over the grid.  Between walls a tile needs
+// no halo beyond them.
+void even_tiles(const lbm_config* c, int vx, int rows, int H, int* tvx, int* tvy, int* ntx, int* nxy)
+{
+    *ntx = (c->nx + vx - 1) / vx;
+    *tvx = (c->nx + *ntx - 1) / *ntx;
+    *ntx = (c->nx + *tvx - 1) / *tvx;
+    int nty = (c->ny + rows - 2 * H - 1) / (rows - 2 * H);
+    if (c->walls_y && c->ny <= rows) nty = 1;
+    else if (c->walls_y && c->ny <= 2 * (rows - H)) nty = 2;
+    *tvy = (c->ny + nty - 1) / nty;
+    nty = (c->ny + *tvy - 1) / *tvy;
+    *nxy = *ntx * nty;
+}
+
+// Tiles of the filter chains (k_chain, k_chain_pair).  A wavefront's 64 lanes hold a tile's
 // cells in x and a halo of H = powers on each side; the workgroup's rows
 // hold its cells in y and the same halo, except at a wall, beyond which rows
 // are zero anyway.  Tiles are evened out over the grid.
 void chain_tiles(const lbm_config* c, Plan* P)
 {
     const int H = P->cnl, NR = chain_waves(P->D) * chain_rows(P->D, P->esz);
-    const int vx = 64 - 2 * H, vy = NR - 2 * H;
-    P->cntx = (c->nx + vx - 1) / vx;
-    P->cvx = (c->nx + P->cntx - 1) / P->cntx;
-    P->cntx = (c->nx + P->cvx - 1) / P->cvx;
-    if (c->walls_y && c->ny <= NR) P->cnty = 1;
-    else if (c->walls_y && c->ny <= 2 * (NR - H)) P->cnty = 2;
-    else P->cnty = (c->ny + vy - 1) / vy;
-    P->cvy = (c->ny + P->cnty - 1) / P->cnty;
-    P->cnty = (c->ny + P->cvy - 1) / P->cvy;
-    const int nxy = P->cntx * P->cnty;
+    int nxy;
+    even_tiles(c, 64 - 2 * H, NR, H, &P->cvx, &P->cvy, &P->cntx, &nxy);
+    P->cnty = nxy / P->cntx;
     P->czc = 1;
     if (P->D == 3) {
         // z chunk: the fewest rounds of workgroups over the CUs (one per CU)
@@ -212,6 +221,7 @@ void chain_tiles(const lbm_config* c, Plan* P)
             if (zc == 1 || cost < best) { best = cost; P->czc = zc; }
         }
     }
+    if (P->D == 2) even_tiles(c, 64 - 2 * (P->cnl + 2), kPairRows, P->cnl + 1, &P->pvx, &P->pvy, &P->pntx, &P->pnt);
     P->cnt = nxy * (P->D == 3 ? (c->nz + P->czc - 1) / P->czc : 1);
     P->nbc = P->cnt * (P->D + P->NC);
 }
@@ -276,8 +286,9 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
         chain_tiles(c, &P);
         P.part_q = take(sizeof(double) * (size_t)std::max(cs.nsa, 1) * P.cnt * P.D);
         P.workc = take(sizeof(int2) * P.nbc);
+        P.workq = take(sizeof(int2) * std::max(P.pnt, 1));
         P.rec = take(e * 2 * P.D * N);
-        P.part_to = take(sizeof(double) * (size_t)std::max(cs.npart(), 1) * P.nbr);
+        P.part_to = take(sizeof(double) * (size_t)std::max(cs.npart(), 1) * std::max(P.nbr, P.pnt));
         P.bandw = take(sizeof(double) * (size_t)std::max(cs.nbands, 1) * c->ny);
         P.cmp = take(sizeof(double) * c->ny);
         P.workr = take(sizeof(int2) * P.nbr);
@@ -474,11 +485,19 @@ namespace {
 // The larger of a closure's numbers of E and Z QoIs.
 int chain_kinds(const ClosureShape& cs) { return std::max(cs.nzb, cs.nsa - cs.nzb); }
 
+// 2-D binomial closures of at most one QoI of each kind and no mean-profile
+// QoIs form their sums in the chains' launch (k_chain_pair).
+int pair_closure(const lbm_ctx* c)
+{
+    return c->plan.D == 2 && c->cur.nsa > 0 && !c->cur.kf && c->cur.nmp == 0 && chain_kinds(c->cur) <= 1;
+}
+
 // The member record's fields that follow the closure mode.
 void refresh_member(lbm_ctx* c)
 {
     c->hm.defer = c->defers() ? 1 : 0;
     c->hm.nst = c->defers() ? c->plan.nbb : c->plan.nb1;
+    c->hm.pair = pair_closure(c);
 }
 
 // The kernel filters of a member in a launch group.
@@ -522,6 +541,9 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.nbb = c->plan.nbb;
     g.workc = (const int2*)(c->arena + c->plan.workc);
     g.nbc = c->plan.nbc;
+    g.pair = pair_closure(c);
+    g.workq = (const int2*)(c->arena + c->plan.workq);
+    g.nbq = c->plan.pnt;
     g.works = (const int2*)(c->arena + c->plan.works);
     g.nbs = c->plan.nbs;
     g.workm = (const int*)(c->arena + c->plan.workm);
@@ -975,6 +997,7 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
         m.cvx = plan.cvx; m.cvy = plan.cvy; m.czc = plan.czc;
         m.cntx = plan.cntx; m.cnty = plan.cnty; m.cnt = plan.cnt;
         m.cd = plan.D; m.cnc = plan.NC;
+        m.pvx = plan.pvx; m.pvy = plan.pvy; m.pntx = plan.pntx; m.pnt = plan.pnt;
         m.rec = A + plan.rec;
     }
     m.nst = plan.nb1;
@@ -1019,6 +1042,12 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
             for (int b = 0; b < plan.nbc; ++b) wc[b] = make_int2(0, o[b]);
         }
         if (!rc) rc = upload(c, A + plan.workc, wc.data(), sizeof(int2) * wc.size());
+        std::vector<int2> wq(plan.pnt);
+        {
+            const std::vector<int> o = xcd_order(plan.pnt);
+            for (int b = 0; b < plan.pnt; ++b) wq[b] = make_int2(0, o[b]);
+        }
+        if (!rc && plan.pnt) rc = upload(c, A + plan.workq, wq.data(), sizeof(int2) * wq.size());
         std::vector<int2> ws(plan.nbs);
         for (int b = 0; b < plan.nbs; ++b) ws[b] = make_int2(0, ksum_slot(b, plan.cap.nhc));
         if (!rc) rc = upload(c, A + plan.works, ws.data(), sizeof(int2) * ws.size());
@@ -1551,13 +1580,13 @@ static int batch_build(lbm_batch* b)
     batch_free_dev(b);
     const int n = (int)b->mem.size();
     // group members by kernel kind
-    struct Key { int lat, prec, sub, mode, sab, btx, cnl, kfm, def, sep; };   // kfm: kernel-filter member (own group)
+    struct Key { int lat, prec, sub, mode, sab, btx, cnl, pair, kfm, def, sep; };   // kfm: kernel-filter member (own group)
     std::vector<Key> keys;
     std::vector<std::vector<int>> gm;
     for (int i = 0; i < n; ++i) {
         const lbm_ctx* c = b->mem[i];
         Key k{c->cfg.lattice, c->cfg.precision, c->cfg.substrate, c->mode(), c->cur.nsa <= 2 ? 2 : (c->cur.nsa <= 6 ? 6 : 8),
-              c->plan.btx, c->mode() == 2 ? c->plan.cnl : 0, c->mode() == 2 && c->cur.kf ? i : -1, (int)c->defers(), (c->cfg.tune_mem & 8) != 0};
+              c->plan.btx, c->mode() == 2 ? c->plan.cnl : 0, c->mode() == 2 ? pair_closure(c) : 0, c->mode() == 2 && c->cur.kf ? i : -1, (int)c->defers(), (c->cfg.tune_mem & 8) != 0};
         int gi = -1;
         for (size_t j = 0; j < keys.size(); ++j)
             if (!memcmp(&keys[j], &k, sizeof k)) gi = (int)j;
@@ -1567,7 +1596,7 @@ static int batch_build(lbm_batch* b)
     std::vector<DevMember> hmem(n);
     std::vector<int2> work;
     std::vector<int> workm;
-    struct Off { size_t w1, nb1, wp, nbp, wr, nbr, wb, nbb, wc, nbc, ws, nbs, wm, nm; };
+    struct Off { size_t w1, nb1, wp, nbp, wr, nbr, wb, nbb, wc, nbc, wq, nbq, ws, nbs, wm, nm; };
     std::vector<Off> offs;
     for (size_t gi = 0; gi < keys.size(); ++gi) {
         Off o{};
@@ -1605,6 +1634,11 @@ static int batch_build(lbm_batch* b)
                 for (int k = 0; k < b->mem[i]->plan.nbc; ++k) work.push_back(make_int2(i, oc[k]));
             }
         o.nbc = work.size() - o.wc;
+        o.wq = work.size();
+        if (keys[gi].pair)
+            for (int i : gm[gi])
+                for (int k : xcd_order(b->mem[i]->plan.pnt)) work.push_back(make_int2(i, k));
+        o.nbq = work.size() - o.wq;
         o.ws = work.size();
         if (keys[gi].mode == 2)
             for (int i : gm[gi])
@@ -1641,6 +1675,7 @@ static int batch_build(lbm_batch* b)
         g.mode = keys[gi].mode;
         g.btx = keys[gi].btx;
         g.cnl = keys[gi].cnl;
+        g.pair = keys[gi].pair;
         double pop_bytes = 0;   // one launch covers the whole group
         for (int i : gm[gi]) pop_bytes += (double)b->mem[i]->plan.N * b->mem[i]->plan.Q * b->mem[i]->plan.esz;
         g.wt = write_through(pop_bytes);
@@ -1673,6 +1708,8 @@ static int batch_build(lbm_batch* b)
         g.nbb = (int)offs[gi].nbb;
         g.workc = b->dwork + offs[gi].wc;
         g.nbc = (int)offs[gi].nbc;
+        g.workq = b->dwork + offs[gi].wq;
+        g.nbq = (int)offs[gi].nbq;
         g.works = b->dwork + offs[gi].ws;
         g.nbs = (int)offs[gi].nbs;
         g.workm = b->dworkm + offs[gi].wm;
@@ -1802,7 +1839,7 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
         launches[1] = m == 2 && g.kf && g.any_z ? 1 : 0;
         launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.maxk > 0 ? 1 : 0)) : 0;
-        launches[3] = m == 2 ? 1 : 0;
+        launches[3] = m == 2 && !g.pair ? 1 : 0;   // (k_chain_pair forms the sums)
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)
         launches[5] = m == 2 ? 1 : (m == 1 ? 2 : 0);
     }

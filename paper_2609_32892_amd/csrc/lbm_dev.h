@@ -37,6 +37,7 @@ constexpr int kFusedApplyPairs = 512;
 // exchange.
 __host__ __device__ constexpr int chain_waves(int d) { return d == 3 ? 8 : 1; }
 __host__ __device__ constexpr int chain_rows(int d, int esz) { return d == 3 ? (esz == 4 ? 4 : 3) : 16; }
+constexpr int kPairRows = 16;   // rows of a k_chain_pair wavefront
 constexpr int kHistRows = 512;   // LRS history rows (x entries) per k_sum workgroup
 constexpr int kMaxHistChunks = 64;                 // so 2 h nq <= 32768
 constexpr int kMaxRad = 12;     // kernel filters: largest radius of a 1-D factor
@@ -105,6 +106,8 @@ struct DevMember {
     int cvx, cvy, czc;                 // filter chains: cells of a tile in x, y and z
     int cntx, cnty, cnt;               // tiles in x, in y, and in all
     int cd, cnc;                       // components of v and of w
+    int pair;                          // chains and Gram sums by k_chain_pair
+    int pvx, pvy, pntx, pnt;           // its tiles: cells in x and y, tiles in x and in all
     DevParam* prm;
     DevCtl* ctl;
     lbm_qoi_rec* recs;

@@ -1346,6 +1346,161 @@ __global__ __launch_bounds__(64 * chain_waves(Lat<LAT>::D), Lat<LAT>::D == 2 ? 1
     else chain_job<LAT, T, NL, MS, 2>(m, prm, 2, tile, edge, red);
 }
 
+// K2 and K2c of 2-D closures of at most one E and one Z QoI and no
+// mean-profile QoIs (the paper's 2-D set): chains, adjoint curl and Gram sums
+// in one launch, one wavefront per tile.  v* of the tile and its halo lies in
+// registers (16 rows, lanes in x); powers as in k_chain, the curls from
+// neighbouring lanes and rows, so the halo is NL + 2 cells in x and NL + 1 in y.
+// Bound by its launch and one load latency: measured on MI355X, 256 x 256, FP32,
+// k_chain and k_reduce 5.0 and 4.9 us -> one launch of 5.5 us; 16 members of
+// 128 to 208 cells squared, 7 and 11 -> 7.2 us.
+// EZ: bit 0 an E QoI, bit 1 a Z QoI; MASK: the tile has rows beyond a wall.
+// (Template parameters, so that the chains of a tile are one block of code
+// that the compiler can interleave.)
+template <typename T, int NL, bool WT, int EZ, bool MASK>
+__device__ __forceinline__ void chain_pair(KMember& m, KParam* prm, int tile)
+{
+    constexpr int HX = NL + 2, HY = NL + 1, R = kPairRows;
+    constexpr int ne = EZ & 1, nz = EZ >> 1;
+    const int nx = m.nx, ny = m.ny, walls = m.walls;
+    const unsigned sN = (unsigned)m.N;
+    const int tx = tile % m.pntx, ty = tile / m.pntx, lane = threadIdx.x;
+    const int x0 = tx * m.pvx, xe = min(x0 + m.pvx, nx), y0 = ty * m.pvy, ye = min(y0 + m.pvy, ny);
+    const int xc = modi(x0 - HX + lane, nx);
+    const bool ownx = lane >= HX && lane - HX < xe - x0;
+    const int ys = walls && ty == 0 ? 0 : y0 - HY;
+    unsigned yo[R + 2], outm = 0;   // rows -1 .. R; bit r + 1: row r is beyond a wall
+    {
+        int yy = modi(ys - 1, ny);
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r) {
+            const int y = ys - 1 + r;
+            const bool ok = !walls || (y >= 0 && y < ny);
+            yo[r] = ok ? (unsigned)(yy * nx) : 0u;
+            outm |= ok ? 0u : 1u << r;
+            yy = yy + 1 == ny ? 0 : yy + 1;
+        }
+    }
+    const T* vs = (const T*)m.vs;
+    T a[R + 2], b[R];   // v_x of rows -1 .. R, v_y
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) a[r] = ld_at(vs, yo[r] + (unsigned)xc);
+#pragma unroll
+    for (int r = 0; r < R; ++r) b[r] = ld_at(vs + sN, yo[r + 1] + (unsigned)xc);
+    // rows beyond the walls count as zero
+    auto mask = [&](T* f, int first, int n) {
+        if constexpr (MASK) {
+#pragma unroll
+            for (int r = 0; r < n; ++r) f[r] = (outm >> (first + r)) & 1 ? T(0) : f[r];
+        }
+    };
+    mask(a, 0, R + 2);
+    mask(b, 1, R);
+    T w[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r] = (lane_next(b[r]) - lane_prev(b[r])) - (a[r + 2] - a[r]);
+    mask(w, 1, R);
+    auto filter = [&](T (&f)[R]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const T t = f[r] + lane_prev(f[r]);
+            f[r] = t + lane_next(t);
+        }
+        T s = f[0];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const T n = r + 1 < R ? f[r] + f[r + 1 < R ? r + 1 : r] : f[r];
+            f[r] = s + n;
+            s = n;
+        }
+        mask(f, 1, R);
+    };
+    // f -> R R f in place, its QoI density |R f|^2 summed over the own cells
+    auto own_row = [&](int r) { return ys + r >= y0 && ys + r < ye; };
+    auto chain = [&](T (&f)[R], int s, double& q) {
+        T cr[3], crr[NL + 1], v[R], d[R];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) cr[j] = chain_r<T>(prm, s, j);
+#pragma unroll
+        for (int j = 0; j <= NL; ++j) crr[j] = chain_rr<T>(prm, s, j);
+#pragma unroll
+        for (int r = 0; r < R; ++r) { v[r] = crr[0] * f[r]; d[r] = cr[0] * f[r]; }
+#pragma unroll
+        for (int j = 1; j <= NL; ++j) {
+            filter(f);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                v[r] = fma_(crr[j], f[r], v[r]);
+                if (j < 3) d[r] = fma_(cr[j < 3 ? j : 0], f[r], d[r]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            f[r] = v[r];
+            if (own_row(r) && ownx) q = __builtin_fma((double)d[r], (double)d[r], q);
+        }
+    };
+    T* kV = (T*)m.kV;
+    T ve[2][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) { ve[0][r] = a[r + 1]; ve[1][r] = b[r]; }
+    double acc[5] = {0, 0, 0, 0, 0};   // q_E, q_Z, G_EE, G_EZ, G_ZZ
+    if (ne) {   // uniform
+        chain(ve[0], 0, acc[0]);
+        chain(ve[1], 0, acc[0]);
+    }
+    if (nz) chain(w, ne, acc[1]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (!own_row(r)) continue;   // uniform; an own row has its neighbours among the thread's rows
+        const T wn = lane_next(w[r]), wp = lane_prev(w[r]);
+        const T up = r + 1 < R ? w[r + 1 < R ? r + 1 : r] : T(0), dn = r > 0 ? w[r > 0 ? r - 1 : 0] : T(0);
+        const T z0 = T(0.5) * (up - dn), z1 = -(T(0.5) * (wn - wp));
+        if (!ownx) continue;
+        const unsigned c = yo[r + 1] + (unsigned)xc;
+        if (ne) {
+            st_fld_at(kV, c, ve[0][r], WT);
+            st_fld_at(kV + sN, c, ve[1][r], WT);
+            acc[2] += (double)(ve[0][r] * ve[0][r] + ve[1][r] * ve[1][r]);
+        }
+        if (nz) {
+            st_fld_at(kV + (size_t)(2 * ne) * sN, c, z0, WT);
+            st_fld_at(kV + (size_t)(2 * ne + 1) * sN, c, z1, WT);
+            acc[4] += (double)(z0 * z0 + z1 * z1);
+        }
+        if (ne && nz) acc[3] += (double)(ve[0][r] * z0 + ve[1][r] * z1);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
+    if (lane == 0) {
+        double* out = m.part_to + tile;
+        const size_t n = (size_t)m.pnt;
+        if (ne) out[0] = 0.5 * acc[0];
+        if (nz) out[ne * n] = 0.5 * acc[1];
+        const int g = ne + nz;
+        if (ne) out[g * n] = acc[2];
+        if (ne && nz) out[(g + 1) * n] = acc[3];
+        if (nz) out[(ne ? g + 2 : g) * n] = acc[4];
+    }
+}
+
+template <typename T, int NL, bool WT>
+__global__ __launch_bounds__(64) void k_chain_pair(const DevMember* __restrict__ mems, const int2* __restrict__ work)
+{
+    const int2 wk = work[blockIdx.x];
+    KMember& m = *kc(mems + wk.x);
+    KParam* prm = kc(m.prm);
+    const int ez = prm->nk[0] + 2 * prm->nk[1];
+#define LBM_EZ(MASK)                                                        \
+    do {                                                                    \
+        if (ez == 3) chain_pair<T, NL, WT, 3, MASK>(m, prm, wk.y);          \
+        else if (ez == 2) chain_pair<T, NL, WT, 2, MASK>(m, prm, wk.y);     \
+        else chain_pair<T, NL, WT, 1, MASK>(m, prm, wk.y);                  \
+    } while (0)
+    if (m.walls) LBM_EZ(true); else LBM_EZ(false);
+#undef LBM_EZ
+}
+
 // ---------------------------------------------------------------------------
 // K2c: per-cell sensitivities and Gram products, FP64 partial sums per
 // workgroup.  Workgroups cover one y row (2-D) or one y plane (3-D) each, so
@@ -1648,8 +1803,8 @@ static __global__ __launch_bounds__(kBlock) void k_sum(const DevMember* __restri
         // the QoI sums of binomial closures are k_chain's, the others k_reduce's
         KParam* prm = kc(m.prm);
         const int s = slot - 4;
-        const bool chain = s < prm->nsa && !prm->kf;
-        const int nblk = chain ? m.cnt * (prm->sa_kind[s] == 0 ? m.cd : m.cnc) : m.ny * m.nbx2;
+        const bool chain = s < prm->nsa && !prm->kf && !m.pair;
+        const int nblk = chain ? m.cnt * (prm->sa_kind[s] == 0 ? m.cd : m.cnc) : m.pair ? m.pnt : m.ny * m.nbx2;
         const double* p = chain ? m.part_q + (size_t)s * m.cnt * m.cd : m.part_to + (size_t)s * nblk;
 #pragma unroll 8
         for (int b = threadIdx.x; b < nblk; b += kBlock) v[0] += p[b];
@@ -2852,7 +3007,17 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
                 hipLaunchKernelGGL((k_kz<T>), dim3((nzb + 7) / 8 * 8, g.nkfil * 3), blk, 0, st, g.mems, g.kmem, jobs, nzb);
         }
     }
-    if (!g.kf && g.maxk > 0) {
+    if (g.pair) {
+        if constexpr (Lat<LAT>::D == 2) {
+#define LBM_PAIR(NLV)                                                                                          \
+    do {                                                                                                       \
+        if (g.wt) hipLaunchKernelGGL((k_chain_pair<T, NLV, true>), dim3(g.nbq), dim3(64), 0, st, g.mems, g.workq); \
+        else hipLaunchKernelGGL((k_chain_pair<T, NLV, false>), dim3(g.nbq), dim3(64), 0, st, g.mems, g.workq); \
+    } while (0)
+            if (g.cnl == 2) LBM_PAIR(2); else LBM_PAIR(4);
+#undef LBM_PAIR
+        }
+    } else if (!g.kf && g.maxk > 0) {
 #define LBM_CHAIN(NLV, MSV)                                                                                    \
     hipLaunchKernelGGL((k_chain<LAT, T, NLV, MSV>), dim3(g.nbc), dim3(64 * chain_waves(Lat<LAT>::D)), 0, st, g.mems, g.workc)
         if (g.cnl == 2) { if (g.maxk <= 4) LBM_CHAIN(2, 4); else LBM_CHAIN(2, 8); }
@@ -2872,7 +3037,7 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
         else if (g.maxk <= 4) LBM_REDUCE(4, 4, KFV); \
         else LBM_REDUCE(0, 8, KFV);            \
     } while (0)
-    if (g.kf) LBM_REDUCE_KIND(true); else LBM_REDUCE_KIND(false);
+    if (g.kf) LBM_REDUCE_KIND(true); else if (!g.pair) LBM_REDUCE_KIND(false);
 #undef LBM_REDUCE_KIND
 #undef LBM_REDUCE
     mark(4);

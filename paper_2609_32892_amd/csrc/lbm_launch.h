@@ -61,6 +61,9 @@ struct LaunchGroup {
     int nbb;
     const int2* workc;  // filter chains: (member, tile * (D + NC) + chain)
     int nbc;
+    int pair;           // 2-D closures of at most one E and one Z QoI: k_chain_pair
+    const int2* workq;  // its tiles: (member, tile)
+    int nbq;
     const int2* works;  // cross-block sums: (member, value slot)
     int nbs;
     const int* workm;   // one workgroup per member

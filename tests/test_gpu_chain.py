@@ -18,6 +18,10 @@ SETS = {
     "energy": [("E", "B2", 0), ("E", "IMB", 0)],
     "enstrophy": [("Z", "I", 0), ("Z", "BMID", 0)],
     "uneven": [("Z", "B", 0)] + [("E", f, 0) for f in ("I", "B", "B2", "BMID", "IMB")],
+    "pair": [("E", "B", 0), ("Z", "B", 0)],
+    "pair4": [("Z", "BMID", 0), ("E", "B2", 0)],
+    "one": [("Z", "IMB", 0)],
+    "one4": [("E", "BMID", 0)],
 }
 
 CASES = [
@@ -29,6 +33,10 @@ CASES = [
     (9, 10, 6, 1, "energy"), (9, 10, 6, 1, "enstrophy"), (9, 10, 6, 1, "uneven"),
     (60, 12, 1, 0, "two"), (61, 13, 1, 0, "two"), (7, 16, 1, 1, "two"), (8, 17, 1, 1, "two"), (7, 28, 1, 1, "two"),
     (6, 29, 1, 1, "two"), (57, 8, 1, 0, "four"), (9, 9, 1, 0, "four"), (12, 11, 1, 0, "uneven"),
+    # one QoI of each kind at most, in 2-D: 64 - 2 (j + 2) cells in x, 16 rows with a halo of j + 1
+    (56, 10, 1, 0, "pair"), (57, 11, 1, 0, "pair"), (112, 3, 1, 0, "pair"), (7, 16, 1, 1, "pair"), (8, 17, 1, 1, "pair"),
+    (7, 26, 1, 1, "pair"), (3, 27, 1, 1, "pair"), (52, 6, 1, 0, "pair4"), (53, 7, 1, 0, "pair4"), (9, 22, 1, 1, "pair4"),
+    (9, 23, 1, 1, "pair4"), (20, 21, 1, 0, "one"), (20, 21, 1, 1, "one4"),
 ]
 
 
