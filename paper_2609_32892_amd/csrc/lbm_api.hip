@@ -173,7 +173,7 @@ int check_config(const lbm_config* c)
 struct Plan {
     size_t member, param, ctl, recs, g0, g1, fprof, vn, part_stats, part_diag, work1, workp, workm;
     size_t rho, vs, W, rec, part_to, part_q, bandw, cmp, workr, workb, workc, workq, sums, works, hpart, kV, kT, ktaps, kjobs;
-    size_t fspec_v, fspec_w, fband_e, fband_z;
+    size_t fspec, fband;
     size_t total;
     int N, D, NC, Q, esz, nb1, nbp, nbx2, cpt2, nbr, nbb, nbs, zc, btx, rec_cap;
     int cnl, cvx, cvy, czc, cntx, cnty, cnt, nbc, pvx, pvy, pntx, pnt;   // filter chains: powers, tile, tiles in x and y and in all, workgroups
@@ -306,11 +306,10 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
             P.ktaps = take(e * kMaxSA * (kMaxRad + 1));
             P.kjobs = take(sizeof(KFil) * 2 * kMaxSA);
             if (cs.nf) {
-                // Fourier bands: spectra of v* and w and one work spectrum (complex)
-                P.fspec_v = take(2 * e * P.D * N);
-                P.fspec_w = take(2 * e * P.NC * N);
-                P.fband_e = take(2 * e * P.D * N * (size_t)std::max(cs.nf - cs.nfz, 1));
-                P.fband_z = take(2 * e * P.NC * N * (size_t)std::max(cs.nfz, 1));
+                // Fourier bands (complex): the packed components' spectra, and
+                // the fields of every band QoI
+                P.fspec = take(2 * e * P.D * N);
+                P.fband = take(2 * e * (P.D - 1) * N * (size_t)cs.nf);
             }
         }
     }
@@ -567,29 +566,70 @@ void drop_graphs(lbm_ctx* c)
     c->gver = -1;
 }
 
-// Fourier band QoIs: hipFFT plans (batched C2C / Z2Z over the components,
-// in place, dimensions z, y, x) and the program that launch_fourier runs.
+// Fourier band QoIs: the program that launch_fourier runs, and its hipFFT
+// plans (batched C2C / Z2Z, in place, dimensions z, y, x).
 void drop_fourier(lbm_ctx* c)
 {
-    for (int k = 0; k < 4; ++k)
-        if (c->fprog.plan[k]) hipfftDestroy((hipfftHandle)c->fprog.plan[k]);
+    for (void* p : c->fprog.plan)
+        if (p) hipfftDestroy((hipfftHandle)p);
     c->fprog = FourierProg{};
 }
 
-int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq, int nsa)
+int build_fourier(lbm_ctx* c, std::vector<FourierQ> fq)
 {
     drop_fourier(c);
     if (fq.empty()) return LBM_OK;
     FourierProg& f = c->fprog;
-    const int D = c->plan.D, NC = c->plan.NC, N = c->plan.N;
+    const int D = c->plan.D, N = c->plan.N;
+    const size_t comp = (size_t)N * c->plan.esz;
+    bool has[2] = {false, false};
+    for (const FourierQ& q : fq) has[q.e ? 0 : 1] = true;
+    // packed fields: components 0 .. D - 1 of v, then those of w
+    auto field = [&](int re, int im) { f.re[f.nf] = re; f.im[f.nf++] = im; };
+    if (D == 2) {
+        if (has[0]) field(0, 1);
+        if (has[1]) field(2, -1);
+    } else if (has[0] && has[1]) {
+        field(0, 1); field(2, 5); field(3, 4);
+    } else {
+        field(has[0] ? 0 : 3, has[0] ? 1 : 4);
+        field(has[0] ? 2 : 5, -1);
+    }
+    // bands, an E and a Z QoI of the same band together
+    std::vector<char> used(fq.size(), 0);
+    for (size_t a = 0; a < fq.size(); ++a) {
+        if (used[a]) continue;
+        char* dst[2] = {nullptr, nullptr};   // of R v, of R w
+        dst[fq[a].e ? 0 : 1] = (char*)fq[a].dst;
+        for (size_t b = a + 1; b < fq.size(); ++b)
+            if (!used[b] && fq[b].e != fq[a].e && fq[b].l == fq[a].l && fq[b].m == fq[a].m) {
+                dst[fq[b].e ? 0 : 1] = (char*)fq[b].dst;
+                used[b] = 1;
+                break;
+            }
+        auto out = [&](int k) -> void* {
+            if (k < 0) return nullptr;
+            char* d = dst[k < D ? 0 : 1];
+            return d ? d + comp * (k < D ? k : k - D) : nullptr;
+        };
+        for (int k = 0; k < f.nf; ++k) {
+            void* re = out(f.re[k]);
+            void* im = out(f.im[k]);
+            if (!re && !im) continue;
+            const int n = f.slots.n++;
+            f.slots.field[n] = k;
+            f.slots.l[n] = fq[a].l;
+            f.slots.m[n] = fq[a].m;
+            f.slots.re[n] = re;
+            f.slots.im[n] = im;
+        }
+    }
     int n[3] = {c->cfg.nz, c->cfg.ny, c->cfg.nx};
     const int rank = D == 3 ? 3 : 2;
     int* dims = D == 3 ? n : n + 1;
     const hipfftType type = c->cfg.precision == LBM_FP64 ? HIPFFT_Z2Z : HIPFFT_C2C;
-    for (const FourierQ& q : fq) (q.e ? f.qe : f.qz).push_back(q);
-    const int batch[4] = {D, NC, (int)f.qe.size() * D, (int)f.qz.size() * NC};
-    for (int k = 0; k < 4; ++k) {
-        if (batch[k] == 0) continue;
+    const int batch[2] = {f.nf, f.slots.n};
+    for (int k = 0; k < 2; ++k) {
         hipfftHandle h;
         if (hipfftPlanMany(&h, rank, dims, nullptr, 1, N, nullptr, 1, N, type, batch[k]) != HIPFFT_SUCCESS) {
             drop_fourier(c);
@@ -597,13 +637,9 @@ int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq, int nsa)
         }
         f.plan[k] = (void*)h;
     }
-    char* A = c->arena;
-    f.spec_v = A + c->plan.fspec_v;
-    f.spec_w = A + c->plan.fspec_w;
-    f.band_e = A + c->plan.fband_e;
-    f.band_z = A + c->plan.fband_z;
-    f.vs = A + c->plan.vs;
-    f.w = A + c->plan.W + (size_t)nsa * NC * N * c->plan.esz;
+    f.spec = c->arena + c->plan.fspec;
+    f.band = c->arena + c->plan.fband;
+    f.vs = c->arena + c->plan.vs;
     f.nx = c->cfg.nx; f.ny = c->cfg.ny; f.nz = c->cfg.nz;
     return LBM_OK;
 }
@@ -674,7 +710,7 @@ int build_kfil(lbm_ctx* c, const lbm_closure* cl, const ClosureShape& cs, const 
     first.insert(first.end(), second.begin(), second.end());
     int rc = first.empty() ? LBM_OK : upload(c, A + c->plan.kjobs, first.data(), sizeof(KFil) * first.size());
     if (rc) return rc;
-    rc = build_fourier(c, fq, cs.nsa);
+    rc = build_fourier(c, fq);
     if (rc) return rc;
     // tap tables in the run's element type
     if (e == 8) return upload(c, A + c->plan.ktaps, taps.data(), sizeof(double) * taps.size());
@@ -1837,7 +1873,7 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
     if (launches) {
         const int m = g.mode;
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
-        launches[1] = m == 2 && g.kf && g.any_z ? 1 : 0;
+        launches[1] = m == 2 && g.nkfil > 0 && g.any_z ? 1 : 0;
         launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.maxk > 0 ? 1 : 0)) : 0;
         launches[3] = m == 2 && !g.pair ? 1 : 0;   // (k_chain_pair forms the sums)
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)

@@ -2537,66 +2537,98 @@ constexpr size_t kfil_lds_bytes(int ra, size_t esz)
 }
 
 // ---------------------------------------------------------------------------
-// Sharp Fourier band filters (eq. scale-aware-energy-fourier) through hipFFT:
-// real fields into complex ones, forward transforms, per QoI the band mask
-// (l - 1/2 <= |k| < m + 1/2, integer mode indices; with the 1/N of the
-// inverse transform), the inverse transform and the real part.
+// Sharp Fourier band filters (eq. scale-aware-energy-fourier) through hipFFT.
+// A band filter is a real operator (its mask is real and even), so two real
+// components travel as the real and imaginary part of one complex field, and R
+// of both comes out of one inverse transform:
+//   2-D: v_x + i v_y, w;  3-D: v_x + i v_y, v_z + i w_z, w_x + i w_y
+// (without Z or E QoIs: that kind's components alone).  k_fpack forms w = curl
+// v* and packs; one forward transform of all fields; k_fmask writes, per band
+// and field it needs, the masked spectrum (l - 1/2 <= |k| < m + 1/2, integer
+// mode indices; with the 1/N of the inverse transform), where an E and a Z QoI
+// of the same band share a field; one inverse transform of all of them;
+// k_funpack takes the parts to V_s = R v* (E) and U_s = R w (Z).
+// 256 x 256, FP32, three bands of each kind, MI355X: fourteen launches and nine
+// inverse fields per step -> seven and six, the step 75 -> 48 us (with the solve
+// in the apply).
 // ---------------------------------------------------------------------------
-template <typename T, typename CT>
-__global__ __launch_bounds__(kBlock) void k_fpack(const T* __restrict__ src, CT* __restrict__ dst, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    CT c;
-    c.x = src[i];
-    c.y = T(0);
-    dst[i] = c;
-}
+// v_x, v_y, v_z, w_x, w_y, w_z (2-D: v_x, v_y, w) of the packed fields; -1: zero
+struct FFields { int nf, re[3], im[3]; };
 
-struct FBands { int nb, l[kMaxBands], m[kMaxBands]; };
-template <typename T> struct FDst { T* d[kMaxBands]; };
-
-// the masked spectrum of every band, out[b][comp][cell]
-template <typename T, typename CT>
-__global__ __launch_bounds__(kBlock) void k_fmask(const CT* __restrict__ spec, CT* __restrict__ out, int ncomp,
-                                                  int nx, int ny, int nz, FBands bands)
+template <int LAT, typename T, typename CT>
+__global__ __launch_bounds__(kBlock) void k_fpack(const T* __restrict__ vs, CT* __restrict__ dst, FFields ff, int nx,
+                                                  int ny, int nz)
 {
-    const size_t N = (size_t)nx * ny * nz;
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= N * ncomp) return;
-    const size_t cell = i % N;
-    const int jx = (int)(cell % nx), jy = (int)((cell / nx) % ny), jz = (int)(cell / ((size_t)nx * ny));
-    const int kx = jx <= nx / 2 ? jx : jx - nx, ky = jy <= ny / 2 ? jy : jy - ny, kz = jz <= nz / 2 ? jz : jz - nz;
-    const double kn = sqrt((double)kx * kx + (double)ky * ky + (double)kz * kz);
-    const CT c = spec[i];
-    for (int b = 0; b < bands.nb; ++b) {
-        const bool keep = kn >= bands.l[b] - 0.5 && kn < bands.m[b] + 0.5;
-        const T s = keep ? T(1.0 / (double)N) : T(0);
+    using L = Lat<LAT>;
+    constexpr int D = L::D;
+    const unsigned N = (unsigned)nx * ny * nz, i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= N) return;
+    const int x = (int)(i % nx), t = (int)(i / nx), y = t % ny, z = t / ny;
+    T c[D + 3] = {};   // v, then w
+#pragma unroll
+    for (int a = 0; a < D; ++a) c[a] = ld_at(vs + (size_t)a * N, i);
+    if (ff.re[ff.nf - 1] >= D) {   // uniform: some field holds w
+        const Nbr n = nbr_at(i, x, y, z, nx, ny, nz, 0, D);
+        curl_nb<D, T>(vs, N, i, n, c + D);
+    }
+    auto comp = [&](int k) {
+        T v = 0;
+#pragma unroll
+        for (int a = 0; a < D + L::NC; ++a) v = k == a ? c[a] : v;
+        return v;
+    };
+    for (int f = 0; f < ff.nf; ++f) {
         CT o;
-        o.x = c.x * s;
-        o.y = c.y * s;
-        out[(size_t)b * ncomp * N + i] = o;
+        o.x = comp(ff.re[f]);
+        o.y = comp(ff.im[f]);
+        dst[(size_t)f * N + i] = o;
     }
 }
 
-// the real parts of the inverse transforms into each band's destination
+// the masked spectrum of every slot, out[slot][cell]
 template <typename T, typename CT>
-__global__ __launch_bounds__(kBlock) void k_funpack(const CT* __restrict__ src, FDst<T> dst, int nb, size_t n)
+__global__ __launch_bounds__(kBlock) void k_fmask(const CT* __restrict__ spec, CT* __restrict__ out, FSlots sl, int nx,
+                                                  int ny, int nz)
+{
+    const size_t N = (size_t)nx * ny * nz;
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= N) return;
+    const int jx = (int)(i % nx), jy = (int)((i / nx) % ny), jz = (int)(i / ((size_t)nx * ny));
+    const int kx = jx <= nx / 2 ? jx : jx - nx, ky = jy <= ny / 2 ? jy : jy - ny, kz = jz <= nz / 2 ? jz : jz - nz;
+    const double kn = sqrt((double)kx * kx + (double)ky * ky + (double)kz * kz);
+    const T s = T(1.0 / (double)N);
+    for (int b = 0; b < sl.n; ++b) {
+        const bool keep = kn >= sl.l[b] - 0.5 && kn < sl.m[b] + 0.5;
+        CT o;
+        o.x = o.y = T(0);
+        if (keep) {
+            const CT c = spec[(size_t)sl.field[b] * N + i];
+            o.x = c.x * s;
+            o.y = c.y * s;
+        }
+        out[(size_t)b * N + i] = o;
+    }
+}
+
+// the parts of the inverse transforms into their destinations
+template <typename T, typename CT>
+__global__ __launch_bounds__(kBlock) void k_funpack(const CT* __restrict__ src, FSlots sl, size_t N)
 {
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n * nb) return;
-    dst.d[i / n][i % n] = src[i].x;
+    if (i >= N) return;
+    const int b = blockIdx.y;
+    const CT c = src[(size_t)b * N + i];
+    if (sl.re[b]) ((T*)sl.re[b])[i] = c.x;
+    if (sl.im[b]) ((T*)sl.im[b])[i] = c.y;
 }
 
 template <int LAT, typename T>
 static void launch_fourier(const FourierProg& f, hipStream_t st)
 {
     using L = Lat<LAT>;
-    const int nx = f.nx, ny = f.ny, nz = f.nz;
     using CT = typename std::conditional<std::is_same<T, float>::value, float2, double2>::type;
-    const size_t N = (size_t)nx * ny * nz;
-    const dim3 blk(kBlock);
-    auto grid = [&](size_t n) { return dim3((unsigned)((n + kBlock - 1) / kBlock)); };
+    const size_t N = (size_t)f.nx * f.ny * f.nz;
+    const dim3 blk(kBlock), grd((unsigned)((N + kBlock - 1) / kBlock));
     auto exec = [&](void* plan, void* data, int dir) {
         hipfftHandle h = (hipfftHandle)plan;
         hipfftResult r = hipfftSetStream(h, st);
@@ -2608,28 +2640,14 @@ static void launch_fourier(const FourierProg& f, hipStream_t st)
         }
         if (r != HIPFFT_SUCCESS) f.failed = 1;
     };
-    for (int kind = 0; kind < 2; ++kind) {   // E bands (of v*), then Z bands (of w)
-        const std::vector<FourierQ>& qs = kind == 0 ? f.qe : f.qz;
-        if (qs.empty()) continue;
-        const int nc = kind == 0 ? L::D : L::NC;
-        void* spec = kind == 0 ? f.spec_v : f.spec_w;
-        void* band = kind == 0 ? f.band_e : f.band_z;
-        hipLaunchKernelGGL((k_fpack<T, CT>), grid(nc * N), blk, 0, st, (const T*)(kind == 0 ? f.vs : f.w), (CT*)spec,
-                           nc * N);
-        exec(f.plan[kind], spec, HIPFFT_FORWARD);
-        FBands fb{};
-        FDst<T> fd{};
-        fb.nb = (int)qs.size();
-        for (size_t b = 0; b < qs.size(); ++b) {
-            fb.l[b] = qs[b].l;
-            fb.m[b] = qs[b].m;
-            fd.d[b] = (T*)qs[b].dst;
-        }
-        hipLaunchKernelGGL((k_fmask<T, CT>), grid(nc * N), blk, 0, st, (const CT*)spec, (CT*)band, nc, nx, ny, nz, fb);
-        exec(f.plan[2 + kind], band, HIPFFT_BACKWARD);
-        hipLaunchKernelGGL((k_funpack<T, CT>), grid(qs.size() * nc * N), blk, 0, st, (const CT*)band, fd, fb.nb,
-                           nc * N);
-    }
+    FFields ff{};
+    ff.nf = f.nf;
+    for (int k = 0; k < f.nf; ++k) { ff.re[k] = f.re[k]; ff.im[k] = f.im[k]; }
+    hipLaunchKernelGGL((k_fpack<LAT, T, CT>), grd, blk, 0, st, (const T*)f.vs, (CT*)f.spec, ff, f.nx, f.ny, f.nz);
+    exec(f.plan[0], f.spec, HIPFFT_FORWARD);
+    hipLaunchKernelGGL((k_fmask<T, CT>), grd, blk, 0, st, (const CT*)f.spec, (CT*)f.band, f.slots, f.nx, f.ny, f.nz);
+    exec(f.plan[1], f.band, HIPFFT_BACKWARD);
+    hipLaunchKernelGGL((k_funpack<T, CT>), dim3(grd.x, f.slots.n), blk, 0, st, (const CT*)f.band, f.slots, N);
 }
 
 // ---------------------------------------------------------------------------
@@ -2989,7 +3007,7 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], st);
     };
-    if (g.kf && g.any_z) {   // the binomial chains form w in their first pass
+    if (g.nkfil > 0 && g.any_z) {   // (the binomial chains and the Fourier bands form w themselves)
         if (g.wt) hipLaunchKernelGGL((k_curl<LAT, T, true>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
         else hipLaunchKernelGGL((k_curl<LAT, T, false>), dim3(g.nb1), blk, 0, st, g.mems, g.work1);
     }

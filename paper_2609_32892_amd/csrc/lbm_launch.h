@@ -23,22 +23,24 @@ struct KFil {
     void* dst;
 };
 
-// Fourier band QoIs of a member (host side): spectra of v* and w, the
-// masked band spectra of all E QoIs and of all Z QoIs, and per QoI the band
-// and the destination of R v* (E: V_s) or of R w (Z: the input of its
-// adjoint curl).  Plans are hipfftHandle values.
-constexpr int kMaxBands = kMaxSA;   // every E/Z QoI may be a band
+// Fourier band QoIs of a member (host side): the packed fields (components of
+// v*, then of w, as real and imaginary parts; -1: zero) and their spectra; per
+// slot of the inverse transform its field, band and the destinations of its
+// parts (null: not needed).  Plans are hipfftHandle values.
+constexpr int kMaxSlots = 2 * kMaxSA;   // at most two fields per QoI
 struct FourierQ { int e, l, m; void* dst; };
+struct FSlots {
+    int n, field[kMaxSlots], l[kMaxSlots], m[kMaxSlots];
+    void* re[kMaxSlots];
+    void* im[kMaxSlots];
+};
 struct FourierProg {
-    void* plan[4];        // forward: batch D (v*), batch NC (w); inverse: all E bands, all Z bands
-    void* spec_v;         // [D][N] complex
-    void* spec_w;         // [NC][N] complex (Z QoIs only)
-    void* band_e;         // [nE][D][N] complex
-    void* band_z;         // [nZ][NC][N] complex
+    void* plan[2];        // forward: the fields; inverse: the slots
+    void* spec;           // [nf][N] complex
+    void* band;           // [slots][N] complex
     const void* vs;       // v* [D][N]
-    const void* w;        // w [NC][N]
-    int nx, ny, nz;
-    std::vector<FourierQ> qe, qz;   // E and Z bands
+    int nx, ny, nz, nf, re[3], im[3];
+    FSlots slots;
     mutable int failed = 0;         // set when a hipFFT call of a launch fails
 };
 
@@ -83,12 +85,12 @@ struct LaunchGroup {
                         // (k_step_t over the binomial tiles); not with the WALE substrate
 };
 
-// TO mode: the binomial apply forms the solve itself (no k_solve launch):
-// not for kernel-filter closures, probe steps (no apply) or a forced own
-// launch, and only where the apply's workgroups are all resident at once.
+// TO mode: the apply forms the solve itself (no k_solve launch): not for
+// probe steps (no apply) or a forced own launch, and only where the apply's
+// workgroups are all resident at once.
 inline bool fused_solve(const LaunchGroup& g)
 {
-    return !g.kf && !g.probe && !g.sep_solve && g.nbp <= kFusedApplyPairs;
+    return !g.probe && !g.sep_solve && g.nbp <= kFusedApplyPairs;
 }
 
 enum { OP_INIT = 0, OP_GET_POP = 1, OP_SET_POP = 2, OP_STREAM = 3 };
