@@ -86,12 +86,11 @@ typedef struct {
     int tune_mem;       /* memory-access variant of the step (0: automatic by size): bit 0
                            forces 64-bit population offsets, bit 1 non-temporal population
                            stores in plain runs, bit 2 the SGS change recorded and applied
-                           by the next step's pull (binomial closures, BGK or Smagorinsky
-                           substrate) also where the populations (up to 192 MB) would
-                           apply it in place, bit 3 the closure's solve in a launch of its
-                           own also where the apply would form it (binomial closures on
-                           launches of at most 1024 blocks of 256 cells, paired into 512
-                           workgroups); bitwise the same
+                           by the next step's pull (BGK or Smagorinsky substrate) also on
+                           the small grids that would apply it in place, bit 3 the
+                           closure's solve in a launch of its own also where the apply
+                           would form it (launches of at most 1024 blocks of 256 cells,
+                           paired into 512 workgroups); bitwise the same
                            result either way (for tests of the large-grid forms); 0..15 */
 } lbm_config;
 

@@ -449,19 +449,34 @@ struct lbm_ctx {
     long gver = -1;
     int gchunk = 32;
     int mode() const { return cur.nq > 0 ? 2 : (cfg.diag ? 1 : 0); }
-    // The SGS change goes into the next step's pull (a record per cell)
+    // The SGS change goes into the next step's pull (a record per cell, 2 D
+    // values written and read instead of Q populations read and written)
     // except with the WALE substrate, whose velocity gradients need the
-    // complete post-streaming state, and on grids whose populations stay in
-    // the 256 MB Infinity Cache (up to 192 MB), where the in-place apply is
-    // cheaper than the tiled pull with its staged records (measured on
-    // MI355X, FP32 channel TO-LES: 96 x 48 x 48 2659 -> 2714 MLUPS, 295 x 47
-    // x 98 3866 -> 4230, 192 x 96 x 96 4858 -> 4897; at 256 x 128 x 128, 304
-    // MB of populations, the record form is faster, 6329 against 5938).
-    // Either way the result is bitwise the same.
+    // complete post-streaming state, and on small grids, where the in-place
+    // apply is cheaper than the tiled pull with its staged records (32 x 8
+    // tiles: lanes past the grid's edge idle).  Either way the result is
+    // bitwise the same.  Where the lines lie (MI355X, whole TO step, us,
+    // in place -> records):
+    //  - past the 256 MB Infinity Cache (192 MB of populations) records always;
+    //    FP32 channels below it are level on aligned rows (96 x 48 x 48 64.6
+    //    -> 64.8, 160 x 80 x 80 176 -> 178, 192 x 96 x 96 279 -> 273) and lose
+    //    on others (295 x 47 x 98 216 -> 239).
+    //  - D3Q19 in FP64, twice the bytes: records on rows of whole half tiles
+    //    (48 x 24 x 24 56 -> 54, 96 x 48 x 48 102 -> 92, 128 x 64 x 64 183 ->
+    //    175, 144 x 48 x 51 136 -> 127, 160 x 80 x 80 304 -> 292), in place on
+    //    others (97 x 47 x 49 105 -> 111, 161 x 79 x 81 312 -> 341).
+    //  - D2Q9 pulls need no aligned rows in FP64: records from 24 MB (512^2, 18
+    //    MB, 29.4 -> 29.5; 640^2, 28 MB, 52 -> 48; 897 x 701 73 -> 71; 1024^2
+    //    103 -> 92); in FP32 on rows of whole tiles from 32 MB (768^2, 20 MB,
+    //    35.5 -> 34.8; 1024^2, 36 MB, 60.6 -> 58.5; 512 x 4096 102 -> 93; but
+    //    1001 x 1003 56.9 -> 58.7, 1290^2 86 -> 90).
     bool defers() const
     {
-        return mode() == 2 && cfg.substrate != LBM_WALE &&
-               ((cfg.tune_mem & 4) || (double)plan.N * plan.Q * plan.esz > 192.0 * 1024 * 1024);
+        if (mode() != 2 || cfg.substrate == LBM_WALE) return false;
+        const double mb = (double)plan.N * plan.Q * plan.esz / (1024.0 * 1024);
+        if ((cfg.tune_mem & 4) || mb > 192) return true;
+        if (plan.D == 3) return plan.esz == 8 && cfg.nx % (kBinTX / 2) == 0;
+        return plan.esz == 8 ? mb > 24 : cfg.nx % kBinTX == 0 && mb > 32;
     }
 };
 
