@@ -243,19 +243,32 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
     P.nbx2 = (plane + kBlock * P.cpt2 - 1) / (kBlock * P.cpt2);
     P.nbr = P.nbx2 * c->ny;
     {
-        // tile: 64 x 8 (512-thread workgroups) on 3-D grids whose rows are
-        // whole multiples of 64 cells and at least 256 long, else 32 x 8
-        // (measured on MI355X on a 384 x 192 x 192 channel: 64-wide tiles 9%
-        // less binomial time than 32 x 8; 64 x 8 another 6% less than 64 x 4)
+        // Tile of k_step_t: 64 x 8 (512-thread workgroups) on 3-D grids whose
+        // rows are whole multiples of 64 cells and at least 256 long, else 32
+        // x 8 (fewer halo records staged; FP32 on MI355X, phase: 256 x 128 x
+        // 128 181 us with 32-wide tiles, 176 with 64-wide; 384 x 192 x 192
+        // level, 579 and 577).
         P.btx = c->tune_btx ? c->tune_btx : (P.D == 3 && c->nx % kBinTXW == 0 && c->nx >= 256 ? kBinTXW : kBinTX);
-        // z chunk: as many planes per workgroup as keeps about 400 or more
-        // workgroups (measured on MI355X: fewer staged halo planes pay more
-        // than extra workgroups once the chip has 1.5 per CU)
-        const int bty = kBinTY;
-        const int nxy = ((c->nx + P.btx - 1) / P.btx) * ((c->ny + bty - 1) / bty);
-        P.zc = P.D == 3 ? (c->tune_zc > 0 ? std::min(c->tune_zc, c->nz)
-                                           : std::max(1, std::min(kBinZCMax, nxy * c->nz / 400)))
-                        : 1;
+        // Its z chunk: the fewest rounds of workgroups over the chip times a
+        // workgroup's planes and two planes' time for its halo planes.  A CU
+        // holds 1024 threads of it in FP32 and 512 in FP64 (registers; LDS
+        // allows no more).  FP64 on MI355X, phase, with the first chunk that
+        // left about 400 workgroups and now: 128 x 64 x 64, 5 -> 4 planes, 55
+        // -> 49 us, 160 x 80 x 80, 10 -> 8, 99 -> 89, 256 x 64 x 64, 5 -> 8,
+        // 103 -> 91; 96 x 48 x 48 keeps its 2 (25.4 us; 1, 3, 4: 28.5, 32.5,
+        // 30.8).  FP32 beyond the caches is level over 4 to 16 planes.
+        const int nxy = ((c->nx + P.btx - 1) / P.btx) * ((c->ny + kBinTY - 1) / kBinTY);
+        const long slots = (long)kCus * (P.esz == 8 ? 512 : 1024) / (P.btx * kBinTY);
+        P.zc = 1;
+        if (P.D == 3 && c->tune_zc > 0) P.zc = std::min(c->tune_zc, c->nz);
+        else if (P.D == 3) {
+            long best = 0;
+            for (int zc = 1; zc <= std::min(kBinZCMax, c->nz); ++zc) {
+                const long wgs = (long)nxy * ((c->nz + zc - 1) / zc);
+                const long cost = (wgs + slots - 1) / slots * (zc + 2);
+                if (zc == 1 || cost < best) { best = cost; P.zc = zc; }
+            }
+        }
         P.nbb = nxy * (P.D == 3 ? (c->nz + P.zc - 1) / P.zc : 1);
     }
     const size_t N = P.N, e = P.esz;
@@ -271,7 +284,7 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
     P.fprof = take(sizeof(double) * c->ny);
     P.vn = take(e * P.D * N);
     // statistics partials: one per stream-collide workgroup (1-D blocks, or
-    // the binomial tiles when the SGS change is deferred)
+    // the tiles of k_step_t when the SGS change is deferred)
     P.part_stats = take(sizeof(double) * 4 * std::max(P.nb1, P.nbb));
     P.part_diag = take(sizeof(double) * 2 * P.nb1);
     P.work1 = take(sizeof(int2) * P.nb1);
@@ -353,7 +366,7 @@ std::vector<int> xcd_order(int n)
     return order;
 }
 
-// The same for the binomial tiles, in tile-id order (xy fastest): the
+// The same for the tiles of k_step_t, in tile-id order (xy fastest): the
 // workgroups an XCD runs at the same time are neighbouring tiles of the same
 // z chunks, whose halo rows they share in that XCD's L2 (measured on MI355X:
 // 8-13% faster than keeping the z chunks of a tile together).
@@ -458,25 +471,23 @@ struct lbm_ctx {
     // bitwise the same.  Where the lines lie (MI355X, whole TO step, us,
     // in place -> records):
     //  - past the 256 MB Infinity Cache (192 MB of populations) records always;
-    //    FP32 channels below it are level on aligned rows (96 x 48 x 48 64.6
-    //    -> 64.8, 160 x 80 x 80 176 -> 178, 192 x 96 x 96 279 -> 273) and lose
-    //    on others (295 x 47 x 98 216 -> 239).
-    //  - D3Q19 in FP64, twice the bytes: records on rows of whole half tiles
-    //    (48 x 24 x 24 56 -> 54, 96 x 48 x 48 102 -> 92, 128 x 64 x 64 183 ->
-    //    175, 144 x 48 x 51 136 -> 127, 160 x 80 x 80 304 -> 292), in place on
-    //    others (97 x 47 x 49 105 -> 111, 161 x 79 x 81 312 -> 341).
-    //  - D2Q9 pulls need no aligned rows in FP64: records from 24 MB (512^2, 18
-    //    MB, 29.4 -> 29.5; 640^2, 28 MB, 52 -> 48; 897 x 701 73 -> 71; 1024^2
-    //    103 -> 92); in FP32 on rows of whole tiles from 32 MB (768^2, 20 MB,
-    //    35.5 -> 34.8; 1024^2, 36 MB, 60.6 -> 58.5; 512 x 4096 102 -> 93; but
-    //    1001 x 1003 56.9 -> 58.7, 1290^2 86 -> 90).
+    //    FP32 channels below it are level (96 x 48 x 48 64.6 -> 64.8, 160 x 80 x
+    //    80 176 -> 178, 192 x 96 x 96 279 -> 273) or lose (97 x 47 x 49 66 ->
+    //    72, 295 x 47 x 98 217 -> 222).
+    //  - D3Q19 in FP64, twice the bytes: records (48 x 24 x 24 56 -> 54, 96 x 48
+    //    x 48 102 -> 92, 97 x 47 x 49 104 -> 101, 128 x 64 x 64 183 -> 167),
+    //    from 64 MB only on rows of whole half tiles (160 x 80 x 80 304 -> 281,
+    //    but 161 x 79 x 81 309 -> 317, 33 x 80 x 200 195 -> 204).
+    //  - D2Q9: records from 24 MB (FP64 512^2, 18 MB, 29.4 -> 29.5, 640^2, 28 MB,
+    //    52 -> 48, 1001 x 1003 100 -> 84; FP32 768^2, 20 MB, 35.5 -> 34.8, 900^2,
+    //    28 MB, 51 -> 50, 1290^2 87 -> 79, 2048^2 175 -> 163).
     bool defers() const
     {
         if (mode() != 2 || cfg.substrate == LBM_WALE) return false;
         const double mb = (double)plan.N * plan.Q * plan.esz / (1024.0 * 1024);
         if ((cfg.tune_mem & 4) || mb > 192) return true;
-        if (plan.D == 3) return plan.esz == 8 && cfg.nx % (kBinTX / 2) == 0;
-        return plan.esz == 8 ? mb > 24 : cfg.nx % kBinTX == 0 && mb > 32;
+        if (plan.D == 3) return plan.esz == 8 && (mb < 64 || cfg.nx % (kBinTX / 2) == 0);
+        return mb > 24;
     }
 };
 
@@ -537,6 +548,7 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.cnl = c->plan.cnl;
     g.btx = c->plan.btx;
     g.wt = write_through((double)c->plan.N * c->plan.Q * c->plan.esz);
+    g.rag = c->cfg.nx * c->plan.esz % 128 != 0;
     g.a32 = (double)c->plan.popn * c->plan.esz < 4294967296.0 && !(c->cfg.tune_mem & 1);
     g.nt = non_temporal((double)c->plan.popn * c->plan.esz) || (c->cfg.tune_mem & 2);
     g.defer = c->defers();
@@ -1736,6 +1748,7 @@ static int batch_build(lbm_batch* b)
             g.a32 &= (double)b->mem[i]->plan.popn * b->mem[i]->plan.esz < 4294967296.0 &&
                      !(b->mem[i]->cfg.tune_mem & 1);
             g.nt |= (b->mem[i]->cfg.tune_mem & 2) != 0;
+            g.rag |= b->mem[i]->cfg.nx * b->mem[i]->plan.esz % 128 != 0;
             const lbm_ctx* c = b->mem[i];
             g.any_z |= c->cur.has_z;
             g.maxsa = std::max(g.maxsa, c->cur.nsa);
@@ -1861,7 +1874,7 @@ void lbm_batch_destroy(lbm_batch* b)
 
 // Per-phase timing: nsteps eager steps with events at the phase boundaries,
 // on the context stream.  ms[k] is the mean duration of phase k per step
-// (stream-collide, curl, binomial powers, reduce, solve, apply); launches[k]
+// (stream-collide, curl, filters, reduce, solve, apply); launches[k]
 // the number of kernel launches of phase k per step.
 int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
 {

@@ -23,7 +23,7 @@ constexpr int kBinTX = 32;      // tiled stream-collide: x extent of a tile
 constexpr int kBinTY = kBlock / kBinTX;  // y extent
 constexpr int kBinTXW = 64;     // the wide tile (64 x 8, 512 threads)
 constexpr int kBinZCMax = 16;   // most z planes per workgroup chosen automatically (3-D)
-// The binomial apply forms the member's solve in every workgroup (one per
+// The apply forms the member's solve in every workgroup (one per
 // pair of 256-cell blocks of a member) where its launch has at most this
 // many workgroups: at two waves per SIMD they are all resident at once on
 // the 256 CUs, so the solve's latency is paid once per launch, under the

@@ -15,6 +15,10 @@
 //   k_chain    binomial closures (Sec. 4.1): from v* the sensitivities
 //              R R v* of the E QoIs, U = R R w of the Z QoIs (w = curl v*) and
 //              the QoI sums, every power of B on chip.
+//   k_chain_pair  2-D closures of at most one E and one Z QoI: the chains,
+//              the adjoint curl and the Gram products in one launch.
+//   k_kxy, k_kz   kernel filters: the x and y parts of a filter, and its z part.
+//   k_fpack, k_fmask, k_funpack  Fourier bands around two hipFFT transforms.
 //   k_reduce   sensitivities curl^T U of the Z QoIs (App. A) and the Gram
 //              products, reduced per workgroup in FP64.
 //   k_sum      fixed-order cross-workgroup sums; the step's LRS draw.
@@ -170,7 +174,11 @@ __device__ __forceinline__ size_t pop_at64(int i, size_t c)
 // non-temporally (5228 -> 5310..5321 MLUPS on 384 x 192 x 192; no change on
 // 295 x 47 x 98): the stream-collide itself slows (457 -> 485 us), but its
 // populations then no longer push the TO fields out of the Infinity Cache
-// (binomial pass 209 -> 203 us, reduce 453 -> 424 us, curl 86 -> 79 us).
+// (reduce 453 -> 424 us).  Except where a kernel stores row segments of rows
+// that are not whole lines (wt = 2, k_step_t): a line's two parts then come
+// from two workgroups, non-temporally each goes out by itself, a plain store
+// leaves it to the L2 to join them (tiled stream-collide, FP32 230 x 130 x 130
+// 344 -> 216 us; FP64 1001 x 1003, whole step 94 -> 84 us).
 template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v)
 {
@@ -179,7 +187,8 @@ __device__ __forceinline__ void st_dev(T* p, T v)
 template <typename T>
 __device__ __forceinline__ void st_fld(T* p, T v, int wt)
 {
-    if (wt) st_dev(p, v);
+    if (wt == 1) st_dev(p, v);
+    else if (wt == 2) *p = v;
     else __builtin_nontemporal_store(v, p);
 }
 // Loads of fields whose last reader in the step is the loading kernel: on
@@ -421,7 +430,7 @@ __device__ __forceinline__ void moments(const T* f, T& drho, T* j)
 // population is updated as f_i + (force term - omega (f_i - feq_i)), one
 // rounding at its own magnitude.  Plain FP32 storage keeps the direct form
 // as the baseline.
-template <int LAT, typename T, int PREC, int SUB, int MODE, bool WT, bool A32 = MODE == 2, bool NT = false>
+template <int LAT, typename T, int PREC, int SUB, int MODE, int WT, bool A32 = MODE == 2, bool NT = false>
 __device__ __forceinline__ void collide_cell(KMember& m, T* f, int x, int y, int z, int cell, T* __restrict__ gd,
                                              double* st, int& bad)
 {
@@ -620,7 +629,7 @@ __global__ __launch_bounds__(kBlock, MODE == 2 ? 1 : 8) void k_step(const DevMem
 
 // K1t: the TO stream-collide with the previous step's SGS change deferred
 // into the pull.  A workgroup owns a TX x TY tile of the xy plane and a chunk
-// of zc planes (the binomial-filter tiling and work table).  For every plane
+// of zc planes.  For every plane
 // of the chunk and one halo plane on each side, the record (a, b) of the tile
 // and its one-cell xy halo is staged in LDS together with e = a.b; the pull
 // of population i at cell x then reads g*_i(x - c_i) from memory and the
@@ -633,7 +642,7 @@ __global__ __launch_bounds__(kBlock, MODE == 2 ? 1 : 8) void k_step(const DevMem
 #ifndef LBM_STEPT_WAVES
 #define LBM_STEPT_WAVES 4
 #endif
-template <int LAT, typename T, int PREC, int SUB, int TX, bool WT, bool A32 = true>
+template <int LAT, typename T, int PREC, int SUB, int TX, int WT, bool A32 = true>
 __global__ __launch_bounds__(TX * kBinTY, sizeof(T) == 4 ? LBM_STEPT_WAVES : 2) void k_step_t(const DevMember* __restrict__ mems,
                                                    const int2* __restrict__ work, int flip)
 {
@@ -1826,7 +1835,7 @@ static __global__ __launch_bounds__(kBlock) void k_sum(const DevMember* __restri
 //
 // It runs in one of two places.  k_solve: one workgroup per member, writing
 // the coefficients, the record and the control state for k_apply.  Or in
-// every workgroup of the binomial apply k_apply_fs (small launches), with
+// every workgroup of the apply k_apply_fs (small launches), with
 // the apply's own field loads in flight meanwhile, each workgroup forming
 // the same coefficients from the same sums with the same arithmetic; there
 // the member's first workgroup alone writes the record, advances the step
@@ -3060,7 +3069,7 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
 #undef LBM_REDUCE
     mark(4);
     hipLaunchKernelGGL(k_sum, dim3(g.nbs), blk, 0, st, g.mems, g.works);
-    // the binomial apply forms the solve itself (one launch less per step)
+    // the apply forms the solve itself on small launches (one launch less per step)
     const bool fused = fused_solve(g);
     if (!fused) hipLaunchKernelGGL(k_solve, dim3(g.nmem), blk, 0, st, g.mems, g.workm);
     mark(5);
@@ -3107,17 +3116,15 @@ void launch_step_group(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_
             hipLaunchKernelGGL((k_moments<LAT, T, PREC, false>), dim3(g.nb1), blk, 0, st, g.mems, g.work1, flip,
                                (double*)nullptr, (double*)nullptr);
     }
+#define LBM_STEP_TK(SUB, TXV, ...)                                                                         \
+    hipLaunchKernelGGL((k_step_t<LAT, T, PREC, SUB, TXV, __VA_ARGS__>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, \
+                       g.workb, flip)
 #define LBM_STEP_T(SUB, TXV)                                                                               \
     do {                                                                                                   \
-        if (!g.a32)                                                                                        \
-            hipLaunchKernelGGL((k_step_t<LAT, T, PREC, SUB, TXV, false, false>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, \
-                               g.mems, g.workb, flip);                                                     \
-        else if (g.wt)                                                                                     \
-            hipLaunchKernelGGL((k_step_t<LAT, T, PREC, SUB, TXV, true>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems,  \
-                               g.workb, flip);                                                             \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_step_t<LAT, T, PREC, SUB, TXV, false>), dim3(g.nbb), dim3(TXV * kBinTY), 0, st, g.mems, \
-                               g.workb, flip);                                                             \
+        if (!g.a32) LBM_STEP_TK(SUB, TXV, 2, false);                                                       \
+        else if (g.wt) LBM_STEP_TK(SUB, TXV, 1);                                                           \
+        else if (g.rag) LBM_STEP_TK(SUB, TXV, 2);                                                          \
+        else LBM_STEP_TK(SUB, TXV, 0);                                                                     \
     } while (0)
 #define LBM_STEP_SUB(SUB)                                                                                  \
     do {                                                                                                   \
@@ -3157,6 +3164,7 @@ void launch_step_group(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_
         LBM_STEP_SUB(LBM_BGK);
 #undef LBM_STEP_SUB
 #undef LBM_STEP_T
+#undef LBM_STEP_TK
 to_chain:
     mark(1);
     if (g.mode == 2) {

@@ -78,11 +78,11 @@ struct LaunchGroup {
     int kmem, kdim[3];  // the member and its grid
     const FourierProg* fprog;   // Fourier band QoIs (host memory; null if none)
     int wt;             // store the fields the next kernel reads through the L2 (small launches)
-    int defer;          // TO mode: the SGS change is recorded and applied by the next step's pull
+    int defer;          // TO mode: the SGS change is recorded and applied by the next step's pull (k_step_t)
     int a32;            // every member's population buffer spans less than 4 GiB (32-bit offsets)
     int nt;             // plain runs: the launch's populations exceed the Infinity Cache (non-temporal stores)
+    int rag;            // rows of some member are not whole 128-byte lines (k_step_t: plain stores)
     int sep_solve;      // TO mode: the solve in its own launch (k_solve) even where k_apply could form it
-                        // (k_step_t over the binomial tiles); not with the WALE substrate
 };
 
 // TO mode: the apply forms the solve itself (no k_solve launch): not for
@@ -97,7 +97,7 @@ enum { OP_INIT = 0, OP_GET_POP = 1, OP_SET_POP = 2, OP_STREAM = 3 };
 
 // ev (nullable): 7 events recorded at the phase boundaries of the step
 // (start, after stream-collide, after the curl of kernel-filter closures,
-// after the binomial powers, after the reduce, after the cross-block sums and
+// after the filters, after the reduce, after the cross-block sums and
 // solve, after the apply).
 constexpr int kNumPhases = 6;
 void launch_step(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev = nullptr);

@@ -1,5 +1,6 @@
-// lbm_tune.cpp -- the autotuner of the launch shapes (binomial tile width,
-// z planes per binomial workgroup, cells per thread of the QoI reduction).
+// lbm_tune.cpp -- the autotuner of the launch shapes (tile width and z planes
+// per workgroup of the tiled stream-collide, cells per thread of the QoI
+// reduction).
 //
 // A client of the library's own C ABI: each candidate tuning is created in
 // the caller's scratch arena, stepped from a small seeded velocity field and

@@ -11,10 +11,12 @@ from gpu_util import fp64_bars, gpu_run, need_gpu, oracle_floor, oracle_run, rel
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (nx, ny, nz, precision): rows of whole half tiles and not; below and
-    # above 24 MB of FP64 populations; above 32 MB of FP32 ones, whole tiles and not
+    # (nx, ny, nz, precision): rows of whole half tiles and not; 2-D below and
+    # above 24 MB of populations; rows that are not whole lines on launches
+    # that do not write through; above 64 MB in FP64
     (15, 9, 6, "fp64"), (16, 9, 6, "fp64"), (17, 8, 5, "fp64"), (48, 10, 9, "fp64"), (16, 9, 6, "fp32"),
     (592, 590, 1, "fp64"), (591, 592, 1, "fp64"), (992, 940, 1, "fp32"), (993, 940, 1, "fp32"),
+    (836, 836, 1, "fp32"), (837, 836, 1, "fp32"), (97, 47, 49, "fp64"), (161, 41, 71, "fp32"), (129, 60, 58, "fp64"),
 ]
 
 
