@@ -1318,25 +1318,21 @@ int lbm_fields(lbm_ctx* c, double* rho, double* u)
     const size_t N = c->plan.N, D = c->plan.D;
     int frc = flush(c);
     if (frc) return frc;
+    // FP32 velocities are widened by the kernel and FP64 ones read where they
+    // are, so the host only receives them (the velocity alone, from a copy of
+    // vn widened by one host thread to now: 480 x 240 x 240 120 -> 63 ms, 384 x
+    // 192 x 192 61 -> 33, 96 x 48 x 48 FP64 0.7..1.6 -> 0.4)
+    const bool wide = c->plan.esz == 4;
     double* buf = nullptr;
-    HIPCHK(hipMalloc(&buf, sizeof(double) * (D + 1) * N));
+    if (wide || rho) HIPCHK(hipMalloc(&buf, sizeof(double) * (D + 1) * N));
     launch_fields(c->cfg.lattice, c->cfg.precision, c->dm, (const int2*)(c->arena + c->plan.work1), c->plan.nb1,
-                  c->has_to, c->phase, c->stream, buf + D * N);
+                  c->has_to, c->phase, c->stream, rho ? buf + D * N : nullptr, wide ? buf : nullptr);
     int rc = LBM_OK;
     if (hipStreamSynchronize(c->stream) != hipSuccess) rc = fail(LBM_EDEVICE, "moments kernel failed");
-    // velocity is in vn (element type of the run); widen on the host
-    if (!rc) {
-        const size_t e = c->plan.esz;
-        std::vector<char> tmp(e * D * N);
-        if (hipMemcpy(tmp.data(), c->arena + c->plan.vn, tmp.size(), hipMemcpyDeviceToHost) != hipSuccess)
-            rc = fail(LBM_EDEVICE, "copy failed");
-        else {
-            for (size_t k = 0; k < D * N; ++k)
-                u[k] = e == 8 ? ((const double*)tmp.data())[k] : (double)((const float*)tmp.data())[k];
-            if (rho && hipMemcpy(rho, buf + D * N, sizeof(double) * N, hipMemcpyDeviceToHost) != hipSuccess)
-                rc = fail(LBM_EDEVICE, "copy failed");
-        }
-    }
+    const void* v = wide ? (const void*)buf : (const void*)(c->arena + c->plan.vn);
+    if (!rc && (hipMemcpy(u, v, sizeof(double) * D * N, hipMemcpyDeviceToHost) != hipSuccess ||
+                (rho && hipMemcpy(rho, buf + D * N, sizeof(double) * N, hipMemcpyDeviceToHost) != hipSuccess)))
+        rc = fail(LBM_EDEVICE, "copy failed");
     (void)hipFree(buf);
     return rc;
 }
