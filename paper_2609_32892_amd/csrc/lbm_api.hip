@@ -1318,22 +1318,34 @@ int lbm_fields(lbm_ctx* c, double* rho, double* u)
     const size_t N = c->plan.N, D = c->plan.D;
     int frc = flush(c);
     if (frc) return frc;
-    // FP32 velocities are widened by the kernel and FP64 ones read where they
-    // are, so the host only receives them (the velocity alone, from a copy of
-    // vn widened by one host thread to now: 480 x 240 x 240 120 -> 63 ms, 384 x
-    // 192 x 192 61 -> 33, 96 x 48 x 48 FP64 0.7..1.6 -> 0.4)
-    const bool wide = c->plan.esz == 4;
+    // The velocity is received in the caller's array, FP32 in its upper half and
+    // widened from there, first to last: the doubles of a block end at or before
+    // the first float still to be read.  (The velocity alone, MI355X, against a
+    // zeroed vector as the stop on the way: 480 x 240 x 240 120 -> 66 ms, 96 x 48
+    // x 48 0.41 -> 0.39 ms, in FP64 0.7..1.6 -> 0.4, 128^2 0.09 -> 0.04; widened by
+    // the kernel and received as doubles instead: 63, 0.58, -, 0.04..0.14 ms.)
+    const size_t n = D * N;
+    const bool narrow = c->plan.esz == 4;
+    char* half = (char*)u + sizeof(float) * n;
     double* buf = nullptr;
-    if (wide || rho) HIPCHK(hipMalloc(&buf, sizeof(double) * (D + 1) * N));
+    if (rho) HIPCHK(hipMalloc(&buf, sizeof(double) * N));
     launch_fields(c->cfg.lattice, c->cfg.precision, c->dm, (const int2*)(c->arena + c->plan.work1), c->plan.nb1,
-                  c->has_to, c->phase, c->stream, rho ? buf + D * N : nullptr, wide ? buf : nullptr);
+                  c->has_to, c->phase, c->stream, buf);
     int rc = LBM_OK;
     if (hipStreamSynchronize(c->stream) != hipSuccess) rc = fail(LBM_EDEVICE, "moments kernel failed");
-    const void* v = wide ? (const void*)buf : (const void*)(c->arena + c->plan.vn);
-    if (!rc && (hipMemcpy(u, v, sizeof(double) * D * N, hipMemcpyDeviceToHost) != hipSuccess ||
-                (rho && hipMemcpy(rho, buf + D * N, sizeof(double) * N, hipMemcpyDeviceToHost) != hipSuccess)))
+    else if (hipMemcpy(narrow ? (void*)half : (void*)u, c->arena + c->plan.vn, c->plan.esz * n,
+                       hipMemcpyDeviceToHost) != hipSuccess ||
+             (rho && hipMemcpy(rho, buf, sizeof(double) * N, hipMemcpyDeviceToHost) != hipSuccess))
         rc = fail(LBM_EDEVICE, "copy failed");
-    (void)hipFree(buf);
+    else if (narrow) {
+        float t[1024];
+        for (size_t k = 0; k < n; k += 1024) {
+            const size_t m = std::min<size_t>(1024, n - k);
+            std::memcpy(t, half + sizeof(float) * k, sizeof(float) * m);
+            for (size_t l = 0; l < m; ++l) u[k + l] = (double)t[l];
+        }
+    }
+    if (buf) (void)hipFree(buf);
     return rc;
 }
 
