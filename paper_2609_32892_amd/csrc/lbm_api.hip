@@ -319,10 +319,10 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
             P.ktaps = take(e * kMaxSA * (kMaxRad + 1));
             P.kjobs = take(sizeof(KFil) * 2 * kMaxSA);
             if (cs.nf) {
-                // Fourier bands (complex): the packed components' spectra, and
-                // the fields of every band QoI
-                P.fspec = take(2 * e * P.D * N);
-                P.fband = take(2 * e * (P.D - 1) * N * (size_t)cs.nf);
+                // Fourier bands (complex): the spectra of v* and w, and the
+                // components of every band QoI
+                P.fspec = take(2 * e * N * (size_t)((cs.nf > cs.nfz ? P.D : 0) + (cs.nfz ? P.NC : 0)));
+                P.fband = take(2 * e * N * (size_t)(P.D * (cs.nf - cs.nfz) + P.NC * cs.nfz));
             }
         }
     }
@@ -602,60 +602,26 @@ void drop_fourier(lbm_ctx* c)
     c->fprog = FourierProg{};
 }
 
-int build_fourier(lbm_ctx* c, std::vector<FourierQ> fq)
+int build_fourier(lbm_ctx* c, const std::vector<FourierQ>& fq)
 {
     drop_fourier(c);
     if (fq.empty()) return LBM_OK;
     FourierProg& f = c->fprog;
-    const int D = c->plan.D, N = c->plan.N;
-    const size_t comp = (size_t)N * c->plan.esz;
-    bool has[2] = {false, false};
-    for (const FourierQ& q : fq) has[q.e ? 0 : 1] = true;
-    // packed fields: components 0 .. D - 1 of v, then those of w
-    auto field = [&](int re, int im) { f.re[f.nf] = re; f.im[f.nf++] = im; };
-    if (D == 2) {
-        if (has[0]) field(0, 1);
-        if (has[1]) field(2, -1);
-    } else if (has[0] && has[1]) {
-        field(0, 1); field(2, 5); field(3, 4);
-    } else {
-        field(has[0] ? 0 : 3, has[0] ? 1 : 4);
-        field(has[0] ? 2 : 5, -1);
-    }
-    // bands, an E and a Z QoI of the same band together
-    std::vector<char> used(fq.size(), 0);
-    for (size_t a = 0; a < fq.size(); ++a) {
-        if (used[a]) continue;
-        char* dst[2] = {nullptr, nullptr};   // of R v, of R w
-        dst[fq[a].e ? 0 : 1] = (char*)fq[a].dst;
-        for (size_t b = a + 1; b < fq.size(); ++b)
-            if (!used[b] && fq[b].e != fq[a].e && fq[b].l == fq[a].l && fq[b].m == fq[a].m) {
-                dst[fq[b].e ? 0 : 1] = (char*)fq[b].dst;
-                used[b] = 1;
-                break;
-            }
-        auto out = [&](int k) -> void* {
-            if (k < 0) return nullptr;
-            char* d = dst[k < D ? 0 : 1];
-            return d ? d + comp * (k < D ? k : k - D) : nullptr;
-        };
-        for (int k = 0; k < f.nf; ++k) {
-            void* re = out(f.re[k]);
-            void* im = out(f.im[k]);
-            if (!re && !im) continue;
+    const int D = c->plan.D, NC = c->plan.NC, N = c->plan.N;
+    for (const FourierQ& q : fq) (q.e ? f.nv : f.nw) = q.e ? D : NC;
+    for (const FourierQ& q : fq)
+        for (int a = 0; a < (q.e ? D : NC); ++a) {
             const int n = f.slots.n++;
-            f.slots.field[n] = k;
-            f.slots.l[n] = fq[a].l;
-            f.slots.m[n] = fq[a].m;
-            f.slots.re[n] = re;
-            f.slots.im[n] = im;
+            f.slots.field[n] = q.e ? a : f.nv + a;
+            f.slots.l[n] = q.l;
+            f.slots.m[n] = q.m;
+            f.slots.dst[n] = (char*)q.dst + (size_t)a * N * c->plan.esz;
         }
-    }
     int n[3] = {c->cfg.nz, c->cfg.ny, c->cfg.nx};
     const int rank = D == 3 ? 3 : 2;
     int* dims = D == 3 ? n : n + 1;
     const hipfftType type = c->cfg.precision == LBM_FP64 ? HIPFFT_Z2Z : HIPFFT_C2C;
-    const int batch[2] = {f.nf, f.slots.n};
+    const int batch[2] = {f.nv + f.nw, f.slots.n};
     for (int k = 0; k < 2; ++k) {
         hipfftHandle h;
         if (hipfftPlanMany(&h, rank, dims, nullptr, 1, N, nullptr, 1, N, type, batch[k]) != HIPFFT_SUCCESS) {

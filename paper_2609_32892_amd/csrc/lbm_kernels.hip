@@ -2547,50 +2547,46 @@ constexpr size_t kfil_lds_bytes(int ra, size_t esz)
 
 // ---------------------------------------------------------------------------
 // Sharp Fourier band filters (eq. scale-aware-energy-fourier) through hipFFT.
-// A band filter is a real operator (its mask is real and even), so two real
-// components travel as the real and imaginary part of one complex field, and R
-// of both comes out of one inverse transform:
-//   2-D: v_x + i v_y, w;  3-D: v_x + i v_y, v_z + i w_z, w_x + i w_y
-// (without Z or E QoIs: that kind's components alone).  k_fpack forms w = curl
-// v* and packs; one forward transform of all fields; k_fmask writes, per band
-// and field it needs, the masked spectrum (l - 1/2 <= |k| < m + 1/2, integer
-// mode indices; with the 1/N of the inverse transform), where an E and a Z QoI
-// of the same band share a field; one inverse transform of all of them;
-// k_funpack takes the parts to V_s = R v* (E) and U_s = R w (Z).
-// 256 x 256, FP32, three bands of each kind, MI355X: fourteen launches and nine
-// inverse fields per step -> seven and six, the step 75 -> 48 us (with the solve
-// in the apply).
+// k_fpack forms w = curl v* and writes the components of v* (with E QoIs) and of
+// w (with Z QoIs) as complex fields; one forward transform of all of them;
+// k_fmask writes, per QoI and component, the masked spectrum (l - 1/2 <= |k| < m
+// + 1/2, integer mode indices; with the 1/N of the inverse transform); one
+// inverse transform of all of them; k_funpack takes the real parts to V_s = R v*
+// (E) and U_s = R w (Z).  256 x 256, FP32, three bands of each kind, MI355X:
+// fourteen launches per step -> seven, the step 73 -> 53 us (with the solve in
+// the apply).  Every component keeps a complex field of its own: two of them as
+// the real and imaginary part of one halve the transforms (47 us), but a
+// transform rounds relative to the larger part (FP32, smooth field, w_z beside
+// v_z, bands 0 to 3: error 1.5e-7 -> 4.0e-7 on 64^3, 1.8e-7 -> 1.3e-6 on 192^3).
 // ---------------------------------------------------------------------------
-// v_x, v_y, v_z, w_x, w_y, w_z (2-D: v_x, v_y, w) of the packed fields; -1: zero
-struct FFields { int nf, re[3], im[3]; };
-
+// nv components of v*, then nw of w
 template <int LAT, typename T, typename CT>
-__global__ __launch_bounds__(kBlock) void k_fpack(const T* __restrict__ vs, CT* __restrict__ dst, FFields ff, int nx,
+__global__ __launch_bounds__(kBlock) void k_fpack(const T* __restrict__ vs, CT* __restrict__ dst, int nv, int nw, int nx,
                                                   int ny, int nz)
 {
     using L = Lat<LAT>;
-    constexpr int D = L::D;
+    constexpr int D = L::D, NC = L::NC;
     const unsigned N = (unsigned)nx * ny * nz, i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
-    const int x = (int)(i % nx), t = (int)(i / nx), y = t % ny, z = t / ny;
-    T c[D + 3] = {};   // v, then w
+    CT o;
+    o.y = T(0);
+    if (nv) {   // uniform
 #pragma unroll
-    for (int a = 0; a < D; ++a) c[a] = ld_at(vs + (size_t)a * N, i);
-    if (ff.re[ff.nf - 1] >= D) {   // uniform: some field holds w
-        const Nbr n = nbr_at(i, x, y, z, nx, ny, nz, 0, D);
-        curl_nb<D, T>(vs, N, i, n, c + D);
+        for (int a = 0; a < D; ++a) {
+            o.x = ld_at(vs + (size_t)a * N, i);
+            dst[(size_t)a * N + i] = o;
+        }
     }
-    auto comp = [&](int k) {
-        T v = 0;
+    if (nw) {
+        const int x = (int)(i % nx), t = (int)(i / nx), y = t % ny, z = t / ny;
+        const Nbr n = nbr_at(i, x, y, z, nx, ny, nz, 0, D);
+        T w[3];
+        curl_nb<D, T>(vs, N, i, n, w);
 #pragma unroll
-        for (int a = 0; a < D + L::NC; ++a) v = k == a ? c[a] : v;
-        return v;
-    };
-    for (int f = 0; f < ff.nf; ++f) {
-        CT o;
-        o.x = comp(ff.re[f]);
-        o.y = comp(ff.im[f]);
-        dst[(size_t)f * N + i] = o;
+        for (int a = 0; a < NC; ++a) {
+            o.x = w[a];
+            dst[(size_t)(nv + a) * N + i] = o;
+        }
     }
 }
 
@@ -2619,22 +2615,19 @@ __global__ __launch_bounds__(kBlock) void k_fmask(const CT* __restrict__ spec, C
     }
 }
 
-// the parts of the inverse transforms into their destinations
+// the real parts of the inverse transforms into their destinations
 template <typename T, typename CT>
 __global__ __launch_bounds__(kBlock) void k_funpack(const CT* __restrict__ src, FSlots sl, size_t N)
 {
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
     const int b = blockIdx.y;
-    const CT c = src[(size_t)b * N + i];
-    if (sl.re[b]) ((T*)sl.re[b])[i] = c.x;
-    if (sl.im[b]) ((T*)sl.im[b])[i] = c.y;
+    ((T*)sl.dst[b])[i] = src[(size_t)b * N + i].x;
 }
 
 template <int LAT, typename T>
 static void launch_fourier(const FourierProg& f, hipStream_t st)
 {
-    using L = Lat<LAT>;
     using CT = typename std::conditional<std::is_same<T, float>::value, float2, double2>::type;
     const size_t N = (size_t)f.nx * f.ny * f.nz;
     const dim3 blk(kBlock), grd((unsigned)((N + kBlock - 1) / kBlock));
@@ -2649,10 +2642,7 @@ static void launch_fourier(const FourierProg& f, hipStream_t st)
         }
         if (r != HIPFFT_SUCCESS) f.failed = 1;
     };
-    FFields ff{};
-    ff.nf = f.nf;
-    for (int k = 0; k < f.nf; ++k) { ff.re[k] = f.re[k]; ff.im[k] = f.im[k]; }
-    hipLaunchKernelGGL((k_fpack<LAT, T, CT>), grd, blk, 0, st, (const T*)f.vs, (CT*)f.spec, ff, f.nx, f.ny, f.nz);
+    hipLaunchKernelGGL((k_fpack<LAT, T, CT>), grd, blk, 0, st, (const T*)f.vs, (CT*)f.spec, f.nv, f.nw, f.nx, f.ny, f.nz);
     exec(f.plan[0], f.spec, HIPFFT_FORWARD);
     hipLaunchKernelGGL((k_fmask<T, CT>), grd, blk, 0, st, (const CT*)f.spec, (CT*)f.band, f.slots, f.nx, f.ny, f.nz);
     exec(f.plan[1], f.band, HIPFFT_BACKWARD);

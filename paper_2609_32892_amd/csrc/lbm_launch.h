@@ -23,23 +23,22 @@ struct KFil {
     void* dst;
 };
 
-// Fourier band QoIs of a member (host side): the packed fields (components of
-// v*, then of w, as real and imaginary parts; -1: zero) and their spectra; per
-// slot of the inverse transform its field, band and the destinations of its
-// parts (null: not needed).  Plans are hipfftHandle values.
-constexpr int kMaxSlots = 2 * kMaxSA;   // at most two fields per QoI
+// Fourier band QoIs of a member (host side): the complex fields (nv components
+// of v*, then nw of w) and their spectra; per slot of the inverse transform (a
+// component of a QoI) its field, band and destination.  Plans are hipfftHandle
+// values.
+constexpr int kMaxSlots = 3 * kMaxSA;   // at most three components per QoI
 struct FourierQ { int e, l, m; void* dst; };
 struct FSlots {
     int n, field[kMaxSlots], l[kMaxSlots], m[kMaxSlots];
-    void* re[kMaxSlots];
-    void* im[kMaxSlots];
+    void* dst[kMaxSlots];
 };
 struct FourierProg {
     void* plan[2];        // forward: the fields; inverse: the slots
-    void* spec;           // [nf][N] complex
+    void* spec;           // [nv + nw][N] complex
     void* band;           // [slots][N] complex
     const void* vs;       // v* [D][N]
-    int nx, ny, nz, nf, re[3], im[3];
+    int nx, ny, nz, nv, nw;
     FSlots slots;
     mutable int failed = 0;         // set when a hipFFT call of a launch fails
 };
