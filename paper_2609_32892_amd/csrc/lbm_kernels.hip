@@ -1470,14 +1470,14 @@ __device__ __forceinline__ void chain_pair(KMember& m, KParam* prm, int tile)
         if (ne) {
             st_fld_at(kV, c, ve[0][r], WT);
             st_fld_at(kV + sN, c, ve[1][r], WT);
-            acc[2] += (double)(ve[0][r] * ve[0][r] + ve[1][r] * ve[1][r]);
+            acc[2] += (double)fma_(ve[1][r], ve[1][r], ve[0][r] * ve[0][r]);
         }
         if (nz) {
             st_fld_at(kV + (size_t)(2 * ne) * sN, c, z0, WT);
             st_fld_at(kV + (size_t)(2 * ne + 1) * sN, c, z1, WT);
-            acc[4] += (double)(z0 * z0 + z1 * z1);
+            acc[4] += (double)fma_(z1, z1, z0 * z0);
         }
-        if (ne && nz) acc[3] += (double)(ve[0][r] * z0 + ve[1][r] * z1);
+        if (ne && nz) acc[3] += (double)fma_(ve[1][r], z1, ve[0][r] * z0);
     }
 #pragma unroll
     for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
@@ -1611,9 +1611,11 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) voi
         for (int s = 0; s < MAXSA; ++s)
 #pragma unroll
             for (int t2 = s; t2 < MAXSA; ++t2, ++g) {
-                T d = 0;
+                // (contracted alike in every variant: a batch may take another
+                // one than a member alone)
+                T d = V[s][0] * V[t2][0];
 #pragma unroll
-                for (int a = 0; a < D; ++a) d += V[s][a] * V[t2][a];
+                for (int a = 1; a < D; ++a) d = fma_(V[s][a], V[t2][a], d);
                 acc[NQ + g] += (double)d;
             }
         if (hasmp) {
