@@ -197,12 +197,20 @@ void even_tiles(const lbm_config* c, int vx, int rows, int H, int* tvx, int* tvy
     *nxy = *ntx * nty;
 }
 
+// Chains of a binomial closure, the workgroups of a tile: the components of v*
+// with E QoIs, those of w with Z QoIs.
+int chain_jobs(const Plan& P, const ClosureShape& cs)
+{
+    return cs.kf ? 0 : (cs.nsa > cs.nzb ? P.D : 0) + (cs.nzb ? P.NC : 0);
+}
+
 // Tiles of the filter chains (k_chain, k_chain_pair).  A wavefront's 64 lanes hold a tile's
 // cells in x and a halo of H = powers on each side; the workgroup's rows
 // hold its cells in y and the same halo, except at a wall, beyond which rows
 // are zero anyway.  Tiles are evened out over the grid.
-void chain_tiles(const lbm_config* c, Plan* P)
+void chain_tiles(const lbm_config* c, const ClosureShape& cs, Plan* P)
 {
+    const int jobs = std::max(chain_jobs(*P, cs), 1);
     const int H = P->cnl, NR = chain_waves(P->D) * chain_rows(P->D, P->esz);
     int nxy;
     even_tiles(c, 64 - 2 * H, NR, H, &P->cvx, &P->cvy, &P->cntx, &nxy);
@@ -210,14 +218,16 @@ void chain_tiles(const lbm_config* c, Plan* P)
     P->czc = 1;
     if (P->D == 3) {
         // z chunk: the fewest rounds of workgroups over the CUs (one per CU)
-        // times a workgroup's planes, taken in pairs, and about ten planes'
-        // time to start and end (measured on MI355X, whole phase: 96 x 48 x 48
-        // with chunks of 3, 4, 5, 6, 8 planes 37, 37, 26, 27, 30 us; 384 x 192
-        // x 192 with 32, 48, 64 planes 540, 571, 515 us)
+        // times a workgroup's planes, taken in pairs, and about six planes'
+        // time to start and end
+        // (measured on MI355X, whole phase: 96 x 48 x 48 with chunks of 3, 4, 5,
+        // 6, 8 planes 37, 37, 26, 27, 30 us; 384 x 192 x 192 with 32, 48, 64 planes
+        // 540, 571, 515 us; 256 x 128 x 128 with 32, 64, 128 planes 193, 232, 226
+        // us, two E QoIs alone 102, 98, 177)
         double best = 0;
         for (int zc = 1; zc <= c->nz; ++zc) {
-            const int wgs = nxy * ((c->nz + zc - 1) / zc) * (P->D + P->NC);
-            const double cost = (double)((wgs + kCus - 1) / kCus) * ((zc + 2 * P->cnl + 1) / 2 * 2 + 10);
+            const int wgs = nxy * ((c->nz + zc - 1) / zc) * jobs;
+            const double cost = (double)((wgs + kCus - 1) / kCus) * ((zc + 2 * P->cnl + 1) / 2 * 2 + 6);
             if (zc == 1 || cost < best) { best = cost; P->czc = zc; }
         }
     }
@@ -296,7 +306,7 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
         P.W = take(cs.has_z ? e * (size_t)(cs.nsa + (cs.kf ? 1 : 0)) * P.NC * N : kAlign);
         P.kV = take(e * (size_t)std::max(cs.nsa, 1) * P.D * N);
         P.cnl = std::max(cs.jv, cs.jw) <= 2 ? 2 : 4;
-        chain_tiles(c, &P);
+        chain_tiles(c, cs, &P);
         P.part_q = take(sizeof(double) * (size_t)std::max(cs.nsa, 1) * P.cnt * P.D);
         P.workc = take(sizeof(int2) * P.nbc);
         P.workq = take(sizeof(int2) * std::max(P.pnt, 1));
@@ -373,6 +383,16 @@ std::vector<int> xcd_order(int n)
 std::vector<int> xcd_tile_order(int ntx, int nty, int ntz)
 {
     return xcd_order(ntx * nty * ntz);
+}
+
+// The same for the filter chains, entries tile (D + NC) + chain: a tile's chains
+// one after another, those of a kind without QoIs left out.
+std::vector<int> chain_order(const Plan& P, const ClosureShape& cs)
+{
+    const int n = chain_jobs(P, cs), nv = cs.nsa > cs.nzb ? P.D : 0;
+    std::vector<int> o = xcd_order(P.cnt * n);
+    for (int& b : o) b = b / n * (P.D + P.NC) + (b % n < nv ? b % n : P.D + b % n - nv);
+    return o;
 }
 
 // The same for the reduce, whose workgroup y nbx2 + bx takes cells of one row
@@ -507,14 +527,11 @@ struct lbm_batch {
 
 namespace {
 
-// The larger of a closure's numbers of E and Z QoIs.
-int chain_kinds(const ClosureShape& cs) { return std::max(cs.nzb, cs.nsa - cs.nzb); }
-
 // 2-D binomial closures of at most one QoI of each kind and no mean-profile
 // QoIs form their sums in the chains' launch (k_chain_pair).
 int pair_closure(const lbm_ctx* c)
 {
-    return c->plan.D == 2 && c->cur.nsa > 0 && !c->cur.kf && c->cur.nmp == 0 && chain_kinds(c->cur) <= 1;
+    return c->plan.D == 2 && c->cur.nsa > 0 && !c->cur.kf && c->cur.nmp == 0 && c->cur.nzb <= 1 && c->cur.nsa - c->cur.nzb <= 1;
 }
 
 // The member record's fields that follow the closure mode.
@@ -544,7 +561,8 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.mode = c->mode();
     g.any_z = c->cur.has_z;
     g.maxsa = c->cur.nsa;
-    g.maxk = chain_kinds(c->cur);
+    g.maxe = c->cur.nsa - c->cur.nzb;
+    g.maxz = c->cur.nzb;
     g.cnl = c->plan.cnl;
     g.btx = c->plan.btx;
     g.wt = write_through((double)c->plan.N * c->plan.Q * c->plan.esz);
@@ -566,7 +584,7 @@ LaunchGroup ctx_group(const lbm_ctx* c)
     g.workb = (const int2*)(c->arena + c->plan.workb);
     g.nbb = c->plan.nbb;
     g.workc = (const int2*)(c->arena + c->plan.workc);
-    g.nbc = c->plan.nbc;
+    g.nbc = c->plan.cnt * chain_jobs(c->plan, c->cur);
     g.pair = pair_closure(c);
     g.workq = (const int2*)(c->arena + c->plan.workq);
     g.nbq = c->plan.pnt;
@@ -877,6 +895,11 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
     ctl.s_pend = 0;
     rc = upload(c, c->arena + c->plan.ctl, &ctl, sizeof ctl);
     if (rc) return rc;
+    // the chains' work table
+    std::vector<int2> wc;
+    for (int b : chain_order(c->plan, cs)) wc.push_back(make_int2(0, b));
+    if (!wc.empty()) rc = upload(c, c->arena + c->plan.workc, wc.data(), sizeof(int2) * wc.size());
+    if (rc) return rc;
     c->hp = p;
     c->cur = cl ? cs : ClosureShape{};
     c->hm.npart = c->cur.npart();
@@ -1065,12 +1088,6 @@ int lbm_create(const lbm_config* cfg, const lbm_closure* closure, void* dev_aren
             for (int b = 0; b < plan.nbb; ++b) wb[b] = make_int2(0, o[b]);
         }
         if (!rc) rc = upload(c, A + plan.workb, wb.data(), sizeof(int2) * wb.size());
-        std::vector<int2> wc(plan.nbc);
-        {
-            const std::vector<int> o = xcd_order(plan.nbc);
-            for (int b = 0; b < plan.nbc; ++b) wc[b] = make_int2(0, o[b]);
-        }
-        if (!rc) rc = upload(c, A + plan.workc, wc.data(), sizeof(int2) * wc.size());
         std::vector<int2> wq(plan.pnt);
         {
             const std::vector<int> o = xcd_order(plan.pnt);
@@ -1667,8 +1684,8 @@ static int batch_build(lbm_batch* b)
         o.wc = work.size();
         if (keys[gi].mode == 2)
             for (int i : gm[gi]) {
-                const std::vector<int> oc = xcd_order(b->mem[i]->plan.nbc);
-                for (int k = 0; k < b->mem[i]->plan.nbc; ++k) work.push_back(make_int2(i, oc[k]));
+                const lbm_ctx* c = b->mem[i];
+                for (int k : chain_order(c->plan, c->cur)) work.push_back(make_int2(i, k));
             }
         o.nbc = work.size() - o.wc;
         o.wq = work.size();
@@ -1726,7 +1743,8 @@ static int batch_build(lbm_batch* b)
             const lbm_ctx* c = b->mem[i];
             g.any_z |= c->cur.has_z;
             g.maxsa = std::max(g.maxsa, c->cur.nsa);
-            g.maxk = std::max(g.maxk, chain_kinds(c->cur));
+            g.maxe = std::max(g.maxe, c->cur.nsa - c->cur.nzb);
+            g.maxz = std::max(g.maxz, c->cur.nzb);
             g.defer = c->defers();   // (members of a group share mode and substrate)
             g.sep_solve = (c->cfg.tune_mem & 8) != 0;
             if (keys[gi].kfm >= 0) {
@@ -1876,7 +1894,7 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
         const int m = g.mode;
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
         launches[1] = m == 2 && g.nkfil > 0 && g.any_z ? 1 : 0;
-        launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.maxk > 0 ? 1 : 0)) : 0;
+        launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.nbc > 0 ? 1 : 0)) : 0;
         launches[3] = m == 2 && !g.pair ? 1 : 0;   // (k_chain_pair forms the sums)
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)
         launches[5] = m == 2 ? 1 : (m == 1 ? 2 : 0);

@@ -1340,7 +1340,6 @@ __global__ __launch_bounds__(64 * chain_waves(Lat<LAT>::D), Lat<LAT>::D == 2 ? 1
     KMember& m = *kc(mems + wk.x);
     KParam* prm = kc(m.prm);
     const int tile = wk.y / (D + NC), job = wk.y % (D + NC);
-    if (prm->nk[job < D ? 0 : 1] == 0) return;   // uniform
     if constexpr (NW > 1) {
         for (int k = threadIdx.x; k < NL * 512; k += 64 * NW) {   // the slots beyond the first and last wavefront
             const int l = k / 512, e = k % 512;
@@ -1524,11 +1523,18 @@ __global__ __launch_bounds__(64) void k_chain_pair(const DevMember* __restrict__
 // neighbours missing the L2; 5.5 TB/s) and 11 us on 96 x 48 x 48 (436 and 14.5
 // us with the powers of B as input).
 // ---------------------------------------------------------------------------
+// Waves per SIMD asked of the compiler (FP32): what a variant fits without
+// spills.
+template <typename T, int ME, int MZ, bool KF> constexpr int reduce_waves()
+{
+    if (sizeof(T) == 8 || (ME + MZ == 8 && MZ > 0)) return 1;
+    return KF && (ME > 3 || MZ > 3) ? 3 : 4;
+}
 // ME, MZ: most E and Z QoIs of a member (its E QoIs come first, so that the
 // loads of each kind have their own registers); ME = 0: MZ of either kind
 // (uneven closures).
 template <int LAT, typename T, int ME, int MZ, bool KF, bool WT>
-__global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) void k_reduce(
+__global__ __launch_bounds__(kBlock, (reduce_waves<T, ME, MZ, KF>())) void k_reduce(
     const DevMember* __restrict__ mems, const int2* __restrict__ work)
 {
     using L = Lat<LAT>;
@@ -1536,6 +1542,8 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) voi
     constexpr int MAXSA = ME + MZ, NG = MAXSA * (MAXSA + 1) / 2;
     constexpr int NQ = KF ? MAXSA : 0;
     constexpr int NV = NQ + NG + 1 + MAXSA;
+    constexpr int NLD = D == 2 ? 4 : 12;                                  // loads of a curl
+    constexpr int ZG = D == 3 && MZ == 6 ? 3 : (MZ == 0 ? 1 : MZ);       // Z positions loaded at a time
     __shared__ double lds[NV * (kBlock / 64)];
     const int2 wk = work[blockIdx.x];
     KMember& m = *kc(mems + wk.x);
@@ -1560,41 +1568,77 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 && ME + MZ <= 6 ? 4 : 1) voi
         const int x = p % nx, z = p / nx;
         const unsigned cell = (unsigned)(x + nx * (y + ny * z));
         const Nbr n = nbr_at(cell, x, y, z, nx, ny, nz, m.walls, D);
-        T V[MAXSA][D], v0[D], ld[MZ > 0 ? MZ : 1][D == 2 ? 4 : 12];
+        T V[MAXSA][D], v0[D], ld[ZG][NLD];
         if (KF) {
 #pragma unroll
             for (int a = 0; a < D; ++a) v0[a] = ld_at((const T*)m.vs + (size_t)a * sN, cell);
         } else {
             v0[0] = hasmp ? ld_at((const T*)m.vs, cell) : T(0);
         }
+        if constexpr (MZ <= ZG) {
 #pragma unroll
-        for (int s = 0; s < MZ; ++s) {
+            for (int s = 0; s < MZ; ++s) {
 #pragma unroll
-            for (int k = 0; k < (D == 2 ? 4 : 12); ++k) ld[s][k] = 0;
-            const int q = nz0 + s;   // (the branches are uniform)
-            if (ME == 0 && q < ne) {
+                for (int k = 0; k < NLD; ++k) ld[s][k] = 0;
+                const int q = nz0 + s;   // (the branches are uniform)
+                if (ME == 0 && q < ne) {
 #pragma unroll
-                for (int a = 0; a < D; ++a) ld[s][a] = ld_at(kV + (size_t)(q * D + a) * sN, cell);
-            } else if (q < nsa) {
-                curlT_load<D, T>((const T*)m.W + (size_t)q * NC * sN, sN, n, ld[s]);
+                    for (int a = 0; a < D; ++a) ld[s][a] = ld_at(kV + (size_t)(q * D + a) * sN, cell);
+                } else if (q < nsa) {
+                    curlT_load<D, T>((const T*)m.W + (size_t)q * NC * sN, sN, n, ld[s]);
+                }
             }
-        }
 #pragma unroll
-        for (int s = 0; s < ME; ++s)
+            for (int s = 0; s < ME; ++s)
 #pragma unroll
-            for (int a = 0; a < D; ++a) V[s][a] = s < ne ? ld_at(kV + (size_t)(s * D + a) * sN, cell) : T(0);
+                for (int a = 0; a < D; ++a) V[s][a] = s < ne ? ld_at(kV + (size_t)(s * D + a) * sN, cell) : T(0);
 #pragma unroll
-        for (int s = 0; s < MZ; ++s) {
-            const int q = nz0 + s;
-            if (ME == 0 && q < ne) {
+            for (int s = 0; s < MZ; ++s) {
+                const int q = nz0 + s;
+                if (ME == 0 && q < ne) {
 #pragma unroll
-                for (int a = 0; a < D; ++a) V[s][a] = ld[s][a];
-                continue;
+                    for (int a = 0; a < D; ++a) V[s][a] = ld[s][a];
+                    continue;
+                }
+                curlT_eval<D, T>(ld[s], n.okm, n.okp, V[ME + s]);
+                if (q < nsa) {
+#pragma unroll
+                    for (int a = 0; a < D; ++a) st_fld_at(kV + (size_t)(q * D + a) * sN, cell, V[ME + s][a], WT);
+                }
             }
-            curlT_eval<D, T>(ld[s], n.okm, n.okp, V[ME + s]);
-            if (q < nsa) {
+        } else {
+            // ZG positions at a time, within the registers of ld
+            static_assert(ME == 0, "grouped positions hold either kind");
 #pragma unroll
-                for (int a = 0; a < D; ++a) st_fld_at(kV + (size_t)(q * D + a) * sN, cell, V[ME + s][a], WT);
+            for (int s0 = 0; s0 < MZ; s0 += ZG) {
+#pragma unroll
+                for (int k = 0; k < ZG; ++k) {
+                    const int q = s0 + k;
+                    if (q >= MZ) continue;
+#pragma unroll
+                    for (int j = 0; j < NLD; ++j) ld[k][j] = 0;
+                    if (q < ne) {
+#pragma unroll
+                        for (int a = 0; a < D; ++a) ld[k][a] = ld_at(kV + (size_t)(q * D + a) * sN, cell);
+                    } else if (q < nsa) {
+                        curlT_load<D, T>((const T*)m.W + (size_t)q * NC * sN, sN, n, ld[k]);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < ZG; ++k) {
+                    const int q = s0 + k;
+                    if (q >= MZ) continue;
+                    if (q < ne) {
+#pragma unroll
+                        for (int a = 0; a < D; ++a) V[q][a] = ld[k][a];
+                        continue;
+                    }
+                    curlT_eval<D, T>(ld[k], n.okm, n.okp, V[q]);
+                    if (q < nsa) {
+#pragma unroll
+                        for (int a = 0; a < D; ++a) st_fld_at(kV + (size_t)(q * D + a) * sN, cell, V[q][a], WT);
+                    }
+                }
             }
         }
         if constexpr (KF) {
@@ -3036,11 +3080,11 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
             if (g.cnl == 2) LBM_PAIR(2); else LBM_PAIR(4);
 #undef LBM_PAIR
         }
-    } else if (!g.kf && g.maxk > 0) {
+    } else if (g.nbc > 0) {
 #define LBM_CHAIN(NLV, MSV)                                                                                    \
     hipLaunchKernelGGL((k_chain<LAT, T, NLV, MSV>), dim3(g.nbc), dim3(64 * chain_waves(Lat<LAT>::D)), 0, st, g.mems, g.workc)
-        if (g.cnl == 2) { if (g.maxk <= 4) LBM_CHAIN(2, 4); else LBM_CHAIN(2, 8); }
-        else { if (g.maxk <= 4) LBM_CHAIN(4, 4); else LBM_CHAIN(4, 8); }
+        if (g.cnl == 2) { if (g.maxe <= 4 && g.maxz <= 4) LBM_CHAIN(2, 4); else LBM_CHAIN(2, 8); }
+        else { if (g.maxe <= 4 && g.maxz <= 4) LBM_CHAIN(4, 4); else LBM_CHAIN(4, 8); }
 #undef LBM_CHAIN
     }
     mark(3);
@@ -3049,12 +3093,21 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
         if (g.wt) hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, true>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
         else hipLaunchKernelGGL((k_reduce<LAT, T, MEV, MZV, KFV, false>), dim3(g.nbr), blk, 0, st, g.mems, g.workr); \
     } while (0)
-#define LBM_REDUCE_KIND(KFV)                   \
-    do {                                       \
-        if (g.maxk <= 1) LBM_REDUCE(1, 1, KFV);    \
-        else if (g.maxk <= 3) LBM_REDUCE(3, 3, KFV); \
-        else if (g.maxk <= 4) LBM_REDUCE(4, 4, KFV); \
-        else LBM_REDUCE(0, 8, KFV);            \
+    // The variant of most positions a member fills.  MI355X, FP32, 256 x 128 x 128
+    // and 96 x 48 x 48, us: two E QoIs <3, 0> 22 and 7.4, <3, 3> 37 and 10; five
+    // E <8, 0> 49 and 12, <0, 6> 58 and 11, <0, 8> 92 and 14; two Z <3, 3> 43 and
+    // 10, the same with no E positions; five E and a Z <0, 6> 84 and 12.5, <0, 8>
+    // 125 and 16; an E and five Z 164 and 16, 202 and 20; two E and four Z <4, 4>
+    // 141 and 14, <0, 6> 142 and 15.
+#define LBM_REDUCE_KIND(KFV)                                               \
+    do {                                                                   \
+        if (g.maxe <= 1 && g.maxz <= 1) LBM_REDUCE(1, 1, KFV);             \
+        else if (g.maxe <= 3 && g.maxz == 0) LBM_REDUCE(3, 0, KFV);        \
+        else if (g.maxe <= 3 && g.maxz <= 3) LBM_REDUCE(3, 3, KFV);        \
+        else if (g.maxz == 0) LBM_REDUCE(8, 0, KFV);                       \
+        else if (g.maxe <= 4 && g.maxz <= 4) LBM_REDUCE(4, 4, KFV);        \
+        else if (g.maxsa <= 6) LBM_REDUCE(0, 6, KFV);                      \
+        else LBM_REDUCE(0, 8, KFV);                                        \
     } while (0)
     if (g.kf) LBM_REDUCE_KIND(true); else if (!g.pair) LBM_REDUCE_KIND(false);
 #undef LBM_REDUCE_KIND

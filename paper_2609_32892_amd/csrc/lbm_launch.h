@@ -48,8 +48,8 @@ struct FourierProg {
 // the work tables.
 struct LaunchGroup {
     int lattice, precision, substrate, mode;  // mode 0 plain, 1 plain + records, 2 TO
-    int any_z, maxsa;
-    int maxk, cnl;      // binomial closures: most E or Z QoIs of a member; powers of the chains (2 or 4)
+    int any_z, maxsa, maxe, maxz;   // most E/Z, E and Z QoIs of a member
+    int cnl;            // binomial closures: powers of the chains (2 or 4)
     int btx;            // stream-collide tile width of every member (kBinTX or kBinTXW)
     const DevMember* mems;
     const int2* work1;  // cell kernels: (member, block of kBlock cells)

@@ -1,0 +1,92 @@
+"""The first corrected step against the FP64 oracle, in FP32 and FP64, for
+closures that take each variant of the chains and of the reduce: q*, dQ, gamma
+and the velocity with bars from the closure's own conditioning.
+
+Tracking from step 0 towards references 2% above and below the free step's
+QoIs.  With u the precision's epsilon and kappa the condition number of the Gram
+matrix scaled to unit diagonal: q* is an average of squares of fields with a few
+roundings each (8 u; FP64: the stated 1e-12), dQ = q_ref - q* loses a factor
+1 / 0.02, (G^-1)_kk and beta lose kappa (8 kappa u), and the velocity, whose own
+resolution is 1e-5 (FP64: 1e-12), takes dv with the error of beta."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import gpu_run, need_gpu, oracle_run, rel_err
+
+pytestmark = pytest.mark.gpu
+
+E = lambda *f: [("E", x, 0) for x in f]
+Z = lambda *f: [("Z", x, 0) for x in f]
+FIVE = ("I", "B", "B2", "BMID", "IMB")
+SETS = {
+    "pair": E("B") + Z("B"), "pair4": E("B2") + Z("BMID"), "2E": E("B2", "IMB"), "2Z": Z("B2", "IMB"), "5E": E(*FIVE),
+    "5Z": Z(*FIVE), "3E3Z": E("B2", "BMID", "IMB") + Z("B2", "BMID", "IMB"), "5E1Z": E(*FIVE) + Z("B2"),
+    "1E5Z": E("B2") + Z(*FIVE), "2E4Z": E("B2", "IMB") + Z("I", "B2", "BMID", "IMB"),
+    "5E3Z": E(*FIVE) + Z("I", "B2", "BMID"), "4E4Z": E("I", "B2", "BMID", "IMB") + Z("I", "B2", "BMID", "IMB"),
+}
+CASES = [(s, d, "noise") for s in sorted(SETS) for d in (2, 3)]
+
+
+def _flow(d, kind):
+    """White noise between walls (3-D) or periodic (2-D)."""
+    nx, ny, nz = (60, 41, 1) if d == 2 else (30, 18, 11)
+    walls = d - 2
+    cfg = dict(lattice=d - 2, nx=nx, ny=ny, nz=nz, walls_y=walls, tau=0.55, substrate=d - 2, cmodel=0.1,
+               force_kind=2 if walls else 1, force_amp=1e-6, force_k=1, drag=0.0)
+    return cfg, synth.noise_velocity(d, (nz, ny, nx), 0.02, 3)
+
+
+def _check(case, prec, first=None):
+    """first: the closure the run is created with, replaced by the case's."""
+    lbm = need_gpu()
+    name, d, kind = case
+    qois = SETS[name]
+    cfg, u0 = _flow(d, kind)
+    free = oracle_run(cfg, u0, qois, dict(mode="off"))
+    free.step(1)
+    sign = np.where(np.arange(len(qois)) % 2, -0.02, 0.02)
+    qref = free.record_arrays()["q"][:1] * (1 + sign)
+    cargs = dict(mode="track", spinup=0)
+    o = oracle_run(cfg, u0, qois, cargs, qref=qref)
+    o.step(1)
+    plain = oracle_run(cfg, u0)
+    plain.step(1)
+    G = plain.patterns(oracle.make_closure(qois, mode="off"), plain.post_collision_velocity()[1])["G"]
+    s = np.sqrt(np.diag(G))
+    w = np.linalg.eigvalsh(G / np.outer(s, s))
+    kappa = w[-1] / w[0]
+    print(f"first correction {case} {prec} kappa {kappa:.1e}", flush=True)
+    if first is None:
+        run = gpu_run(lbm, cfg, u0, prec, qois, cargs, qref=qref)
+    else:
+        run = gpu_run(lbm, cfg, u0, prec, SETS[first], dict(mode="off"))
+        run.set_closure(lbm.ClosureSpec(qois, qref=qref, **cargs))
+    run.step(1)
+    assert run.sync() == 0
+    rg, ro = run.record_arrays(), o.record_arrays()
+    assert not np.any(ro["flags"]) and not np.any(rg["flags"])
+    uo = o.velocity()[1]
+    dv = np.max(np.abs(uo - plain.velocity()[1])) / np.max(np.abs(uo))
+    u = 1.2e-7 if prec == "fp32" else 2.2e-16
+    q = 8 * u if prec == "fp32" else 1e-12
+    dq = q / 0.02
+    bars = [(1e-5 if prec == "fp32" else 1e-12) + dv * (dq + 8 * kappa * u), q, dq, dq + 8 * kappa * u]
+    got = [rel_err(run.fields()[1], uo)] + [float(np.max(np.abs(rg[k] / ro[k] - 1))) for k in ("q", "dq", "gamma")]
+    print("  velocity %.1e  q %.1e  dq %.1e  gamma %.1e" % tuple(got), " bars %.1e %.1e %.1e %.1e" % tuple(bars), flush=True)
+    assert all(g <= b for g, b in zip(got, bars))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}-{c[1]}D-{c[2]}")
+def test_first_correction(case, prec):
+    _check(case, prec)
+
+
+@pytest.mark.parametrize("name", ["2E", "2Z", "3E3Z"])
+@pytest.mark.parametrize("d", [2, 3])
+def test_first_correction_of_a_replaced_closure(name, d):
+    """The chains' work follows the kinds of the closure that is set, not of the
+    one the run was created with."""
+    _check((name, d, "noise"), "fp32", first="4E4Z")
