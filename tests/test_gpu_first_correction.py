@@ -1,13 +1,17 @@
 """The first corrected step against the FP64 oracle, in FP32 and FP64, for
-closures that take each variant of the chains and of the reduce: q*, dQ, gamma
-and the velocity with bars from the closure's own conditioning.
+closures that take each variant of the chains and of the reduce, kernel filters
+and Fourier bands: q*, dQ, gamma and the velocity with bars from the closure's
+own conditioning.
 
 Tracking from step 0 towards references 2% above and below the free step's
 QoIs.  With u the precision's epsilon and kappa the condition number of the Gram
 matrix scaled to unit diagonal: q* is an average of squares of fields with a few
 roundings each (8 u; FP64: the stated 1e-12), dQ = q_ref - q* loses a factor
 1 / 0.02, (G^-1)_kk and beta lose kappa (8 kappa u), and the velocity, whose own
-resolution is 1e-5 (FP64: 1e-12), takes dv with the error of beta."""
+resolution is 1e-5 (FP64: 1e-12), takes dv with the error of beta.  Kernel filters
+and Fourier bands form q* as 1/2 <v*, V> and V with an error of u |R R| times the
+field they filter (|R R| at most 4 for L_s, else 1), which the ratio of those
+norms to q* and to |V| amplifies."""
 import numpy as np
 import pytest
 
@@ -25,17 +29,39 @@ SETS = {
     "5Z": Z(*FIVE), "3E3Z": E("B2", "BMID", "IMB") + Z("B2", "BMID", "IMB"), "5E1Z": E(*FIVE) + Z("B2"),
     "1E5Z": E("B2") + Z(*FIVE), "2E4Z": E("B2", "IMB") + Z("I", "B2", "BMID", "IMB"),
     "5E3Z": E(*FIVE) + Z("I", "B2", "BMID"), "4E4Z": E("I", "B2", "BMID", "IMB") + Z("I", "B2", "BMID", "IMB"),
+    "kernel": E("G1", "L1") + Z("G1", "L1"), "kernel_wide": E("G3", "L5") + Z("L3"),
+    "kernel_5E1Z": E("G1", "G2", "G3", "L1", "L3") + Z("L1"),
+    "bands": E("F0-2", "F3-6") + Z("F0-2", "F3-6"), "bands_shared": E("F0-3", "F4-6") + Z("F4-6"),
+    "band_kernel": E("F0-3", "G1") + Z("F2-5"),
 }
-CASES = [(s, d, "noise") for s in sorted(SETS) for d in (2, 3)]
+KF = ("kernel", "kernel_wide", "kernel_5E1Z", "bands", "bands_shared", "band_kernel")
+BANDS = KF[3:]
+CASES = [(s, d, "noise") for s in sorted(SETS) for d in (2, 3)] + [(s, d, "shear") for s in BANDS for d in (2, 3)]
 
 
-def _flow(d, kind):
-    """White noise between walls (3-D) or periodic (2-D)."""
+def _flow(name, d, kind):
+    """White noise, or half of it on a shear v_x = 0.05 cos y; between walls in 3-D
+    except for Fourier bands."""
     nx, ny, nz = (60, 41, 1) if d == 2 else (30, 18, 11)
-    walls = d - 2
+    walls = 1 if d == 3 and name not in BANDS else 0
     cfg = dict(lattice=d - 2, nx=nx, ny=ny, nz=nz, walls_y=walls, tau=0.55, substrate=d - 2, cmodel=0.1,
                force_kind=2 if walls else 1, force_amp=1e-6, force_k=1, drag=0.0)
-    return cfg, synth.noise_velocity(d, (nz, ny, nx), 0.02, 3)
+    u0 = synth.noise_velocity(d, (nz, ny, nx), 0.02 if kind == "noise" else 0.01, 3)
+    if kind == "shear":
+        u0[0] += (0.05 * np.cos(2 * np.pi * np.arange(ny) / ny)[None, :, None] * np.ones((nz, 1, nx))).ravel()
+    return cfg, u0
+
+
+def _amplification(o, cfg, qois, v, q, V):
+    """Largest factors from u to the relative errors of q* and of V."""
+    norm = lambda f: float(np.sqrt(np.sum(f * f)))
+    nv, nw = norm(v), norm(o.curl(v))
+    aq = av = 1.0
+    for k, (kind, filt, _) in enumerate(qois):
+        src = (4.0 if filt[0] == "L" else 1.0) * (nv if kind == "E" else nw)
+        aq = max(aq, nv * src / (2 * q[k]))
+        av = max(av, src / norm(V[k]))
+    return aq, av
 
 
 def _check(case, prec, first=None):
@@ -43,7 +69,7 @@ def _check(case, prec, first=None):
     lbm = need_gpu()
     name, d, kind = case
     qois = SETS[name]
-    cfg, u0 = _flow(d, kind)
+    cfg, u0 = _flow(name, d, kind)
     free = oracle_run(cfg, u0, qois, dict(mode="off"))
     free.step(1)
     sign = np.where(np.arange(len(qois)) % 2, -0.02, 0.02)
@@ -53,11 +79,14 @@ def _check(case, prec, first=None):
     o.step(1)
     plain = oracle_run(cfg, u0)
     plain.step(1)
-    G = plain.patterns(oracle.make_closure(qois, mode="off"), plain.post_collision_velocity()[1])["G"]
+    vs = plain.post_collision_velocity()[1]
+    pat = plain.patterns(oracle.make_closure(qois, mode="off"), vs)
+    G = pat["G"]
     s = np.sqrt(np.diag(G))
     w = np.linalg.eigvalsh(G / np.outer(s, s))
     kappa = w[-1] / w[0]
-    print(f"first correction {case} {prec} kappa {kappa:.1e}", flush=True)
+    aq, av = _amplification(plain, cfg, qois, vs, pat["q"], pat["V"]) if name in KF else (1.0, 1.0)
+    print(f"first correction {case} {prec} kappa {kappa:.1e} amplification {aq:.1e} {av:.1e}", flush=True)
     if first is None:
         run = gpu_run(lbm, cfg, u0, prec, qois, cargs, qref=qref)
     else:
@@ -70,9 +99,10 @@ def _check(case, prec, first=None):
     uo = o.velocity()[1]
     dv = np.max(np.abs(uo - plain.velocity()[1])) / np.max(np.abs(uo))
     u = 1.2e-7 if prec == "fp32" else 2.2e-16
-    q = 8 * u if prec == "fp32" else 1e-12
+    q = max(8 * u * aq, 0 if prec == "fp32" else 1e-12)
     dq = q / 0.02
-    bars = [(1e-5 if prec == "fp32" else 1e-12) + dv * (dq + 8 * kappa * u), q, dq, dq + 8 * kappa * u]
+    g = dq + 8 * kappa * av * u
+    bars = [(1e-5 if prec == "fp32" else 1e-12) + dv * g, q, dq, g]
     got = [rel_err(run.fields()[1], uo)] + [float(np.max(np.abs(rg[k] / ro[k] - 1))) for k in ("q", "dq", "gamma")]
     print("  velocity %.1e  q %.1e  dq %.1e  gamma %.1e" % tuple(got), " bars %.1e %.1e %.1e %.1e" % tuple(bars), flush=True)
     assert all(g <= b for g, b in zip(got, bars))
