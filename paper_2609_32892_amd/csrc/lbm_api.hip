@@ -65,7 +65,7 @@ struct ClosureShape {
     int h = 0, nhc = 0;   // LRS history length; k_sum workgroups of its product
     int kf = 0;           // E/Z QoIs use the kernel filters (materialised sensitivities)
     int nzb = 0;          // Z QoIs
-    int kslots = 0, nzq = 0;   // kernel filters: separable terms over the QoIs; Z QoIs
+    int nkq = 0, kcap = 0;     // kernel-filter QoIs; those a workspace of this shape holds
     int nf = 0, nfz = 0;       // Fourier band QoIs; of them Z QoIs
     int npart() const { return nsa + nsa * (nsa + 1) / 2 + nmp * (1 + nsa); }
 };
@@ -118,13 +118,6 @@ int closure_shape(const lbm_config* cfg, const lbm_closure* cl, ClosureShape* ou
             binom = true;
     }
     if (s.kf && binom) return fail(LBM_EINVAL, "closure: binomial and kernel filters cannot be mixed");
-    if (s.kf)
-        for (int k = 0; k < cl->nq; ++k) {
-            const lbm_qoi_spec& q = cl->q[k];
-            if (q.kind != LBM_QOI_E && q.kind != LBM_QOI_Z) continue;
-            s.kslots += q.filter == LBM_FILT_LAPL ? (cfg->lattice == LBM_D2Q9 ? 2 : 3) : (q.filter == LBM_FILT_FOURIER ? 0 : 1);
-            s.nzq += q.kind == LBM_QOI_Z;
-        }
     for (int k = 0; k < cl->nq; ++k) {
         const lbm_qoi_spec& q = cl->q[k];
         if (q.kind == LBM_QOI_E || q.kind == LBM_QOI_Z) {
@@ -132,6 +125,11 @@ int closure_shape(const lbm_config* cfg, const lbm_closure* cl, ClosureShape* ou
             if (q.kind == LBM_QOI_E) { s.jv = std::max(s.jv, p); s.has_e = 1; }
             else { s.jw = std::max(s.jw, p); s.has_z = 1; s.nzb++; }
             s.nsa++;
+            if (s.kf && q.filter != LBM_FILT_FOURIER) {
+                // (a Laplacian makes room for as many Gaussians as it has arms)
+                s.nkq++;
+                s.kcap += q.filter == LBM_FILT_LAPL ? (cfg->lattice == LBM_D2Q9 ? 2 : 3) : 1;
+            }
         } else if (q.kind == LBM_QOI_MP) {
             if (!cfg->walls_y) return fail(LBM_EINVAL, "closure: mean-profile QoIs need walls_y = 1");
             if (q.band < 0 || q.band >= cl->nbands) return fail(LBM_EINVAL, "closure: QoI %d band out of range", k);
@@ -139,6 +137,7 @@ int closure_shape(const lbm_config* cfg, const lbm_closure* cl, ClosureShape* ou
         } else
             return fail(LBM_EINVAL, "closure: QoI %d bad kind", k);
     }
+    s.kcap = std::min(s.kcap, s.nsa);
     if (s.nsa > kMaxSA) return fail(LBM_EINVAL, "closure: at most %d energy/enstrophy QoIs", kMaxSA);
     if (s.nmp > 0 && !(cl->band_dmin > 0 && cl->band_dmax > cl->band_dmin)) return fail(LBM_EINVAL, "closure: band range");
     if (cl->mode == LBM_CLOSURE_LRS && (!cl->C || !cl->Sigma)) return fail(LBM_EINVAL, "closure: LRS needs C and Sigma");
@@ -303,6 +302,8 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
     if (cs.nq > 0) {
         P.rho = take(e * N);
         P.vs = take(e * P.D * N);
+        // U_s of every QoI: a closure that replaces this one may have all nsa
+        // of its QoIs of kind Z
         P.W = take(cs.has_z ? e * (size_t)(cs.nsa + (cs.kf ? 1 : 0)) * P.NC * N : kAlign);
         P.kV = take(e * (size_t)std::max(cs.nsa, 1) * P.D * N);
         P.cnl = std::max(cs.jv, cs.jw) <= 2 ? 2 : 4;
@@ -323,9 +324,10 @@ void make_plan(const lbm_config* c, const ClosureShape& cs, Plan* p)
         P.works = take(sizeof(int2) * P.nbs);
         P.hpart = take(sizeof(double) * kMaxQ * std::max(cs.nhc, 1));
         if (cs.kf) {
-            // kernel filters: [D][N] work fields, three per QoI (the two
-            // intermediates and R u); tap tables; the jobs of both applications
-            P.kT = take(e * P.D * N * (size_t)(3 * cs.nsa));
+            // kernel filters: [D][N] work fields, three per kernel-filter QoI
+            // (the two intermediates and R u); tap tables; the jobs of both
+            // applications
+            P.kT = take(e * P.D * N * (size_t)(3 * cs.kcap));
             P.ktaps = take(e * kMaxSA * (kMaxRad + 1));
             P.kjobs = take(sizeof(KFil) * 2 * kMaxSA);
             if (cs.nf) {
@@ -707,7 +709,7 @@ int build_kfil(lbm_ctx* c, const lbm_closure* cl, const ClosureShape& cs, const 
         c->krad = std::max(c->krad, j.ra);
         j.ncomp = E ? D : NC;
         j.taps = A + c->plan.ktaps + first.size() * W * e;
-        char* work = A + c->plan.kT + (size_t)(3 * s) * D * N * e;   // y1, y2, R u
+        char* work = A + c->plan.kT + 3 * first.size() * D * N * e;   // y1, y2, R u
         j.y1 = work;
         j.y2 = work + D * N * e;
         j.src = E ? A + c->plan.vs : A + c->plan.W + (size_t)cs.nsa * NC * N * e;
@@ -764,8 +766,7 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         const ClosureShape& cap = c->plan.cap;
         if (!c->has_to || cs.nsa > cap.nsa || cs.jv > cap.jv || (cs.has_z && (!cap.has_z || cs.jw > cap.jw)) ||
             cs.npart() > cap.npart() || cs.nbands > std::max(cap.nbands, 1) || cs.nhc > cap.nhc ||
-            (cs.kf && (!cap.kf || cs.kslots > cap.kslots || cs.nzq > cap.nzq || cs.nf - cs.nfz > cap.nf - cap.nfz ||
-                       cs.nfz > cap.nfz)))
+            (cs.kf && (!cap.kf || cs.nkq > cap.kcap || cs.nf - cs.nfz > cap.nf - cap.nfz || cs.nfz > cap.nfz)))
             return fail(LBM_ENOMEM, "closure does not fit the workspace planned at creation");
         if (cs.h > 0 && cl->spinup < c->host_step + cs.h)
             return fail(LBM_EINVAL, "closure: spinup must be at least the step count plus the history length");
@@ -818,6 +819,7 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         }
         const int nq = cl->nq;
         p.kf = cs.kf;
+        c->nkfil = 0;
         if (cs.kf) {
             rc = build_kfil(c, cl, cs, sa);
             if (rc) return rc;

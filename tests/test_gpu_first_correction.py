@@ -31,19 +31,21 @@ SETS = {
     "5E3Z": E(*FIVE) + Z("I", "B2", "BMID"), "4E4Z": E("I", "B2", "BMID", "IMB") + Z("I", "B2", "BMID", "IMB"),
     "kernel": E("G1", "L1") + Z("G1", "L1"), "kernel_wide": E("G3", "L5") + Z("L3"),
     "kernel_5E1Z": E("G1", "G2", "G3", "L1", "L3") + Z("L1"),
+    "gauss": E("G1", "G2") + Z("G1", "G2"), "gauss_pair": E("G1") + Z("G2"), "lapl_bands": E("F0-3") + Z("L1"),
+    "identity": E("I") + Z("I"),
     "bands": E("F0-2", "F3-6") + Z("F0-2", "F3-6"), "bands_shared": E("F0-3", "F4-6") + Z("F4-6"),
     "band_kernel": E("F0-3", "G1") + Z("F2-5"),
 }
-KF = ("kernel", "kernel_wide", "kernel_5E1Z", "bands", "bands_shared", "band_kernel")
-BANDS = KF[3:]
+BANDS = ("bands", "bands_shared", "band_kernel", "lapl_bands")
+KF = ("kernel", "kernel_wide", "kernel_5E1Z", "gauss", "gauss_pair") + BANDS
 CASES = [(s, d, "noise") for s in sorted(SETS) for d in (2, 3)] + [(s, d, "shear") for s in BANDS for d in (2, 3)]
 
 
-def _flow(name, d, kind):
+def _flow(names, d, kind):
     """White noise, or half of it on a shear v_x = 0.05 cos y; between walls in 3-D
     except for Fourier bands."""
     nx, ny, nz = (60, 41, 1) if d == 2 else (30, 18, 11)
-    walls = 1 if d == 3 and name not in BANDS else 0
+    walls = 1 if d == 3 and not any(n in BANDS for n in names) else 0
     cfg = dict(lattice=d - 2, nx=nx, ny=ny, nz=nz, walls_y=walls, tau=0.55, substrate=d - 2, cmodel=0.1,
                force_kind=2 if walls else 1, force_amp=1e-6, force_k=1, drag=0.0)
     u0 = synth.noise_velocity(d, (nz, ny, nx), 0.02 if kind == "noise" else 0.01, 3)
@@ -69,7 +71,7 @@ def _check(case, prec, first=None):
     lbm = need_gpu()
     name, d, kind = case
     qois = SETS[name]
-    cfg, u0 = _flow(name, d, kind)
+    cfg, u0 = _flow((name, first), d, kind)
     free = oracle_run(cfg, u0, qois, dict(mode="off"))
     free.step(1)
     sign = np.where(np.arange(len(qois)) % 2, -0.02, 0.02)
@@ -114,9 +116,21 @@ def test_first_correction(case, prec):
     _check(case, prec)
 
 
-@pytest.mark.parametrize("name", ["2E", "2Z", "3E3Z"])
+@pytest.mark.parametrize("first,name", [("4E4Z", "2E"), ("4E4Z", "2Z"), ("4E4Z", "3E3Z"), ("gauss", "kernel"),
+                                        ("kernel", "gauss"), ("lapl_bands", "gauss_pair"), ("kernel", "identity")])
 @pytest.mark.parametrize("d", [2, 3])
-def test_first_correction_of_a_replaced_closure(name, d):
-    """The chains' work follows the kinds of the closure that is set, not of the
-    one the run was created with."""
-    _check((name, d, "noise"), "fp32", first="4E4Z")
+def test_first_correction_of_a_replaced_closure(first, name, d):
+    """The work follows the closure that is set, not the one the run was created
+    with: chains of the other kind, Laplacians in the place of as many Gaussians
+    and back, Gaussians in the fields of a Laplacian, no kernel filters left."""
+    _check((name, d, "noise"), "fp32", first=first)
+
+
+def test_kernel_filters_need_fields_planned():
+    """Bands plan no fields for a kernel filter that replaces them."""
+    lbm = need_gpu()
+    cfg, u0 = _flow(("bands",), 2, "noise")
+    run = gpu_run(lbm, cfg, u0, "fp32", E("F0-2"), dict(mode="off"))
+    with pytest.raises(lbm.LbmError) as e:
+        run.set_closure(lbm.ClosureSpec(E("G1")))
+    assert e.value.code == lbm.ENOMEM
