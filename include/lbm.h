@@ -325,7 +325,8 @@ int lbm_set_state(lbm_ctx* ctx, const void* host, size_t bytes);
  * lbm_autotune_bytes(cfg, closure) bytes; its contents are overwritten),
  * each for `steps` steps after a warm-up, started from a small seeded
  * velocity field: a coordinate descent from the automatic choice over the
- * tile width, then the z chunk, then the cells per thread.  Every candidate
+ * tile width, then the z chunk, then the cells per thread, each only where the
+ * run launches what it shapes (else 0, the automatic choice).  Every candidate
  * gives the same per-cell results (tile width and z chunk bitwise; the
  * cells per thread change only the order of the FP64 partial sums).
  * cache_path (may be NULL): a text file with one line per device, grid and

@@ -450,9 +450,61 @@ bool cholesky_host(const double* A, int n, double* L, int ld)
 
 }  // namespace
 
-// Error reporting for the library's other translation units.
+namespace {
+
+// The SGS change goes into the next step's pull (a record per cell, 2 D
+// values written and read instead of Q populations read and written)
+// except with the WALE substrate, whose velocity gradients need the
+// complete post-streaming state, and on small grids, where the in-place
+// apply is cheaper than the tiled pull with its staged records (32 x 8
+// tiles: lanes past the grid's edge idle).  Either way the result is
+// bitwise the same.  Where the lines lie (MI355X, whole TO step, us,
+// in place -> records):
+//  - past the 256 MB Infinity Cache (192 MB of populations) records always;
+//    FP32 channels below it are level (96 x 48 x 48 64.6 -> 64.8, 160 x 80 x
+//    80 176 -> 178, 192 x 96 x 96 279 -> 273) or lose (97 x 47 x 49 66 ->
+//    72, 295 x 47 x 98 217 -> 222).
+//  - D3Q19 in FP64, twice the bytes: records (48 x 24 x 24 56 -> 54, 96 x 48
+//    x 48 102 -> 92, 97 x 47 x 49 104 -> 101, 128 x 64 x 64 183 -> 167),
+//    from 64 MB only on rows of whole half tiles (160 x 80 x 80 304 -> 281,
+//    but 161 x 79 x 81 309 -> 317, 33 x 80 x 200 195 -> 204).
+//  - D2Q9: records from 24 MB (FP64 512^2, 18 MB, 29.4 -> 29.5, 640^2, 28 MB,
+//    52 -> 48, 1001 x 1003 100 -> 84; FP32 768^2, 20 MB, 35.5 -> 34.8, 900^2,
+//    28 MB, 51 -> 50, 1290^2 87 -> 79, 2048^2 175 -> 163).
+bool deferred(const lbm_config& cfg, const Plan& plan)
+{
+    if (cfg.substrate == LBM_WALE) return false;
+    const double mb = (double)plan.N * plan.Q * plan.esz / (1024.0 * 1024);
+    if ((cfg.tune_mem & 4) || mb > 192) return true;
+    if (plan.D == 3) return plan.esz == 8 && (mb < 64 || cfg.nx % (kBinTX / 2) == 0);
+    return mb > 24;
+}
+
+// 2-D binomial closures of at most one QoI of each kind and no mean-profile
+// QoIs form their sums in the chains' launch (k_chain_pair).
+bool pair_shape(const Plan& plan, const ClosureShape& cs)
+{
+    return plan.D == 2 && cs.nsa > 0 && !cs.kf && cs.nmp == 0 && cs.nzb <= 1 && cs.nsa - cs.nzb <= 1;
+}
+
+}  // namespace
+
+// For the library's other translation units.
 namespace lbm {
 int set_error(int code, const char* msg) { return fail(code, "%s", msg); }
+
+// Whether a run of cfg and closure launches the tiled stream-collide and the
+// reduce (whose shapes the tune_* fields are).
+void tuned_launches(const lbm_config* cfg, const lbm_closure* closure, bool* tiled, bool* reduce)
+{
+    ClosureShape cs;
+    Plan p;
+    *tiled = *reduce = false;
+    if (!closure || check_config(cfg) || closure_shape(cfg, closure, &cs)) return;
+    make_plan(cfg, cs, &p);
+    *tiled = deferred(*cfg, p);
+    *reduce = !pair_shape(p, cs);
+}
 }
 
 struct lbm_ctx {
@@ -484,33 +536,7 @@ struct lbm_ctx {
     long gver = -1;
     int gchunk = 32;
     int mode() const { return cur.nq > 0 ? 2 : (cfg.diag ? 1 : 0); }
-    // The SGS change goes into the next step's pull (a record per cell, 2 D
-    // values written and read instead of Q populations read and written)
-    // except with the WALE substrate, whose velocity gradients need the
-    // complete post-streaming state, and on small grids, where the in-place
-    // apply is cheaper than the tiled pull with its staged records (32 x 8
-    // tiles: lanes past the grid's edge idle).  Either way the result is
-    // bitwise the same.  Where the lines lie (MI355X, whole TO step, us,
-    // in place -> records):
-    //  - past the 256 MB Infinity Cache (192 MB of populations) records always;
-    //    FP32 channels below it are level (96 x 48 x 48 64.6 -> 64.8, 160 x 80 x
-    //    80 176 -> 178, 192 x 96 x 96 279 -> 273) or lose (97 x 47 x 49 66 ->
-    //    72, 295 x 47 x 98 217 -> 222).
-    //  - D3Q19 in FP64, twice the bytes: records (48 x 24 x 24 56 -> 54, 96 x 48
-    //    x 48 102 -> 92, 97 x 47 x 49 104 -> 101, 128 x 64 x 64 183 -> 167),
-    //    from 64 MB only on rows of whole half tiles (160 x 80 x 80 304 -> 281,
-    //    but 161 x 79 x 81 309 -> 317, 33 x 80 x 200 195 -> 204).
-    //  - D2Q9: records from 24 MB (FP64 512^2, 18 MB, 29.4 -> 29.5, 640^2, 28 MB,
-    //    52 -> 48, 1001 x 1003 100 -> 84; FP32 768^2, 20 MB, 35.5 -> 34.8, 900^2,
-    //    28 MB, 51 -> 50, 1290^2 87 -> 79, 2048^2 175 -> 163).
-    bool defers() const
-    {
-        if (mode() != 2 || cfg.substrate == LBM_WALE) return false;
-        const double mb = (double)plan.N * plan.Q * plan.esz / (1024.0 * 1024);
-        if ((cfg.tune_mem & 4) || mb > 192) return true;
-        if (plan.D == 3) return plan.esz == 8 && (mb < 64 || cfg.nx % (kBinTX / 2) == 0);
-        return mb > 24;
-    }
+    bool defers() const { return mode() == 2 && deferred(cfg, plan); }
 };
 
 struct lbm_batch {
@@ -529,12 +555,7 @@ struct lbm_batch {
 
 namespace {
 
-// 2-D binomial closures of at most one QoI of each kind and no mean-profile
-// QoIs form their sums in the chains' launch (k_chain_pair).
-int pair_closure(const lbm_ctx* c)
-{
-    return c->plan.D == 2 && c->cur.nsa > 0 && !c->cur.kf && c->cur.nmp == 0 && c->cur.nzb <= 1 && c->cur.nsa - c->cur.nzb <= 1;
-}
+int pair_closure(const lbm_ctx* c) { return pair_shape(c->plan, c->cur); }
 
 // The member record's fields that follow the closure mode.
 void refresh_member(lbm_ctx* c)

@@ -21,6 +21,7 @@
 
 namespace lbm {
 int set_error(int code, const char* msg);
+void tuned_launches(const lbm_config* cfg, const lbm_closure* closure, bool* tiled, bool* reduce);
 }
 
 namespace {
@@ -39,29 +40,35 @@ lbm_config with(const lbm_config* cfg, const Cand& k)
     return c;
 }
 
-// The values each coordinate may take (0: the library's automatic choice).
-// Runs without a closure launch none of the tuned kernels.
-void axes(const lbm_config* cfg, const lbm_closure* cl, std::vector<int>& btx, std::vector<int>& zc,
+// The values each coordinate may take (0: the library's automatic choice);
+// all: also those of launches that the run does not make (the arena covers
+// them).  Tile width and z chunk are the tiled stream-collide's, which runs
+// with the SGS change kept as records (3-D), the cells per thread the
+// reduce's.  Runs without a closure launch neither.
+void axes(const lbm_config* cfg, const lbm_closure* cl, bool all, std::vector<int>& btx, std::vector<int>& zc,
           std::vector<int>& cpt)
 {
     btx = {0};
     zc = {0};
     cpt = {0};
     if (!cl) return;
-    if (cfg->lattice == LBM_D3Q19) {
+    bool tiled = true, reduce = true;
+    if (!all) lbm::tuned_launches(cfg, cl, &tiled, &reduce);
+    if (tiled && cfg->lattice == LBM_D3Q19) {
         btx.push_back(32);
         if (cfg->nx % 64 == 0) btx.push_back(64);
         for (int z : {1, 2, 4, 8, 16})
             if (z <= cfg->nz) zc.push_back(z);
     }
-    cpt = {0, 1, 2, 4, 8};
+    if (reduce) cpt = {0, 1, 2, 4, 8};
 }
 
 std::string key_of(const lbm_config* cfg, const lbm_closure* cl)
 {
     char dev[128] = "unknown";
     lbm_device_tag(dev, sizeof dev);
-    std::string k = "lbm-tune-v1 dev=" + std::string(dev);
+    // (v1: tile width and z planes of the binomial passes)
+    std::string k = "lbm-tune-v2 dev=" + std::string(dev);
     for (char& ch : k)
         if (ch == '\t' || ch == '\n') ch = ' ';
     char buf[256];
@@ -153,7 +160,7 @@ size_t lbm_autotune_bytes(const lbm_config* cfg, const lbm_closure* closure)
 {
     if (!cfg) return 0;
     std::vector<int> bt, zc, cp;
-    axes(cfg, closure, bt, zc, cp);
+    axes(cfg, closure, true, bt, zc, cp);
     size_t most = 0;
     for (int b : bt)
         for (int z : zc)
@@ -192,7 +199,7 @@ int lbm_autotune(const lbm_config* cfg, const lbm_closure* closure, void* dev_ar
         u0[i] = 1e-3 * ((double)(x >> 11) * (1.0 / 9007199254740992.0) - 0.5);
     }
     std::vector<int> bt, zc, cp;
-    axes(cfg, closure, bt, zc, cp);
+    axes(cfg, closure, false, bt, zc, cp);
     std::vector<std::pair<Cand, double>> seen;
     auto eval = [&](const Cand& k) -> double {
         for (const auto& s : seen)
