@@ -411,10 +411,11 @@ void lbm_server_destroy(lbm_server* s);
 /* Per-phase timing for measurement: runs nsteps steps eagerly on the context
  * stream with HIP events between the kernel phases and returns the mean
  * duration per step of each phase in ms[6]: stream-collide (with the WALE
- * moments pass), curl, filters (binomial chains, or the kernel-filter pass
- * program), reduce, cross-block sums and solve, apply (plain runs with
+ * moments pass), curl, filters (binomial chains, or the kernel filters and
+ * Fourier bands), reduce, cross-block sums and solve, apply (plain runs with
  * records: their diagnostics in the last slot); launches[6] (nullable)
- * receives the kernel launches per step of each phase.  Advances the run. */
+ * receives the kernel launches per step of each phase, a hipFFT transform
+ * counted as one.  Advances the run. */
 int lbm_profile_phases(lbm_ctx* ctx, long nsteps, double* ms, int* launches);
 
 /* Test hooks of the device random-number generator (allocate their own

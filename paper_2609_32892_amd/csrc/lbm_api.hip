@@ -1917,7 +1917,9 @@ int lbm_profile_phases(lbm_ctx* c, long nsteps, double* ms, int* launches)
         const int m = g.mode;
         launches[0] = 1 + (g.substrate == LBM_WALE ? 1 : 0);
         launches[1] = m == 2 && g.nkfil > 0 && g.any_z ? 1 : 0;
-        launches[2] = m == 2 ? (g.kf ? (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) : (g.nbc > 0 ? 1 : 0)) : 0;
+        // kernel filters: two or four; Fourier bands: three and the two transforms
+        if (m == 2 && g.kf) launches[2] = (g.nkfil > 0 ? (g.lattice == LBM_D2Q9 ? 2 : 4) : 0) + (g.fprog ? 5 : 0);
+        else launches[2] = m == 2 && g.nbc > 0 ? 1 : 0;
         launches[3] = m == 2 && !g.pair ? 1 : 0;   // (k_chain_pair forms the sums)
         launches[4] = m == 2 ? (fused_solve(g) ? 1 : 2) : 0;   // cross-block sums, solve (unless the apply forms it)
         launches[5] = m == 2 ? 1 : (m == 1 ? 2 : 0);
