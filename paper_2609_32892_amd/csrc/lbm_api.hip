@@ -61,7 +61,7 @@ void filter_poly(int f, double r[3])
 }
 
 struct ClosureShape {
-    int nq = 0, nsa = 0, nmp = 0, jv = 0, jw = 0, has_z = 0, has_e = 0, nbands = 0;
+    int nq = 0, nsa = 0, nmp = 0, jv = 0, jw = 0, has_z = 0, nbands = 0;
     int h = 0, nhc = 0;   // LRS history length; k_sum workgroups of its product
     int kf = 0;           // E/Z QoIs use the kernel filters (materialised sensitivities)
     int nzb = 0;          // Z QoIs
@@ -122,7 +122,7 @@ int closure_shape(const lbm_config* cfg, const lbm_closure* cl, ClosureShape* ou
         const lbm_qoi_spec& q = cl->q[k];
         if (q.kind == LBM_QOI_E || q.kind == LBM_QOI_Z) {
             const int p = s.kf ? 0 : 2 * filter_deg(q.filter);
-            if (q.kind == LBM_QOI_E) { s.jv = std::max(s.jv, p); s.has_e = 1; }
+            if (q.kind == LBM_QOI_E) s.jv = std::max(s.jv, p);
             else { s.jw = std::max(s.jw, p); s.has_z = 1; s.nzb++; }
             s.nsa++;
             if (s.kf && q.filter != LBM_FILT_FOURIER) {
@@ -799,10 +799,7 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         p.nsa = cs.nsa;
         p.nmp = cs.nmp;
         p.nbands = cl->nbands;
-        p.jv = cs.jv;
-        p.jw = cs.jw;
         p.has_z = cs.has_z;
-        p.has_e = cs.has_e;
         p.spinup = cl->spinup;
         p.seed = cl->seed;
         // the E/Z QoIs in order of kind, E first

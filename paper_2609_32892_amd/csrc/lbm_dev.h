@@ -45,8 +45,8 @@ constexpr int kMaxRad = 12;     // kernel filters: largest radius of a 1-D facto
 // Constant closure parameters (written by the host at set_closure).
 struct DevParam {
     int nq, mode, nsa, nmp;
-    int nbands, have_scale, nref, jv;  // jv: highest power of B applied to v
-    int jw, has_z, has_e, h;           // jw: highest power applied to curl v; h: LRS history length
+    int nbands, have_scale, nref;
+    int has_z, h;                      // h: LRS history length
     int nhc, kf;                       // workgroups of the history product (k_sum); kernel filters
     long long spinup;
     unsigned long long seed;
@@ -54,7 +54,7 @@ struct DevParam {
     int sa_kind[kMaxSA];               // 0 E, 1 Z
     int mp_slot[kMaxQ];                // user index of each MP QoI
     int mp_band[kMaxQ];
-    int nk[2], ks[2][kMaxSA];          // binomial closures: the E (Z) QoIs, their indices
+    int nk[2], ks[2][kMaxSA];          // the E (Z) QoIs, their indices
     // R = sum_j r[j] B^j, R R = sum_j rr[j] B^j, scaled for the chains' powers: times 4^(-D j), Z: and 1/2
     double r[kMaxSA][3];
     double rr[kMaxSA][kMaxPow + 1];

@@ -11,7 +11,8 @@
 //              predictor populations and rho, v* = v^{p,n*}.
 //   k_step_t   the same on 2.5-D tiles, adding during the pull the SGS change
 //              the previous step recorded per cell (grids whose populations
-//              exceed the L2s).
+//              exceed the Infinity Cache, and smaller ones by lattice and
+//              precision: FP64 channels, 2-D from 24 MB).
 //   k_chain    binomial closures (Sec. 4.1): from v* the sensitivities
 //              R R v* of the E QoIs, U = R R w of the Z QoIs (w = curl v*) and
 //              the QoI sums, every power of B on chip.
@@ -178,7 +179,11 @@ __device__ __forceinline__ size_t pop_at64(int i, size_t c)
 // that are not whole lines (wt = 2, k_step_t): a line's two parts then come
 // from two workgroups, non-temporally each goes out by itself, a plain store
 // leaves it to the L2 to join them (tiled stream-collide, FP32 230 x 130 x 130
-// 344 -> 216 us; FP64 1001 x 1003, whole step 94 -> 84 us).
+// 344 -> 216 us; FP64 1001 x 1003, whole step 94 -> 84 us).  With 64-bit offsets
+// k_step_t always stores plainly: on rows of whole lines that is level with
+// non-temporal stores (step, non-temporal and plain: 384 x 192 x 192 1766 and
+// 1771 us, 320 x 160 x 160 1033 and 1035, FP64 256 x 128 x 128 991 and 993,
+// 2048 x 2048 199 and 195), so one form serves both.
 template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v)
 {
