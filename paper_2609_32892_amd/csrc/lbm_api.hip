@@ -792,7 +792,11 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
         if (cs.h > 0 && cl->spinup < c->host_step + cs.h)
             return fail(LBM_EINVAL, "closure: spinup must be at least the step count plus the history length");
     }
+    // (before the first upload: a closure that is refused leaves the one in
+    // place, its filter jobs and band weights included, as it was)
     DevParam p{};
+    if (cl && cl->mode == LBM_CLOSURE_LRS && !cholesky_host(cl->Sigma, cl->nq, p.L, kMaxQ))
+        return fail(LBM_EINVAL, "closure: Sigma is not SPD");
     if (cl) {
         p.nq = cl->nq;
         p.mode = cl->mode;
@@ -871,7 +875,6 @@ int apply_closure(lbm_ctx* c, const lbm_closure* cl)
                 p.chist = c->chist_dev;
             }
             for (int k = 0; k < nq; ++k) p.mu[k] = cl->mu ? cl->mu[k] : 0.0;
-            if (!cholesky_host(cl->Sigma, nq, p.L, kMaxQ)) return fail(LBM_EINVAL, "closure: Sigma is not SPD");
             if (cl->scale) {
                 p.have_scale = 1;
                 for (int k = 0; k < nq; ++k) p.scale[k] = cl->scale[k];
