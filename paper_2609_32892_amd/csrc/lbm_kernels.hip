@@ -1474,14 +1474,14 @@ __device__ __forceinline__ void chain_pair(KMember& m, KParam* prm, int tile)
         if (ne) {
             st_fld_at(kV, c, ve[0][r], WT);
             st_fld_at(kV + sN, c, ve[1][r], WT);
-            acc[2] += (double)fma_(ve[1][r], ve[1][r], ve[0][r] * ve[0][r]);
+            acc[2] += (double)fma_(ve[0][r], ve[0][r], ve[1][r] * ve[1][r]);
         }
         if (nz) {
             st_fld_at(kV + (size_t)(2 * ne) * sN, c, z0, WT);
             st_fld_at(kV + (size_t)(2 * ne + 1) * sN, c, z1, WT);
-            acc[4] += (double)fma_(z1, z1, z0 * z0);
+            acc[4] += (double)fma_(z0, z0, z1 * z1);
         }
-        if (ne && nz) acc[3] += (double)fma_(ve[1][r], z1, ve[0][r] * z0);
+        if (ne && nz) acc[3] += (double)fma_(ve[0][r], z0, ve[1][r] * z1);
     }
 #pragma unroll
     for (int k = 0; k < 5; ++k) acc[k] = wave_sum(acc[k]);
@@ -1662,9 +1662,9 @@ __global__ __launch_bounds__(kBlock, (reduce_waves<T, ME, MZ, KF>())) void k_red
             for (int t2 = s; t2 < MAXSA; ++t2, ++g) {
                 // (contracted alike in every variant: a batch may take another
                 // one than a member alone)
-                T d = V[s][0] * V[t2][0];
-#pragma unroll
-                for (int a = 1; a < D; ++a) d = fma_(V[s][a], V[t2][a], d);
+                T d = s == t2 ? fma_(V[s][0], V[s][0], V[s][1] * V[s][1])
+                              : fma_(V[s][1], V[t2][1], V[s][0] * V[t2][0]);
+                if (D == 3) d = fma_(V[s][D - 1], V[t2][D - 1], d);
                 acc[NQ + g] += (double)d;
             }
         if (hasmp) {
