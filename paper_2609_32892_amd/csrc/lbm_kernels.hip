@@ -993,7 +993,7 @@ __global__ __launch_bounds__(kBlock) void k_curl(const DevMember* __restrict__ m
 // moved 260.  Bound by its vector instructions (half of the time; half of
 // those form the sensitivities and densities) and by the stores of row
 // segments that are not whole lines; measured on MI355X: 31.8 us in four
-// launches -> 23 us on 96 x 48 x 48, 781 -> 514 us on 384 x 192 x 192 (352 us
+// launches -> 24 us on 96 x 48 x 48, 781 -> 514 us on 384 x 192 x 192 (352 us
 // with the stores left out); on 256 x 256 two launches of 4.6 us -> one of 5.
 // The stores are plain ones: neighbouring tiles share lines, which the L2
 // merges (non-temporal 624 us, written through 2 us slower on 96 x 48 x 48).
@@ -1655,18 +1655,22 @@ __global__ __launch_bounds__(kBlock, (reduce_waves<T, ME, MZ, KF>())) void k_red
                 acc[s] += qd;
             }
         }
+        // (multiply-adds by hand, so that every variant rounds alike: a batch may
+        // take another one than a member alone)
         int g = 0;
 #pragma unroll
-        for (int s = 0; s < MAXSA; ++s)
+        for (int s = 0; s < MAXSA; ++s) {
+            T d = fma_(V[s][0], V[s][0], V[s][1] * V[s][1]);
+            if (D == 3) d = fma_(V[s][D - 1], V[s][D - 1], d);
+            acc[NQ + g++] += (double)d;
 #pragma unroll
-            for (int t2 = s; t2 < MAXSA; ++t2, ++g) {
-                // (contracted alike in every variant: a batch may take another
-                // one than a member alone)
-                T d = s == t2 ? fma_(V[s][0], V[s][0], V[s][1] * V[s][1])
-                              : fma_(V[s][1], V[t2][1], V[s][0] * V[t2][0]);
-                if (D == 3) d = fma_(V[s][D - 1], V[t2][D - 1], d);
+            for (int t2 = s + 1; t2 < MAXSA; ++t2, ++g) {
+                d = V[s][0] * V[t2][0];
+#pragma unroll
+                for (int a = 1; a < D; ++a) d = fma_(V[s][a], V[t2][a], d);
                 acc[NQ + g] += (double)d;
             }
+        }
         if (hasmp) {
             acc[NQ + NG] += (double)v0[0];
 #pragma unroll
@@ -3107,9 +3111,9 @@ void launch_to(const LaunchGroup& g, hipStream_t st, int flip, hipEvent_t* ev)
 #define LBM_REDUCE_KIND(KFV)                                               \
     do {                                                                   \
         if (g.maxe <= 1 && g.maxz <= 1) LBM_REDUCE(1, 1, KFV);             \
-        else if (g.maxe <= 3 && g.maxz == 0) LBM_REDUCE(3, 0, KFV);        \
-        else if (g.maxe <= 3 && g.maxz <= 3) LBM_REDUCE(3, 3, KFV);        \
+        else if (g.maxz == 0 && g.maxe <= 3) LBM_REDUCE(3, 0, KFV);        \
         else if (g.maxz == 0) LBM_REDUCE(8, 0, KFV);                       \
+        else if (g.maxe <= 3 && g.maxz <= 3) LBM_REDUCE(3, 3, KFV);        \
         else if (g.maxe <= 4 && g.maxz <= 4) LBM_REDUCE(4, 4, KFV);        \
         else if (g.maxsa <= 6) LBM_REDUCE(0, 6, KFV);                      \
         else LBM_REDUCE(0, 8, KFV);                                        \
